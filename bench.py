@@ -32,7 +32,7 @@ sys.path.insert(0, ROOT)
 METRIC = "Dslash HBM GB/s (% roofline); solves/s + p99 latency, mixed vs FP64 at r=1e-11"
 HBM_PEAK_GBS = 8000.0
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_hop_kernels_24c48_12rhs.json")
-KERNEL_SOURCES = ["paper_1006_4028_amd/csrc/hop.hip", "paper_1006_4028_amd/csrc/dp_device.h",
+KERNEL_SOURCES = ["paper_1006_4028_amd/csrc/hop_kernels.h", "paper_1006_4028_amd/csrc/dp_device.h",
                   "paper_1006_4028_amd/csrc/dp_common.h"]
 
 

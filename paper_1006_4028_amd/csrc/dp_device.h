@@ -1,6 +1,8 @@
 // Device-side helpers: complex arithmetic, field loads/stores per storage
 // format, geometry, and the fused block reduction with its finalisers.
 #pragma once
+#include <type_traits>
+
 #include "dp_common.h"
 
 namespace dp {
@@ -26,17 +28,39 @@ __device__ __forceinline__ cx<R> cjmul(cx<R> a, cx<R> b) { return {a.x * b.x + a
 // i * a
 template <typename R>
 __device__ __forceinline__ cx<R> ti(cx<R> a) { return {-a.y, a.x}; }
-// a += b * c
+__device__ __forceinline__ float fmar(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fmar(double a, double b, double c) { return __builtin_fma(a, b, c); }
+// a += b * c.  FP32: two fused multiply-adds a component, written out (the
+// compiler's contraction within an expression takes three instructions: it
+// cannot fuse across the two products).  FP64: the pair of products is formed
+// first, three instructions with one rounding less at the magnitude of a (the
+// FP64 kernels wait for memory, not for instructions).
 template <typename R>
 __device__ __forceinline__ void cfma(cx<R>& a, cx<R> b, cx<R> c) {
-  a.x += b.x * c.x - b.y * c.y;
-  a.y += b.x * c.y + b.y * c.x;
+  if constexpr (sizeof(R) == 8) {
+    a.x += b.x * c.x - b.y * c.y;
+    a.y += b.x * c.y + b.y * c.x;
+  } else {
+    a.x = fmar(-b.y, c.y, fmar(b.x, c.x, a.x));
+    a.y = fmar(b.y, c.x, fmar(b.x, c.y, a.y));
+  }
 }
 // a += conj(b) * c
 template <typename R>
 __device__ __forceinline__ void cjfma(cx<R>& a, cx<R> b, cx<R> c) {
-  a.x += b.x * c.x + b.y * c.y;
-  a.y += b.x * c.y - b.y * c.x;
+  if constexpr (sizeof(R) == 8) {
+    a.x += b.x * c.x + b.y * c.y;
+    a.y += b.x * c.y - b.y * c.x;
+  } else {
+    a.x = fmar(b.y, c.y, fmar(b.x, c.x, a.x));
+    a.y = fmar(-b.y, c.x, fmar(b.x, c.y, a.y));
+  }
+}
+// a += s * b, s real
+template <typename R>
+__device__ __forceinline__ void rfma(cx<R>& a, R s, cx<R> b) {
+  a.x = fmar(s, b.x, a.x);
+  a.y = fmar(s, b.y, a.y);
 }
 
 template <int P>
@@ -76,6 +100,39 @@ __device__ __forceinline__ int xcd_tile(int b, int nb) {
   const int q = nb >> 3, r = nb & 7;
   const int xcd = b & 7, k = b >> 3;
   return xcd * q + (xcd < r ? xcd : r) + k;
+}
+
+// ------------------------------------------------------------ addressing
+
+// Element i of the component array that starts at base, which is the same for
+// the whole wave: the address is a scalar base plus a 32-bit lane offset, so a
+// load takes no 64-bit vector arithmetic (a parity field's component array is
+// below 4 GiB: at most 2^30 / 12 sites of 16 bytes).
+template <typename T>
+__device__ __forceinline__ const T* at(const T* base, int i) {
+  return reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + (size_t)((unsigned)i * (unsigned)sizeof(T)));
+}
+template <typename T>
+__device__ __forceinline__ T* at(T* base, int i) {
+  return reinterpret_cast<T*>(reinterpret_cast<char*>(base) + (size_t)((unsigned)i * (unsigned)sizeof(T)));
+}
+
+// A pointer read from memory that is the same for the whole wave.
+template <typename T>
+__device__ __forceinline__ T* uniform_ptr(T* p) {
+  const unsigned long long u = (unsigned long long)p;
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)u), hi = __builtin_amdgcn_readfirstlane((unsigned)(u >> 32));
+  return reinterpret_cast<T*>(((unsigned long long)hi << 32) | lo);
+}
+
+// The base in scalar registers, opaque: the compiler then cannot merge it with
+// the lane offset into 64-bit vector additions (base must be the same for the
+// whole wave).
+template <typename T>
+__device__ __forceinline__ T* scalar_base(T* base) {
+  auto g = (__attribute__((address_space(1))) T*)uniform_ptr(base);  // global: else the accesses become flat ones
+  asm("" : "+s"(g));
+  return (T*)g;
 }
 
 // ------------------------------------------------------------ streamed access
@@ -175,18 +232,12 @@ struct SpinorIO;
 
 template <>
 struct SpinorIO<F64> {
-  // the components and the factor that multiplies them (1 without a scale)
-  template <typename R>
-  __device__ static __forceinline__ R load_unscaled(const SpinorRef& f, int slot, int i, int Vh, cx<R> (&s)[12]) {
-    load(f, slot, i, Vh, s);
-    return R(1);
-  }
   template <bool NT = false, typename R>
   __device__ static __forceinline__ void load(const SpinorRef& f, int slot, int i, int Vh, cx<R> (&s)[12]) {
     const double2* b = static_cast<const double2*>(f.data) + (long)slot * f.slot_stride;
 #pragma unroll
     for (int c = 0; c < 12; ++c) {
-      const double2 v = vld<NT>(b + (long)c * Vh + i);
+      const double2 v = vld<NT>(at(b + (long)c * Vh, i));
       s[c] = cx<R>{(R)v.x, (R)v.y};
     }
   }
@@ -194,23 +245,18 @@ struct SpinorIO<F64> {
   __device__ static __forceinline__ void store(const SpinorRef& f, int slot, int i, int Vh, const cx<R> (&s)[12]) {
     double2* b = static_cast<double2*>(f.data) + (long)slot * f.slot_stride;
 #pragma unroll
-    for (int c = 0; c < 12; ++c) vst<NT>(b + (long)c * Vh + i, make_double2((double)s[c].x, (double)s[c].y));
+    for (int c = 0; c < 12; ++c) vst<NT>(at(b + (long)c * Vh, i), make_double2((double)s[c].x, (double)s[c].y));
   }
 };
 
 template <>
 struct SpinorIO<F32> {
-  template <typename R>
-  __device__ static __forceinline__ R load_unscaled(const SpinorRef& f, int slot, int i, int Vh, cx<R> (&s)[12]) {
-    load(f, slot, i, Vh, s);
-    return R(1);
-  }
   template <bool NT = false, typename R>
   __device__ static __forceinline__ void load(const SpinorRef& f, int slot, int i, int Vh, cx<R> (&s)[12]) {
     const float4* b = static_cast<const float4*>(f.data) + (long)slot * f.slot_stride;
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
-      const float4 v = vld<NT>(b + (long)k * Vh + i);
+      const float4 v = vld<NT>(at(b + (long)k * Vh, i));
       s[2 * k] = cx<R>{(R)v.x, (R)v.y};
       s[2 * k + 1] = cx<R>{(R)v.z, (R)v.w};
     }
@@ -220,7 +266,7 @@ struct SpinorIO<F32> {
     float4* b = static_cast<float4*>(f.data) + (long)slot * f.slot_stride;
 #pragma unroll
     for (int k = 0; k < 6; ++k)
-      vst<NT>(b + (long)k * Vh + i, make_float4((float)s[2 * k].x, (float)s[2 * k].y, (float)s[2 * k + 1].x,
+      vst<NT>(at(b + (long)k * Vh, i), make_float4((float)s[2 * k].x, (float)s[2 * k].y, (float)s[2 * k + 1].x,
                                                (float)s[2 * k + 1].y));
   }
 };
@@ -236,29 +282,13 @@ __device__ __forceinline__ unsigned f2h(float a, float b) {
 
 template <>
 struct SpinorIO<F16> {
-  // the stored binary16 values (|v| <= 1) and the site's scale
-  template <typename R>
-  __device__ static __forceinline__ R load_unscaled(const SpinorRef& f, int slot, int i, int Vh, cx<R> (&s)[12]) {
-    const uint4* b = static_cast<const uint4*>(f.data) + (long)slot * f.slot_stride;
-    const float sc = f.scale[(long)slot * f.scale_stride + i];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const uint4 v = b[(long)k * Vh + i];
-      const float2 a0 = h2f(v.x), a1 = h2f(v.y), a2 = h2f(v.z), a3 = h2f(v.w);
-      s[4 * k + 0] = cx<R>{(R)a0.x, (R)a0.y};
-      s[4 * k + 1] = cx<R>{(R)a1.x, (R)a1.y};
-      s[4 * k + 2] = cx<R>{(R)a2.x, (R)a2.y};
-      s[4 * k + 3] = cx<R>{(R)a3.x, (R)a3.y};
-    }
-    return (R)sc;
-  }
   template <bool NT = false, typename R>
   __device__ static __forceinline__ void load(const SpinorRef& f, int slot, int i, int Vh, cx<R> (&s)[12]) {
     const uint4* b = static_cast<const uint4*>(f.data) + (long)slot * f.slot_stride;
-    const float sc = vld<NT>(f.scale + (long)slot * f.scale_stride + i);
+    const float sc = vld<NT>(at(f.scale + (long)slot * f.scale_stride, i));
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-      const uint4 v = vld<NT>(b + (long)k * Vh + i);
+      const uint4 v = vld<NT>(at(b + (long)k * Vh, i));
       float2 a0 = h2f(v.x), a1 = h2f(v.y), a2 = h2f(v.z), a3 = h2f(v.w);
       s[4 * k + 0] = cx<R>{(R)(a0.x * sc), (R)(a0.y * sc)};
       s[4 * k + 1] = cx<R>{(R)(a1.x * sc), (R)(a1.y * sc)};
@@ -287,7 +317,7 @@ struct SpinorIO<F16> {
     // far below the FP16 resolution.
     if (!(m >= 1.17549435e-38f)) m = 0.f;  // FLT_MIN
     const float inv = m > 0.f ? 1.0f / m : 0.f;
-    vst<NT>(f.scale + (long)slot * f.scale_stride + i, m);
+    vst<NT>(at(f.scale + (long)slot * f.scale_stride, i), m);
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
       uint4 v;
@@ -295,7 +325,7 @@ struct SpinorIO<F16> {
       v.y = f2h((float)s[4 * k + 1].x * inv, (float)s[4 * k + 1].y * inv);
       v.z = f2h((float)s[4 * k + 2].x * inv, (float)s[4 * k + 2].y * inv);
       v.w = f2h((float)s[4 * k + 3].x * inv, (float)s[4 * k + 3].y * inv);
-      vst<NT>(b + (long)k * Vh + i, v);
+      vst<NT>(at(b + (long)k * Vh, i), v);
       if constexpr (DEC) {
         const float2 a0 = h2f(v.x), a1 = h2f(v.y), a2 = h2f(v.z), a3 = h2f(v.w);
         q[4 * k + 0] = cx<R>{(R)(a0.x * m), (R)(a0.y * m)};
@@ -309,9 +339,9 @@ struct SpinorIO<F16> {
 
 // ------------------------------------------------------------ raw spinors
 //
-// A neighbour spinor as stored (no conversion), so that the loads of several
-// neighbours can be issued before the first is used; decode() converts it
-// and returns the factor its components carry (the FP16 per-site scale, else 1).
+// A spinor as stored (no conversion), so that the loads of several
+// neighbours can be issued before the first is used.  The slot is the same for
+// the whole wave.
 
 template <int P>
 struct RawSpinor;
@@ -329,49 +359,34 @@ struct RawSpinor<F16> {
   float sc;
 };
 
-template <int P>
+template <int P, bool NT = false>
 __device__ __forceinline__ void load_raw_spinor(const SpinorRef& f, int slot, int i, int Vh, RawSpinor<P>& r) {
-  if constexpr (P == F64) {
-    const double2* b = static_cast<const double2*>(f.data) + (long)slot * f.slot_stride;
+  using E = typename std::remove_reference<decltype(r.v[0])>::type;
+  constexpr int n = sizeof(r.v) / sizeof(r.v[0]);
+  const E* b = static_cast<const E*>(f.data) + (long)slot * f.slot_stride;
 #pragma unroll
-    for (int c = 0; c < 12; ++c) r.v[c] = b[(long)c * Vh + i];
-  } else if constexpr (P == F32) {
-    const float4* b = static_cast<const float4*>(f.data) + (long)slot * f.slot_stride;
-#pragma unroll
-    for (int k = 0; k < 6; ++k) r.v[k] = b[(long)k * Vh + i];
-  } else {
-    const uint4* b = static_cast<const uint4*>(f.data) + (long)slot * f.slot_stride;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) r.v[k] = b[(long)k * Vh + i];
-    r.sc = f.scale[(long)slot * f.scale_stride + i];
-  }
+  for (int k = 0; k < n; ++k) r.v[k] = vld<NT>(at(scalar_base(b + (long)k * Vh), i));
+  if constexpr (P == F16) r.sc = vld<NT>(at(scalar_base(f.scale + (long)slot * f.scale_stride), i));
 }
 
-// the same values and factor SpinorIO<P>::load_unscaled gives
-template <int P, typename R>
-__device__ __forceinline__ R decode_spinor(const RawSpinor<P>& r, cx<R> (&s)[12]) {
-  if constexpr (P == F64) {
-#pragma unroll
-    for (int c = 0; c < 12; ++c) s[c] = cx<R>{(R)r.v[c].x, (R)r.v[c].y};
-    return R(1);
-  } else if constexpr (P == F32) {
-#pragma unroll
-    for (int k = 0; k < 6; ++k) {
-      s[2 * k] = cx<R>{(R)r.v[k].x, (R)r.v[k].y};
-      s[2 * k + 1] = cx<R>{(R)r.v[k].z, (R)r.v[k].w};
-    }
-    return R(1);
-  } else {
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const float2 a0 = h2f(r.v[k].x), a1 = h2f(r.v[k].y), a2 = h2f(r.v[k].z), a3 = h2f(r.v[k].w);
-      s[4 * k + 0] = cx<R>{(R)a0.x, (R)a0.y};
-      s[4 * k + 1] = cx<R>{(R)a1.x, (R)a1.y};
-      s[4 * k + 2] = cx<R>{(R)a2.x, (R)a2.y};
-      s[4 * k + 3] = cx<R>{(R)a3.x, (R)a3.y};
-    }
-    return (R)r.sc;
-  }
+typedef _Float16 h2v __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ h2v as_h2(unsigned u) { return __builtin_bit_cast(h2v, u); }
+
+// component c as stored (FP16: the value divided by the site's scale)
+__device__ __forceinline__ cx<double> raw_comp(const RawSpinor<F64>& r, int c) { return {r.v[c].x, r.v[c].y}; }
+__device__ __forceinline__ cx<float> raw_comp(const RawSpinor<F32>& r, int c) {
+  const float4 q = r.v[c >> 1];
+  return (c & 1) ? cx<float>{q.z, q.w} : cx<float>{q.x, q.y};
+}
+__device__ __forceinline__ h2v raw_comp(const RawSpinor<F16>& r, int c) {
+  const uint4 q = r.v[c >> 2];
+  return as_h2((c & 3) == 0 ? q.x : (c & 3) == 1 ? q.y : (c & 3) == 2 ? q.z : q.w);
+}
+// the factor the stored components carry
+template <int P>
+__device__ __forceinline__ float raw_scale(const RawSpinor<P>& r) {
+  if constexpr (P == F16) return r.sc;
+  else return 1.f;
 }
 
 // ------------------------------------------------------------ links
@@ -385,7 +400,7 @@ struct LinkIO<F64> {
     const double2* b = static_cast<const double2*>(base) + (long)mu * 9 * Vh;
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
-      const double2 v = vld<NT>(b + (long)k * Vh + i);
+      const double2 v = vld<NT>(at(b + (long)k * Vh, i));
       u[k] = cx<R>{(R)v.x, (R)v.y};
     }
   }
@@ -397,7 +412,7 @@ struct LinkIO<F32> {
     const float2* b = static_cast<const float2*>(base) + (long)mu * 9 * Vh;
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
-      const float2 v = vld<NT>(b + (long)k * Vh + i);
+      const float2 v = vld<NT>(at(b + (long)k * Vh, i));
       u[k] = cx<R>{(R)v.x, (R)v.y};
     }
   }
@@ -409,7 +424,7 @@ struct LinkIO<F16> {
     const unsigned* b = static_cast<const unsigned*>(base) + (long)mu * 9 * Vh;
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
-      const float2 v = h2f(vld<NT>(b + (long)k * Vh + i));
+      const float2 v = h2f(vld<NT>(at(b + (long)k * Vh, i)));
       u[k] = cx<R>{(R)v.x, (R)v.y};
     }
   }
@@ -439,13 +454,13 @@ struct CloverIO<F64> {
     for (int h = 0; h < 2; ++h) {
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
-        const double2 v = b[(long)(h * 18 + k) * Vh + i];
+        const double2 v = *at(b + (long)(h * 18 + k) * Vh, i);
         B[h].d[2 * k] = (R)v.x;
         B[h].d[2 * k + 1] = (R)v.y;
       }
 #pragma unroll
       for (int k = 0; k < 15; ++k) {
-        const double2 v = b[(long)(h * 18 + 3 + k) * Vh + i];
+        const double2 v = *at(b + (long)(h * 18 + 3 + k) * Vh, i);
         B[h].o[k] = cx<R>{(R)v.x, (R)v.y};
       }
     }
@@ -462,7 +477,7 @@ struct CloverIO<F32> {
     const float4* b = static_cast<const float4*>(base);
 #pragma unroll
     for (int k = 0; k < 18; ++k) {
-      const float4 v = vld<NT>(b + (long)k * Vh + i);
+      const float4 v = vld<NT>(at(b + (long)k * Vh, i));
       r[4 * k] = v.x; r[4 * k + 1] = v.y; r[4 * k + 2] = v.z; r[4 * k + 3] = v.w;
     }
     return 1.f;
@@ -493,12 +508,12 @@ struct CloverIO<F16> {
     const uint4* b = static_cast<const uint4*>(base);
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
-      const uint4 v = vld<NT>(b + (long)k * Vh + i);
+      const uint4 v = vld<NT>(at(b + (long)k * Vh, i));
       float2 a0 = h2f(v.x), a1 = h2f(v.y), a2 = h2f(v.z), a3 = h2f(v.w);
       r[8 * k + 0] = a0.x; r[8 * k + 1] = a0.y; r[8 * k + 2] = a1.x; r[8 * k + 3] = a1.y;
       r[8 * k + 4] = a2.x; r[8 * k + 5] = a2.y; r[8 * k + 6] = a3.x; r[8 * k + 7] = a3.y;
     }
-    return vld<NT>(scale + i);
+    return vld<NT>(at(scale, i));
   }
   template <typename R>
   __device__ static __forceinline__ void assemble(const float (&r)[72], float sc, HermBlock<R> (&B)[2]) {
@@ -520,19 +535,24 @@ struct CloverIO<F16> {
   }
 };
 
-// y = (B + shift) x on one chirality block (components 6h .. 6h+5 of the spinor)
+// y = (B + shift) x on one chirality block (components 6h .. 6h+5 of the
+// spinor); the diagonal, the largest term, is added last (the sum of the
+// others is rounded at its own magnitude).
 template <typename R>
 __device__ __forceinline__ void herm_apply(const HermBlock<R>& B, R shift, const cx<R>* x, cx<R>* y) {
+  y[0] = cmul(B.o[herm_off(0, 1)], x[1]);
 #pragma unroll
-  for (int r = 0; r < 6; ++r) y[r] = (B.d[r] + shift) * x[r];
+  for (int c = 1; c < 6; ++c) y[c] = cjmul(B.o[herm_off(0, c)], x[0]);
 #pragma unroll
   for (int r = 0; r < 6; ++r)
 #pragma unroll
     for (int c = r + 1; c < 6; ++c) {
       const cx<R> a = B.o[herm_off(r, c)];
-      cfma(y[r], a, x[c]);   // A_rc x_c
-      cjfma(y[c], a, x[r]);  // A_cr = conj(A_rc)
+      if (r > 0 || c > 1) cfma(y[r], a, x[c]);  // A_rc x_c
+      if (r > 0) cjfma(y[c], a, x[r]);          // A_cr = conj(A_rc)
     }
+#pragma unroll
+  for (int r = 0; r < 6; ++r) rfma(y[r], B.d[r] + shift, x[r]);
 }
 
 // ------------------------------------------------------------ reductions
@@ -542,6 +562,50 @@ __device__ __forceinline__ double wave_sum(double v) {
   for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
   return v;
 }
+
+// Sums of up to four values over the wave at once: each step halves the
+// number of values a lane holds (the halves of the wave, then the rows of 16
+// lanes, exchange them with one register swap per pair), and the last four
+// steps reduce within a row.  Row q of 16 lanes ends with the sum of value
+// wave_row_value(q) in every lane of it.  17 adds and 36 register moves for
+// four values, against 24 adds and 48 LDS permutes one value at a time.
+__device__ __forceinline__ double swap32_add(double a, double b) {
+  union { double d; unsigned u[2]; } x{a}, y{b};
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const auto r = __builtin_amdgcn_permlane32_swap(x.u[k], y.u[k], false, false);
+    x.u[k] = r[0];
+    y.u[k] = r[1];
+  }
+  return x.d + y.d;
+}
+__device__ __forceinline__ double swap16_add(double a, double b) {
+  union { double d; unsigned u[2]; } x{a}, y{b};
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const auto r = __builtin_amdgcn_permlane16_swap(x.u[k], y.u[k], false, false);
+    x.u[k] = r[0];
+    y.u[k] = r[1];
+  }
+  return x.d + y.d;
+}
+// a + (a of the lane N further round the row of 16)
+template <int N>
+__device__ __forceinline__ double row_ror_add(double a) {
+  union { double d; int u[2]; } x{a}, y;
+#pragma unroll
+  for (int k = 0; k < 2; ++k) y.u[k] = __builtin_amdgcn_update_dpp(0, x.u[k], 0x120 + N, 0xf, 0xf, true);
+  return x.d + y.d;
+}
+__device__ __forceinline__ double wave_sum4(double v0, double v1, double v2, double v3) {
+  double a = swap16_add(swap32_add(v0, v1), swap32_add(v2, v3));
+  a = row_ror_add<8>(a);
+  a = row_ror_add<4>(a);
+  a = row_ror_add<2>(a);
+  return row_ror_add<1>(a);
+}
+// rows 0..3 hold the sums of v0, v2, v1, v3
+__device__ __forceinline__ int wave_row_value(int row) { return ((row & 1) << 1) | (row >> 1); }
 
 // complex a / b
 __device__ __forceinline__ void cdiv(const double* a, const double* b, double* out) {

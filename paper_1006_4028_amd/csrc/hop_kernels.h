@@ -1,0 +1,825 @@
+// The alpha-hop Wilson kernels with clover epilogues (templates; one
+// translation unit per storage precision instantiates them).
+//
+// For an output site x of parity p they compute the hopping term of the
+// preconditioned operator D' = alpha (D + M) alpha^-1 (eq. linsysprec),
+//
+//   H psi(x) = -1/2 sum_mu [ c+_mu(x) (1 - gamma_mu) U_mu(x) psi(x+mu)
+//                          + c-_mu(x) (1 + gamma_mu) U_mu(x-mu)^+ psi(x-mu) ]
+//
+// where the time factors are the ratios of the modified time derivatives
+// (heavy-quark section): c+_0(x) = alpha(x0)/alpha(x0+1) and c-_0(x) =
+// alpha(x0)/alpha(x0-1), per slot, with the fermion boundary sign folded in at
+// the wrap-around (the boundary rule eq. redeftbc reduces to exactly this),
+// and the spatial factors are 1, or the same ratios of the spatial profiles
+// of the light-quark factorisation (eqs. betaa, redefcovs; periodic).
+// The adjoint hop (dag = 1) swaps the projectors and uses the reciprocal
+// ratios; it is the hopping part of gamma5 D'(1/alpha) gamma5 = D'(alpha)^+.
+//
+// Spin projection in the chiral basis, with psi = (u0, u1, l0, l1) in spin and
+// s = +1 for (1 - gamma_mu), s = -1 for (1 + gamma_mu):
+//   mu = 0: h = u + s l,                 lower = s h
+//   mu = k: h = u + s (i sigma_k) l,     lower = -s (i sigma_k) h
+// so only the two upper spins are multiplied by the link.
+//
+// One thread per output site and right-hand side ("slot").  What bounds the
+// kernels: with one slot the traffic of links and blocks; with many slots the
+// traffic of the spinors past L2 (FP64, FP32) or the instructions (FP16).
+// FP32 multiply-adds are therefore fused ones, written out; FP16 values enter
+// the arithmetic through mixed-precision multiply-adds, which convert for
+// free; the slot and with it every base address is a scalar; links and blocks
+// stay in LDS as stored.  24^3x48, 12 slots, in the solve, odd / even sites with
+// one and with four dot products, before -> with these: FP16 250 / 320 / 347 ->
+// 186 / 227 / 237 us (2040 .. 2510 -> 1330 .. 1680 instructions a wave and slot,
+// 0.74 of the issue rate), FP32 306 / 375 / 406 -> 300 / 371 / 379 us (5.1 .. 5.6
+// TB/s fetched and written).  FP64 took two launches' worth of link reads per
+// pair of slots from L2 at one or two waves per SIMD and runs the shared-tile
+// kernel now: 784 / 992 / 999 -> 645 / 849 / 864 us (6.7 TB/s past L2, of which
+// 40% are neighbours fetched again).
+#pragma once
+#include <algorithm>
+#include <cstdlib>
+
+#include "dp_device.h"
+
+namespace dp {
+
+namespace {
+
+template <typename R>
+struct Half {
+  cx<R> h[2][3];
+};
+
+// u + sg l for stored components: one add, or one mixed-precision
+// multiply-add by `one` (1.0f, opaque to the compiler, which would otherwise
+// convert and add).
+template <int SG, typename R>
+__device__ __forceinline__ R pm(R u, R l, float) {
+  return SG > 0 ? u + l : u - l;
+}
+template <int SG>
+__device__ __forceinline__ float pm(_Float16 u, _Float16 l, float one) {
+  return __builtin_fmaf(SG > 0 ? (float)l : -(float)l, one, (float)u);
+}
+
+template <int MU, int S, typename R, int P>
+__device__ __forceinline__ void project(const RawSpinor<P>& r, float one, Half<R>& o) {
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const auto u0 = raw_comp(r, a), u1 = raw_comp(r, 3 + a), l0 = raw_comp(r, 6 + a), l1 = raw_comp(r, 9 + a);
+    if constexpr (MU == 0) {
+      o.h[0][a] = cx<R>{pm<S>(u0.x, l0.x, one), pm<S>(u0.y, l0.y, one)};
+      o.h[1][a] = cx<R>{pm<S>(u1.x, l1.x, one), pm<S>(u1.y, l1.y, one)};
+    } else if constexpr (MU == 1) {  // i sigma_1 l = (i l1, i l0)
+      o.h[0][a] = cx<R>{pm<-S>(u0.x, l1.y, one), pm<S>(u0.y, l1.x, one)};
+      o.h[1][a] = cx<R>{pm<-S>(u1.x, l0.y, one), pm<S>(u1.y, l0.x, one)};
+    } else if constexpr (MU == 2) {  // i sigma_2 l = (l1, -l0)
+      o.h[0][a] = cx<R>{pm<S>(u0.x, l1.x, one), pm<S>(u0.y, l1.y, one)};
+      o.h[1][a] = cx<R>{pm<-S>(u1.x, l0.x, one), pm<-S>(u1.y, l0.y, one)};
+    } else {  // i sigma_3 l = (i l0, -i l1)
+      o.h[0][a] = cx<R>{pm<-S>(u0.x, l0.y, one), pm<S>(u0.y, l0.x, one)};
+      o.h[1][a] = cx<R>{pm<S>(u1.x, l1.y, one), pm<-S>(u1.y, l1.x, one)};
+    }
+  }
+}
+
+// acc += c * (1 - s gamma_mu)-reconstruction of colour a of the
+// link-multiplied half spinor (w0, w1)
+template <int MU, int S, typename R>
+__device__ __forceinline__ void accumulate(cx<R> (&acc)[12], int a, cx<R> w0, cx<R> w1, R c) {
+  const R p = S > 0 ? c : -c;
+  rfma(acc[a], c, w0);
+  rfma(acc[3 + a], c, w1);
+  if constexpr (MU == 0) {
+    rfma(acc[6 + a], p, w0);
+    rfma(acc[9 + a], p, w1);
+  } else if constexpr (MU == 1) {  // -s i sigma_1 w = -s (i w1, i w0)
+    rfma(acc[6 + a], -p, ti(w1));
+    rfma(acc[9 + a], -p, ti(w0));
+  } else if constexpr (MU == 2) {  // -s i sigma_2 w = -s (w1, -w0)
+    rfma(acc[6 + a], -p, w1);
+    rfma(acc[9 + a], p, w0);
+  } else {  // -s i sigma_3 w = -s (i w0, -i w1)
+    rfma(acc[6 + a], -p, ti(w0));
+    rfma(acc[9 + a], p, ti(w1));
+  }
+}
+
+// ------------------------------------------------------------ links
+
+// A link as stored; FP16 links are used as stored halves by mixed-precision
+// multiply-adds.
+template <int P>
+struct RawLink;
+template <>
+struct RawLink<F64> {
+  double2 v[9];
+};
+template <>
+struct RawLink<F32> {
+  float2 v[9];
+};
+template <>
+struct RawLink<F16> {
+  unsigned v[9];
+};
+template <int P>
+using LinkElem = typename std::remove_reference<decltype(RawLink<P>().v[0])>::type;
+
+template <int P, bool NT = false>
+__device__ __forceinline__ void load_raw_link(const void* base, int mu, int i, int Vh, RawLink<P>& r) {
+  using E = LinkElem<P>;
+  const E* b = static_cast<const E*>(base) + (long)mu * 9 * Vh;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) r.v[k] = vld<NT>(at(scalar_base(b + (long)k * Vh), i));
+}
+__device__ __forceinline__ cx<double> elem(double2 v) { return {v.x, v.y}; }
+__device__ __forceinline__ cx<float> elem(float2 v) { return {v.x, v.y}; }
+__device__ __forceinline__ h2v elem(unsigned v) { return as_h2(v); }
+
+// t = u h, t += u h (CONJ: conj(u) h), u a stored link entry
+template <bool CONJ, typename R>
+__device__ __forceinline__ cx<R> lmul(cx<R> u, cx<R> h) { return CONJ ? cjmul(u, h) : cmul(u, h); }
+template <bool CONJ, typename R>
+__device__ __forceinline__ void lfma(cx<R>& t, cx<R> u, cx<R> h) {
+  if constexpr (CONJ) cjfma(t, u, h);
+  else cfma(t, u, h);
+}
+template <bool CONJ>
+__device__ __forceinline__ void lfma(cx<float>& t, h2v u, cx<float> h) {
+  const float ux = (float)u.x, uy = CONJ ? -(float)u.y : (float)u.y;
+  t.x = __builtin_fmaf(-uy, h.y, __builtin_fmaf(ux, h.x, t.x));
+  t.y = __builtin_fmaf(uy, h.x, __builtin_fmaf(ux, h.y, t.y));
+}
+template <bool CONJ>
+__device__ __forceinline__ cx<float> lmul(h2v u, cx<float> h) {
+  cx<float> t{0.f, 0.f};
+  lfma<CONJ>(t, u, h);
+  return t;
+}
+
+// ------------------------------------------------------------ neighbours
+
+// acc += the hop from neighbour K = 2 mu (forward) or 2 mu + 1 (backward);
+// an FP16 spinor's per-site scale multiplies the hop's coefficient (the
+// projection and the link product are linear).  DAG selects the adjoint's
+// projectors at compile time.
+template <int P, int K, bool DAG>
+__device__ __forceinline__ void nb_compute(const RawSpinor<P>& raw, const RawLink<P>& rl, typename Tr<P>::R coef,
+                                           float one, cx<typename Tr<P>::R> (&acc)[12]) {
+  using R = typename Tr<P>::R;
+  constexpr int MU = K >> 1;
+  constexpr bool FWD = (K & 1) == 0;
+  constexpr int S = (DAG ? -1 : 1) * (FWD ? 1 : -1);
+  Half<R> h;
+  project<MU, S>(raw, one, h);
+  const R c = P == F16 ? coef * (R)raw_scale(raw) : coef;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    cx<R> w[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      if constexpr (FWD) {
+        w[s] = lmul<false>(elem(rl.v[3 * a]), h.h[s][0]);
+        lfma<false>(w[s], elem(rl.v[3 * a + 1]), h.h[s][1]);
+        lfma<false>(w[s], elem(rl.v[3 * a + 2]), h.h[s][2]);
+      } else {
+        w[s] = lmul<true>(elem(rl.v[a]), h.h[s][0]);
+        lfma<true>(w[s], elem(rl.v[3 + a]), h.h[s][1]);
+        lfma<true>(w[s], elem(rl.v[6 + a]), h.h[s][2]);
+      }
+    }
+    accumulate<MU, S>(acc, a, w[0], w[1], c);
+  }
+}
+
+// The eight neighbours in order through a ring of PF raw spinors: the load of
+// neighbour K + PF is issued as soon as neighbour K is used, so that PF - 1 or
+// more stay in flight (the scheduling barriers keep the compiler from moving
+// the loads).  LDSL: links from the workgroup's LDS copy lu[8][9][64] (lane =
+// site), else loaded with the spinors (forward hops from U_out at the output
+// site, backward ones from U_in at the neighbour).
+template <int P, int PF, bool DAG, bool LDSL>
+struct Neighbours {
+  using R = typename Tr<P>::R;
+  RawSpinor<P> raw[PF];
+  RawLink<P> rl[LDSL ? 1 : PF];
+
+  template <int K>
+  __device__ __forceinline__ void load(const HopArgs& a, int slot, int i, const int (&nb)[8]) {
+    load_raw_spinor<P>(a.in, slot, nb[K], a.g.Vp, raw[K % PF]);
+    if constexpr (!LDSL) {
+      if constexpr ((K & 1) == 0) load_raw_link<P>(a.U_out, K >> 1, i, a.g.Vp, rl[K % PF]);
+      else load_raw_link<P>(a.U_in, K >> 1, nb[K], a.g.Vp, rl[K % PF]);
+    }
+  }
+  template <int K>
+  __device__ __forceinline__ void fill(const HopArgs& a, int slot, int i, const int (&nb)[8]) {
+    if constexpr (K < PF) {
+      load<K>(a, slot, i, nb);
+      fill<K + 1>(a, slot, i, nb);
+    } else {
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  template <int K, typename E>
+  __device__ __forceinline__ void step(const HopArgs& a, int slot, int i, const int (&nb)[8], const R (&coef)[8],
+                                       float one, const LinkElem<P>* lu, int lane, cx<R> (&acc)[12], E& epi) {
+    if constexpr (K < 8) {
+      if constexpr (LDSL) {
+        RawLink<P> u;
+#pragma unroll
+        for (int k = 0; k < 9; ++k) u.v[k] = lu[(K * 9 + k) * 64 + lane];
+        nb_compute<P, K, DAG>(raw[K % PF], u, coef[K], one, acc);
+      } else {
+        nb_compute<P, K, DAG>(raw[K % PF], rl[K % PF], coef[K], one, acc);
+      }
+      // the sums are complete here: the compiler would otherwise put the
+      // multiply-adds of several neighbours off to the epilogue and spill
+#pragma unroll
+      for (int c = 0; c < 12; ++c) asm volatile("" : "+v"(acc[c].x), "+v"(acc[c].y));
+      if constexpr (K + PF < 8) {
+        __builtin_amdgcn_sched_barrier(0);
+        load<K + PF>(a, slot, i, nb);
+        __builtin_amdgcn_sched_barrier(0);
+      } else if constexpr (K + PF == 8) {
+        __builtin_amdgcn_sched_barrier(0);
+        epi.load(a, slot, i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      step<K + 1>(a, slot, i, nb, coef, one, lu, lane, acc, epi);
+    }
+  }
+};
+
+// ------------------------------------------------------------ epilogue
+
+// One chirality's clover block as stored: 6 diagonal reals, then the 15 upper
+// entries (FP16: halves, to be multiplied by the site's scale).
+template <int P>
+struct Blk;
+template <>
+struct Blk<F64> {
+  double2 v[18];
+  __device__ __forceinline__ double d(int r) const { return (r & 1) ? v[r >> 1].y : v[r >> 1].x; }
+  __device__ __forceinline__ cx<double> o(int k) const { return {v[3 + k].x, v[3 + k].y}; }
+};
+template <>
+struct Blk<F32> {
+  float v[36];
+  __device__ __forceinline__ float d(int r) const { return v[r]; }
+  __device__ __forceinline__ cx<float> o(int k) const { return {v[6 + 2 * k], v[7 + 2 * k]}; }
+};
+template <>
+struct Blk<F16> {
+  unsigned v[18];
+  __device__ __forceinline__ _Float16 d(int r) const { return (r & 1) ? as_h2(v[r >> 1]).y : as_h2(v[r >> 1]).x; }
+  __device__ __forceinline__ h2v o(int k) const { return as_h2(v[3 + k]); }
+};
+
+// block h of a stored field at site i (FP16 blocks straddle a 16-byte unit:
+// the middle one is read for both)
+template <int P>
+__device__ __forceinline__ void load_blk(const void* base, int h, int i, int Vh, Blk<P>& b) {
+  if constexpr (P == F64) {
+    const double2* q = static_cast<const double2*>(base);
+#pragma unroll
+    for (int k = 0; k < 18; ++k) b.v[k] = *at(scalar_base(q + (long)(18 * h + k) * Vh), i);
+  } else if constexpr (P == F32) {
+    const float4* q = static_cast<const float4*>(base);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+      const float4 t = *at(scalar_base(q + (long)(9 * h + k) * Vh), i);
+      b.v[4 * k] = t.x;
+      b.v[4 * k + 1] = t.y;
+      b.v[4 * k + 2] = t.z;
+      b.v[4 * k + 3] = t.w;
+    }
+  } else {
+    const uint4* q = static_cast<const uint4*>(base);
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+      const uint4 t = *at(scalar_base(q + (long)(4 * h + k) * Vh), i);
+      const unsigned w[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int j = 4 * k + e - 2 * h;
+        if (j >= 0 && j < 18) b.v[j] = w[e];
+      }
+    }
+  }
+}
+
+// y = (B + shift) x (FP32, FP64) or y = B x (FP16, without the scale); the
+// order of herm_apply.
+template <int P, typename R>
+__device__ __forceinline__ void blk_apply(const Blk<P>& B, R shift, const cx<R>* x, cx<R>* y) {
+  y[0] = lmul<false>(B.o(herm_off(0, 1)), x[1]);
+#pragma unroll
+  for (int c = 1; c < 6; ++c) y[c] = lmul<true>(B.o(herm_off(0, c)), x[0]);
+#pragma unroll
+  for (int r = 0; r < 6; ++r)
+#pragma unroll
+    for (int c = r + 1; c < 6; ++c) {
+      if (r > 0 || c > 1) lfma<false>(y[r], B.o(herm_off(r, c)), x[c]);  // A_rc x_c
+      if (r > 0) lfma<true>(y[c], B.o(herm_off(r, c)), x[r]);            // A_cr = conj(A_rc)
+    }
+#pragma unroll
+  for (int r = 0; r < 6; ++r) {
+    if constexpr (P == F16) rfma(y[r], (float)B.d(r), x[r]);
+    else rfma(y[r], B.d(r) + shift, x[r]);
+  }
+}
+
+// components 6h .. 6h+5 of a stored spinor in the arithmetic type
+template <int P, typename R>
+__device__ __forceinline__ void decode_half(const RawSpinor<P>& r, int h, cx<R> (&x)[6]) {
+#pragma unroll
+  for (int c = 0; c < 6; ++c) {
+    const auto q = raw_comp(r, 6 * h + c);
+    if constexpr (P == F16) x[c] = cx<R>{(R)((float)q.x * r.sc), (R)((float)q.y * r.sc)};
+    else x[c] = cx<R>{(R)q.x, (R)q.y};
+  }
+}
+
+__device__ __forceinline__ void load_half64(const SpinorRef& f, int slot, int h, int i, int Vh, cx<double> (&x)[6]) {
+  const double2* b = static_cast<const double2*>(f.data) + (long)slot * f.slot_stride;
+#pragma unroll
+  for (int c = 0; c < 6; ++c) {
+    const double2 v = vld<true>(at(scalar_base(b + (long)(6 * h + c) * Vh), i));
+    x[c] = cx<double>{v.x, v.y};
+  }
+}
+
+template <int P, typename R>
+__device__ __forceinline__ void store_half(const SpinorRef& f, int slot, int h, int i, int Vh, const cx<R>* s) {
+  static_assert(P != F16, "an FP16 site is stored whole (its scale is the maximum over the site)");
+  if constexpr (P == F64) {
+    double2* b = static_cast<double2*>(f.data) + (long)slot * f.slot_stride;
+#pragma unroll
+    for (int c = 0; c < 6; ++c) vst<true>(at(scalar_base(b + (long)(6 * h + c) * Vh), i), make_double2(s[c].x, s[c].y));
+  } else {
+    float4* b = static_cast<float4*>(f.data) + (long)slot * f.slot_stride;
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      vst<true>(at(scalar_base(b + (long)(3 * h + k) * Vh), i), make_float4(s[2 * k].x, s[2 * k].y, s[2 * k + 1].x, s[2 * k + 1].y));
+  }
+}
+
+// s += <a, b> (real and imaginary part), s += |a|^2
+template <typename R>
+__device__ __forceinline__ void dot_add(R& re, R& im, cx<R> a, cx<R> b) {
+  re = fmar(a.y, b.y, fmar(a.x, b.x, re));
+  im = fmar(-a.y, b.x, fmar(a.x, b.y, im));
+}
+
+// The stored copy of the clover or A^-1 blocks the epilogue uses in LDS:
+// units of 32 bits [72 (FP32) or 36 (FP16)][64], then the FP16 scales [64].
+// FP64 blocks are read from memory (they would not fit beside the links of
+// two workgroups per CU).
+template <int P, int EPI>
+constexpr bool shared_clover() {
+  return EPI == EPI_DIAG && P != F64;
+}
+constexpr int blk_units(int p) { return p == F32 ? 72 : p == F16 ? 36 : 0; }
+
+// Epilogue and fused reduction terms for one slot, one chirality at a time
+// (fewer live registers).  The epilogue's own inputs and the output are
+// streamed past L2 (read or written once per launch: 3% at 24^3x48 with 12
+// FP32 slots).  The 12 components of a dot product are summed in the
+// arithmetic precision per lane and added to the FP64 partial once.
+// load() issues the streams' loads (while the last neighbours are computed),
+// finish() does the rest.
+template <int P, int EPI, int RED, bool LDSB>
+struct Epilogue {
+  using R = typename Tr<P>::R;
+  static constexpr int PW = rh_prec(P);
+  static constexpr bool XIN = EPI == EPI_DIAG || EPI == EPI_SUB || EPI == EPI_INV_SUB;
+  static constexpr bool INV = EPI == EPI_INV || EPI == EPI_INV_SUB;
+  static constexpr bool DOTW = RED == RED_DOT_EXT || RED == RED_TS4;
+  RawSpinor<P> xr;
+  RawSpinor<PW> wr;
+
+  __device__ __forceinline__ void load(const HopArgs& a, int slot, int i) {
+    if constexpr (XIN) load_raw_spinor<P, true>(a.xin, slot, i, a.g.Vp, xr);
+    if constexpr (DOTW && P != F64) load_raw_spinor<PW, true>(a.red.w, slot, i, a.g.Vp, wr);
+  }
+
+  __device__ __forceinline__ void finish(const HopArgs& a, int slot, int i, cx<R> (&acc)[12], double (&red)[kRedMax],
+                                         const unsigned* lc, int lane) const {
+    const Geom& g = a.g;
+    R s0 = R(0), s1 = R(0), s2 = R(0), s3 = R(0), s4 = R(0), s5 = R(0), s6 = R(0);
+    cx<R> out[P == F16 ? 12 : 6];
+    R bsc = R(1);  // FP16 block scale
+    if constexpr (P == F16 && (EPI == EPI_DIAG || INV)) {
+      if constexpr (LDSB) {
+        bsc = __builtin_bit_cast(float, lc[blk_units(P) * 64 + lane]);
+      } else if constexpr (INV) {
+        bsc = *at(uniform_ptr(a.slots.ainv_scale[slot]), i);
+      } else {
+        bsc = *at(a.clov.scale, i);
+      }
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      __builtin_amdgcn_sched_barrier(0);
+      cx<R>* o = &out[P == F16 ? 6 * h : 0];
+      cx<R>* ac = &acc[6 * h];
+      cx<R> xh[6], wh[6];
+      if constexpr (XIN) decode_half<P>(xr, h, xh);
+      Blk<P> B;
+      if constexpr (EPI == EPI_DIAG || INV) {
+        if constexpr (LDSB && P != F64) {
+          constexpr int n = blk_units(P) / 2;
+#pragma unroll
+          for (int k = 0; k < n; ++k)
+            B.v[k] = __builtin_bit_cast(typename std::remove_reference<decltype(B.v[0])>::type,
+                                        lc[(n * h + k) * 64 + lane]);
+        } else if constexpr (INV) {
+          load_blk<P>(uniform_ptr(a.slots.ainv[slot]), h, i, g.Vp, B);
+        } else {
+          load_blk<P>(a.clov.data, h, i, g.Vp, B);
+        }
+      }
+      if constexpr (EPI == EPI_HOP) {
+#pragma unroll
+        for (int c = 0; c < 6; ++c) o[c] = R(-0.5) * ac[c];
+      } else if constexpr (EPI == EPI_DIAG) {
+        const R m4 = (R)a.slots.m4[slot];
+        const R hs = (R)(-0.5 * a.sign);
+        blk_apply<P>(B, m4, xh, o);
+#pragma unroll
+        for (int c = 0; c < 6; ++c) {
+          if constexpr (P == F16) {
+            cx<R> t = m4 * xh[c];
+            rfma(t, bsc, o[c]);
+            o[c] = t;
+          }
+          rfma(o[c], hs, ac[c]);
+        }
+      } else if constexpr (EPI == EPI_SUB) {
+#pragma unroll
+        for (int c = 0; c < 6; ++c) {
+          o[c] = xh[c];
+          rfma(o[c], R(0.5), ac[c]);
+        }
+      } else {  // EPI_INV, EPI_INV_SUB
+        cx<R> t[6];
+#pragma unroll
+        for (int c = 0; c < 6; ++c) {
+          if constexpr (EPI == EPI_INV_SUB) {
+            t[c] = xh[c];
+            rfma(t[c], R(0.5), ac[c]);
+          } else {
+            t[c] = R(-0.5) * ac[c];
+          }
+          if constexpr (P == F16) t[c] = bsc * t[c];
+        }
+        blk_apply<P>(B, R(0), t, o);
+      }
+      if constexpr (P != F16) store_half<P>(a.out, slot, h, i, g.Vp, o);
+      if constexpr (DOTW) {
+        if constexpr (P == F64) load_half64(a.red.w, slot, h, i, g.Vp, wh);  // here: fewer live registers
+        else decode_half<PW>(wr, h, wh);
+      }
+#pragma unroll
+      for (int c = 0; c < 6; ++c) {
+        if constexpr (RED == RED_DOT_EXT) dot_add(s0, s1, wh[c], o[c]);
+        if constexpr (RED == RED_TS || RED == RED_TS4) {
+          dot_add(s0, s1, o[c], xh[c]);
+          s2 = fmar(o[c].y, o[c].y, fmar(o[c].x, o[c].x, s2));
+        }
+        if constexpr (RED == RED_TS4) {
+          dot_add(s3, s4, wh[c], xh[c]);
+          dot_add(s5, s6, wh[c], o[c]);
+        }
+        if constexpr (RED == RED_NORM) s0 = fmar(o[c].y, o[c].y, fmar(o[c].x, o[c].x, s0));
+      }
+    }
+    if constexpr (P == F16) SpinorIO<P>::template store<true>(a.out, slot, i, g.Vp, out);
+    if constexpr (RED != RED_NONE) red[0] = (double)s0;
+    if constexpr (RED == RED_DOT_EXT || RED == RED_TS || RED == RED_TS4) red[1] = (double)s1;
+    if constexpr (RED == RED_TS || RED == RED_TS4) red[2] = (double)s2;
+    if constexpr (RED == RED_TS4) {
+      red[3] = (double)s3;
+      red[4] = (double)s4;
+      red[5] = (double)s5;
+      red[6] = (double)s6;
+    }
+  }
+};
+
+// ------------------------------------------------------------ sites
+
+// Mapping of the blocks: every XCD (block b runs on XCD b mod 8) owns either
+// a spatial slab, a fixed range of 64-site chunks of each timeslice that it
+// sweeps in x0 (tmap 0), or the timeslices [T k / 8, T (k+1) / 8) of every
+// chunk, chunk by chunk with the timeslices innermost (tmap 1); the x0 +- 1
+// neighbour spinors are then re-read from that XCD's L2.  The reduction
+// partial of an item is x0 nch + chunk (nparts = T nch) whatever the mapping.
+// mL3h, mL2: reciprocals for the site coordinates (div_by).
+struct SlabMap {
+  int nch, maxc;
+  int tmap, tlen;  // tlen: the longest XCD time range
+  unsigned mL3h, mL2;
+};
+
+// n / d for n < 2^31 with m = min(2^32 - 1, floor(2^32 / d)): the product is
+// short of the quotient by at most one
+__device__ __forceinline__ int div_by(int n, int d, unsigned m) {
+  const unsigned q = __umulhi((unsigned)n, m);
+  return (int)(q + ((unsigned)n - q * (unsigned)d >= (unsigned)d ? 1u : 0u));
+}
+
+__device__ __forceinline__ int slab_lo(int nch, int xcd) { return (nch * xcd) >> 3; }
+
+struct Item {
+  int chunk, x0;
+  bool in;  // false: the block owns nothing
+};
+// item j of an XCD; backwards: the timeslices from the last to the first (the
+// even-site kernels: they read the odd field the preceding odd-site kernel
+// wrote in forward order, whose last timeslices are still in the caches; 3%
+// at 24^3x48 with 12 FP32 slots)
+__device__ __forceinline__ Item map_item(const SlabMap& m, int T, int xcd, int j, bool backwards) {
+  Item it;
+  if (m.tmap) {
+    const int lo = (T * xcd) >> 3, hi = (T * (xcd + 1)) >> 3;
+    const int dt = j % m.tlen;
+    it.chunk = j / m.tlen;
+    it.in = lo + dt < hi && it.chunk < m.nch;
+    it.x0 = backwards ? hi - 1 - dt : lo + dt;
+  } else {
+    it.x0 = j / m.maxc;
+    it.chunk = slab_lo(m.nch, xcd) + (j - it.x0 * m.maxc);
+    it.in = it.chunk < slab_lo(m.nch, xcd + 1);
+    if (backwards) it.x0 = T - 1 - it.x0;
+  }
+  return it;
+}
+
+// A thread's output site: its index, spatial coordinates and neighbours
+// (2 mu forward, 2 mu + 1 backward).
+struct Site {
+  int i, x1, x2, x3;
+  int nb[8];
+};
+__device__ __forceinline__ void locate(const HopArgs& a, const SlabMap& m, int x0, int sp, Site& s) {
+  const Geom& g = a.g;
+  const int row = div_by(sp, g.L3h, m.mL3h), h = sp - row * g.L3h;
+  s.x1 = div_by(row, g.L2, m.mL2);
+  s.x2 = row - s.x1 * g.L2;
+  const int odd = (a.p + x0 + s.x1 + s.x2) & 1;  // x3 = 2 h + odd
+  s.x3 = 2 * h + odd;
+  const int i = x0 * g.Vsh + sp, pl = g.L2 * g.L3h;
+  s.i = i;
+  s.nb[0] = x0 + 1 == g.T ? sp : i + g.Vsh;
+  s.nb[1] = x0 == 0 ? i + (g.T - 1) * g.Vsh : i - g.Vsh;
+  s.nb[2] = s.x1 + 1 == g.L1 ? i - (g.L1 - 1) * pl : i + pl;
+  s.nb[3] = s.x1 == 0 ? i + (g.L1 - 1) * pl : i - pl;
+  s.nb[4] = s.x2 + 1 == g.L2 ? i - (g.L2 - 1) * g.L3h : i + g.L3h;
+  s.nb[5] = s.x2 == 0 ? i + (g.L2 - 1) * g.L3h : i - g.L3h;
+  // x3 + 1 is at the same half index from an even x3, at the next from an odd one
+  s.nb[6] = !odd ? i : h + 1 == g.L3h ? i - (g.L3h - 1) : i + 1;
+  s.nb[7] = odd ? i : h == 0 ? i + (g.L3h - 1) : i - 1;
+}
+
+// The hop for one slot at the thread's site (if valid), the epilogue, and the
+// wave's share of the fused reductions, stored as partial `part` of `nparts`.
+// Every lane of the wave calls it.  lu, lc: the workgroup's LDS copies of the
+// links (LDSL) and of the blocks (LDSB).
+template <int P, int EPI, int RED, int PF, bool DAG, bool LDSL, bool LDSB>
+__device__ __forceinline__ void slot_work(const HopArgs& a, int slot, const Site& s, int x0, bool valid, int part,
+                                          int nparts, const LinkElem<P>* lu, const unsigned* lc, int lane) {
+  using R = typename Tr<P>::R;
+  const Geom& g = a.g;
+  double red[kRedMax];
+#pragma unroll
+  for (int q = 0; q < kRedMax; ++q) red[q] = 0.0;
+  if (valid) {
+    const double* rt = a.slots.ratio + (long)slot * 4 * g.T + (DAG ? 2 * g.T : 0);
+    R coef[8] = {(R)rt[x0], (R)rt[g.T + x0], R(1), R(1), R(1), R(1), R(1), R(1)};
+    if (a.sratio) {  // uniform over the launch
+      const int x[3] = {s.x1, s.x2, s.x3};
+      const int Ls[3] = {g.L1, g.L2, g.L3};
+      int off = 0;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        coef[2 + 2 * k] = (R)a.sratio[off + (DAG ? 2 * Ls[k] : 0) + x[k]];
+        coef[3 + 2 * k] = (R)a.sratio[off + (DAG ? 3 * Ls[k] : Ls[k]) + x[k]];
+        off += 4 * Ls[k];
+      }
+    }
+    float one = 1.f;
+    if constexpr (P == F16) asm("" : "+s"(one));
+    cx<R> acc[12];
+#pragma unroll
+    for (int c = 0; c < 12; ++c) acc[c] = cx<R>{R(0), R(0)};
+    // opaque here: hoisted out of the caller's slot loop, the offsets would be
+    // kept widened to 64 bits and every load would add its base to them
+    int i = s.i, nb[8];
+    asm volatile("" : "+v"(i));
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      nb[k] = s.nb[k];
+      asm volatile("" : "+v"(nb[k]));
+    }
+    Neighbours<P, PF, DAG, LDSL> n;
+    n.template fill<0>(a, slot, i, nb);
+    Epilogue<P, EPI, RED, LDSB> epi;
+    n.template step<0>(a, slot, i, nb, coef, one, lu, lane, acc, epi);
+    epi.finish(a, slot, i, acc, red, lc, lane);
+  }
+  if constexpr (RED != RED_NONE) {
+    constexpr int nv = red_values(RED);
+    double* pt = a.red.partials + ((long)slot * nparts + part) * kRedMax;
+    const int v = wave_row_value(lane >> 4);
+    const double w = wave_sum4(red[0], red[1], red[2], red[3]);
+    if ((lane & 15) == 0 && v < nv) pt[v] = w;
+    if constexpr (nv > 4) {
+      const double w2 = wave_sum4(red[4], red[5], red[6], red[7]);
+      if ((lane & 15) == 0 && 4 + v < nv) pt[4 + v] = w2;
+    }
+  }
+}
+
+// ------------------------------------------------------------ kernels
+
+// Neighbours in flight (ring depth) and waves per SIMD the registers must
+// allow, per precision.  Measured on MI355X, even / odd sites, us:
+//   one slot, 32^3x64: FP64 1 neighbour 505 / 500, 2: 496 / 487, 3 at one
+//   wave: 487 / 459; FP32 2 at three waves 243 / 230, 3 at three 244 / 219, 4 at
+//   two 248 / 230, 6: 274 / 261; FP16 1 to 8: 131 .. 134 / 120 .. 125;
+//   12 slots, 24^3x48: FP64 1 or 2: 750 / 680, 3 (spills): 854 / 765; FP32 2: 336 /
+//   346, 3: 340 / 334, 4: 349 / 343, 6: 340 / 336; FP16 2: 208 / 208, 4: 212 / 213, 8:
+//   244 / 226.
+// Neither depth nor waves matter much: the kernels are bound by what the L2
+// fetches (FP64, FP32) or by instruction issue (FP16).  Fetching the next
+// slot's first neighbours during the epilogue was 5-20% slower.
+constexpr int slab_pf(int p) { return p == F64 ? 3 : p == F32 ? 2 : 4; }
+constexpr int slab_min_waves(int p) { return p == F64 ? 1 : 3; }
+constexpr int shared_pf(int p) { return p == F32 ? 3 : 2; }
+constexpr int kSharedThreads = 256;
+constexpr int kSharedMinWaves = 2;
+
+// One slot: one wave per (chunk, timeslice), the slots of a chunk in
+// neighbouring blocks of the same XCD.
+template <int P, int EPI, int RED, bool DAG>
+__global__ void __launch_bounds__(64, slab_min_waves(P)) hop_kernel_slab(HopArgs a, SlabMap m) {
+  const int j = blockIdx.x >> 3, jj = j / a.nslots, slot = j - jj * a.nslots;
+  const Item it = map_item(m, a.g.T, blockIdx.x & 7, jj, EPI == EPI_DIAG);
+  if (!it.in || (a.slots.mask && !a.slots.mask[slot])) return;
+  const int sp = it.chunk * 64 + threadIdx.x;
+  const bool valid = sp < a.g.Vsh;
+  Site s;
+  locate(a, m, it.x0, valid ? sp : 0, s);
+  slot_work<P, EPI, RED, slab_pf(P), DAG, false, false>(a, slot, s, it.x0, valid, it.x0 * m.nch + it.chunk,
+                                                        a.g.T * m.nch, nullptr, nullptr, threadIdx.x);
+}
+
+// Several slots: one workgroup per (chunk, timeslice), its waves take the
+// slots in turn.  The links of the chunk's 64 sites in the 8 hop directions
+// (and the clover blocks of the even-site epilogue, or the A^-1 blocks of the
+// odd-site ones when all slots share one mass: LINV) are loaded once into
+// LDS, as stored, instead of once per slot.  Per-slot arithmetic and
+// reduction partials are those of the one-slot kernel: bitwise the same.
+template <int P>
+constexpr size_t shared_tile_bytes(bool blocks) {
+  return 8 * 9 * 64 * sizeof(LinkElem<P>) + (blocks ? (blk_units(P) + (P == F16)) * 64 * sizeof(unsigned) : 0);
+}
+
+template <int P, int EPI, int RED, bool DAG, bool LINV>
+__global__ void __launch_bounds__(kSharedThreads, kSharedMinWaves) hop_kernel_shared(HopArgs a, SlabMap m) {
+  using E = LinkElem<P>;
+  extern __shared__ __align__(16) unsigned char smem[];
+  E* lu = reinterpret_cast<E*>(smem);
+  unsigned* lc = reinterpret_cast<unsigned*>(smem + 8 * 9 * 64 * sizeof(E));
+  const Geom& g = a.g;
+  const Item it = map_item(m, g.T, blockIdx.x & 7, blockIdx.x >> 3, EPI == EPI_DIAG);
+  if (!it.in) return;  // the whole workgroup, before any barrier
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
+  const int sp = it.chunk * 64 + lane;
+  const bool valid = sp < g.Vsh;
+  Site s;
+  locate(a, m, it.x0, valid ? sp : 0, s);
+  // fill: tasks 0..7 are the link directions, task 8 the blocks; wave w takes
+  // tasks w, w + nw, ...  Read once per launch: streamed past L2 (2-3%).
+  constexpr bool blocks = (shared_clover<P, EPI>() || LINV) && P != F64;
+  if (valid) {
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+      if (t % nw != wv || (t == 8 && !blocks)) continue;
+      if (t < 8) {
+        RawLink<P> u;
+        if (t & 1) load_raw_link<P, true>(a.U_in, t >> 1, s.nb[t], g.Vp, u);
+        else load_raw_link<P, true>(a.U_out, t >> 1, s.i, g.Vp, u);
+#pragma unroll
+        for (int k = 0; k < 9; ++k) lu[(t * 9 + k) * 64 + lane] = u.v[k];
+      } else if constexpr (blocks) {
+        const void* src = LINV ? a.slots.ainv_common : a.clov.data;
+        const uint4* q = static_cast<const uint4*>(src);
+#pragma unroll
+        for (int k = 0; k < blk_units(P) / 4; ++k) {
+          const uint4 v = vld<true>(at(scalar_base(q + (long)k * g.Vp), s.i));
+          lc[(4 * k) * 64 + lane] = v.x;
+          lc[(4 * k + 1) * 64 + lane] = v.y;
+          lc[(4 * k + 2) * 64 + lane] = v.z;
+          lc[(4 * k + 3) * 64 + lane] = v.w;
+        }
+        if constexpr (P == F16) {
+          const float* sc = LINV ? a.slots.ainv_common_scale : a.clov.scale;
+          lc[blk_units(P) * 64 + lane] = __builtin_bit_cast(unsigned, vld<true>(at(sc, s.i)));
+        }
+      }
+    }
+  }
+  __syncthreads();
+  const int part = it.x0 * m.nch + it.chunk, nparts = g.T * m.nch;
+#pragma unroll 1
+  for (int slot = wv; slot < a.nslots; slot += nw) {
+    if (a.slots.mask && !a.slots.mask[slot]) continue;
+    // keeps the compiler from hoisting the LDS reads out of this loop into
+    // (many) registers
+    asm volatile("" ::: "memory");
+    slot_work<P, EPI, RED, shared_pf(P), DAG, true, blocks>(a, slot, s, it.x0, valid, part, nparts, lu, lc, lane);
+  }
+}
+
+int env_knob(const char* name, int dflt) {
+  const char* e = getenv(name);
+  return e ? atoi(e) : dflt;
+}
+
+unsigned recip32(int d) {
+  const unsigned long long m = (1ULL << 32) / (unsigned)d;
+  return (unsigned)std::min<unsigned long long>(m, 0xffffffffULL);
+}
+
+template <int P, int EPI, int RED, bool DAG>
+hipError_t launch_one(const HopArgs& a, hipStream_t st, int* nparts_out) {
+  SlabMap m;
+  m.nch = (a.g.Vsh + 63) / 64;
+  m.maxc = (m.nch + 7) / 8;
+  m.tlen = (a.g.T + 7) / 8;
+  m.mL3h = recip32(a.g.L3h);
+  m.mL2 = recip32(a.g.L2);
+  // XCD mapping, chosen per launch: both mappings give bitwise the same
+  // results.  Measured on MI355X: timeslice ranges 2-6% faster for one FP32
+  // or FP16 slot and for 12 FP16 slots at 24^3x48 and 32^3x64, slabs 6% faster
+  // for 12 FP32 slots; FP64 keeps the slabs (one slot: 2% faster on timeslice
+  // ranges at 24^3x48, 4-10% slower at 32^3x64).  DP_HOP_TMAP = 0 / 1 forces
+  // one of them.
+  static const int tmap_knob = env_knob("DP_HOP_TMAP", -1);
+  m.tmap = tmap_knob == 0 || tmap_knob == 1 ? tmap_knob : (P != F64 && (a.nslots == 1 || P == F16) ? 1 : 0);
+  const int nblocks = m.tmap ? 8 * m.tlen * m.nch : 8 * a.g.T * m.maxc;
+  *nparts_out = a.g.T * m.nch;
+  if (a.nslots >= 2) {
+    // waves per workgroup: the fewest rounds over the slots with at most four waves
+    const int maxw = kSharedThreads / 64, rounds = (a.nslots + maxw - 1) / maxw;
+    const dim3 grid(nblocks), block(64 * ((a.nslots + rounds - 1) / rounds));
+    constexpr bool inv = EPI == EPI_INV || EPI == EPI_INV_SUB;
+    if (inv && P != F64 && a.slots.ainv_common)
+      hipLaunchKernelGGL((hop_kernel_shared<P, EPI, RED, DAG, inv && P != F64>), grid, block, shared_tile_bytes<P>(true),
+                         st, a, m);
+    else
+      hipLaunchKernelGGL((hop_kernel_shared<P, EPI, RED, DAG, false>), grid, block,
+                         shared_tile_bytes<P>(shared_clover<P, EPI>()), st, a, m);
+  } else {
+    hipLaunchKernelGGL((hop_kernel_slab<P, EPI, RED, DAG>), dim3(nblocks * a.nslots), dim3(64), 0, st, a, m);
+  }
+  return hipGetLastError();
+}
+
+template <int P, bool DAG>
+hipError_t launch_epi(const HopArgs& a, hipStream_t st, int* np) {
+  // fused reductions are only used with the even-site Schur epilogue
+  if (a.red.red != RED_NONE && a.epi != EPI_DIAG) return hipErrorInvalidValue;
+  switch (a.epi) {
+    case EPI_HOP: return launch_one<P, EPI_HOP, RED_NONE, DAG>(a, st, np);
+    case EPI_INV: return launch_one<P, EPI_INV, RED_NONE, DAG>(a, st, np);
+    case EPI_SUB: return launch_one<P, EPI_SUB, RED_NONE, DAG>(a, st, np);
+    case EPI_INV_SUB: return launch_one<P, EPI_INV_SUB, RED_NONE, DAG>(a, st, np);
+    case EPI_DIAG:
+      switch (a.red.red) {
+        case RED_NONE: return launch_one<P, EPI_DIAG, RED_NONE, DAG>(a, st, np);
+        // the reductions with the shadow residual belong to BiCGStab, which
+        // never applies the adjoint: those variants are not built
+        case RED_DOT_EXT:
+          if constexpr (DAG) return hipErrorInvalidValue;
+          else return launch_one<P, EPI_DIAG, RED_DOT_EXT, DAG>(a, st, np);
+        case RED_TS: return launch_one<P, EPI_DIAG, RED_TS, DAG>(a, st, np);
+        case RED_NORM: return launch_one<P, EPI_DIAG, RED_NORM, DAG>(a, st, np);
+        case RED_TS4:
+          if constexpr (DAG) return hipErrorInvalidValue;
+          else return launch_one<P, EPI_DIAG, RED_TS4, DAG>(a, st, np);
+        default: return hipErrorInvalidValue;
+      }
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace
+
+}  // namespace dp

@@ -216,3 +216,31 @@ def test_dirichlet_time_boundary_operator(precision, tol):
             assert max_rel(L.apply(psi, precond=True, dagger=dagger, precision=precision), ref) < tol
             refs = oracle_schur(oracle, U, C, 0.3, psi, alpha, bc_t=0, dagger=dagger)
             assert max_rel(L.apply(psi, precond=True, schur=True, dagger=dagger, precision=precision), refs) < tol
+
+
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (4, 2, 6, 2), (2, 34, 2, 6), (6, 10, 14, 6)])
+@pytest.mark.parametrize("nrhs", [1, 2, 5])
+def test_operator_extents(dims, nrhs):
+    """The kernels' site arithmetic at the edges of its range: extents of 2
+    (half rows of one site, both neighbours the same site), rows that do not
+    divide a 64-site chunk, partial chunks; full operator and Schur operator
+    in FP64 with one slot and with several, against the oracle."""
+    import torch
+    log(f"test_operator_extents dims={dims} nrhs={nrhs}")
+    U, C, alpha = setup_field(dims, 700 + dims[1])
+    psi = synth.random_spinor(dims, 15, nrhs=nrhs)
+    with lattice(dims) as L:
+        L.set_gauge(U)
+        L.set_clover(1.6)
+        L.set_mass(0.2)
+        L.set_alpha(alpha)
+        in_t = torch.from_numpy(psi.reshape(nrhs, -1)).cuda()
+        out_t = torch.empty_like(in_t)
+        torch.cuda.synchronize()
+        for schur, tol in ((False, 1e-13), (True, 1e-12)):
+            L.apply_dev(in_t, out_t, precond=True, schur=schur)
+            got = out_t.cpu().numpy().reshape(psi.shape)
+            for k in range(nrhs):
+                ref = (oracle_schur(oracle, U, C, 0.2, psi[k], alpha) if schur
+                       else oracle.apply(U, C, 0.2, psi[k], alpha=alpha))
+                assert max_rel(got[k], ref) < tol, (schur, k)
