@@ -203,86 +203,134 @@ __global__ void clover_pack_kernel(Geom g, const double2* __restrict__ C, double
   }
 }
 
-// (B + m4)^-1 by Gauss-Jordan elimination with partial pivoting, FP64.
-__global__ void __launch_bounds__(128) clover_invert_kernel(Geom g, const double2* __restrict__ C, double m4,
-                                                            double2* Ainv, int* bad) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int h = blockIdx.y;
-  if (i >= g.Vh) return;
-  z A[6][6], X[6][6];
+// FP32 and FP16 copies of a site's packed blocks, from the FP64 values of one
+// chirality in each of two lanes: lane (h, site), 36 reals r.  The FP16 scale is
+// the site's largest real; the 16-byte unit that both blocks share is
+// written in halves.
+__device__ __forceinline__ void store_inner(const double (&r)[36], int h, int i, int Vp, float4* o32, uint4* o16,
+                                            float* scale) {
+#pragma unroll
+  for (int k = 0; k < 9; ++k)
+    o32[(long)(9 * h + k) * Vp + i] =
+        make_float4((float)r[4 * k], (float)r[4 * k + 1], (float)r[4 * k + 2], (float)r[4 * k + 3]);
+  double m = 0.0;
+#pragma unroll
+  for (int k = 0; k < 36; ++k) m = fmax(m, fabs(r[k]));
+  m = fmax(m, __shfl_xor(m, 32, 64));
+  const double inv = m > 0 ? 1.0 / m : 0.0;
+  if (h == 0) scale[i] = (float)m;
+  unsigned w[18];
+#pragma unroll
+  for (int k = 0; k < 18; ++k) w[k] = f2h((float)(r[2 * k] * inv), (float)(r[2 * k + 1] * inv));
+  // block 0: units 0..3 and the first half of unit 4; block 1: the rest
+  reinterpret_cast<uint2*>(o16 + 4L * Vp + i)[h] = h ? make_uint2(w[0], w[1]) : make_uint2(w[16], w[17]);
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    o16[(long)(5 * h + k) * Vp + i] = h ? make_uint4(w[4 * k + 2], w[4 * k + 3], w[4 * k + 4], w[4 * k + 5])
+                                        : make_uint4(w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3]);
+}
+
+// the 36 reals of a packed block in storage order
+__device__ __forceinline__ void pack_block(const z (&A)[6][6], double (&r)[36]) {
+#pragma unroll
+  for (int k = 0; k < 6; ++k) r[k] = A[k][k].x;
+  int n = 0;
+#pragma unroll
+  for (int a = 0; a < 6; ++a)
+#pragma unroll
+    for (int b = a + 1; b < 6; ++b, ++n) {
+      r[6 + 2 * n] = A[a][b].x;
+      r[7 + 2 * n] = A[a][b].y;
+    }
+}
+
+__device__ __forceinline__ void select_swap(bool c, z& a, z& b) {
+  const z t = a;
+  a = z{c ? b.x : a.x, c ? b.y : a.y};
+  b = z{c ? t.x : b.x, c ? t.y : b.y};
+}
+
+// (B + m4)^-1 by Gauss-Jordan elimination in place with partial pivoting,
+// FP64; lanes 0..31 of a wave take the upper blocks of 32 sites, lanes 32..63
+// the lower ones.  Every index is a constant (rows and columns are swapped by
+// selects), so the block stays in registers: with the pivot row indexed and
+// the inverse beside the matrix it lay in scratch memory, 18 GB of traffic and
+// 7.0 ms at 32^3x64.
+__global__ void __launch_bounds__(64) clover_invert_kernel(Geom g, const double2* __restrict__ C, double m4,
+                                                           double2* Ainv, float4* a32, uint4* a16, float* s16,
+                                                           int* bad) {
+  const int h = threadIdx.x >> 5, site = blockIdx.x * 32 + (threadIdx.x & 31);
+  const int i = min(site, g.Vh - 1);  // every lane takes part in the exchange of the scale
+  z A[6][6];
   load_block(C, g.Vp, i, h, A);
-  for (int r = 0; r < 6; ++r) {
-    A[r][r].x += m4;
-    for (int c = 0; c < 6; ++c) X[r][c] = z{r == c ? 1.0 : 0.0, 0.0};
-  }
-  int singular = 0;
+#pragma unroll
+  for (int r = 0; r < 6; ++r) A[r][r].x += m4;
+  int piv[6];
+  bool singular = false;
+#pragma unroll
   for (int k = 0; k < 6; ++k) {
-    int piv = k;
+    piv[k] = k;
     double best = A[k][k].x * A[k][k].x + A[k][k].y * A[k][k].y;
+#pragma unroll
     for (int r = k + 1; r < 6; ++r) {
       const double m = A[r][k].x * A[r][k].x + A[r][k].y * A[r][k].y;
-      if (m > best) { best = m; piv = r; }
-    }
-    if (!(best > 0.0)) { singular = 1; break; }
-    if (piv != k)
-      for (int c = 0; c < 6; ++c) {
-        z t = A[k][c]; A[k][c] = A[piv][c]; A[piv][c] = t;
-        t = X[k][c]; X[k][c] = X[piv][c]; X[piv][c] = t;
+      if (m > best) {
+        best = m;
+        piv[k] = r;
       }
+    }
+    singular |= !(best > 0.0);
+#pragma unroll
+    for (int r = k + 1; r < 6; ++r)
+#pragma unroll
+      for (int c = 0; c < 6; ++c) select_swap(piv[k] == r, A[k][c], A[r][c]);
     const z d = A[k][k];
     const double dn = d.x * d.x + d.y * d.y;
     const z inv = z{d.x / dn, -d.y / dn};
-    for (int c = 0; c < 6; ++c) {
-      A[k][c] = cmul(A[k][c], inv);
-      X[k][c] = cmul(X[k][c], inv);
-    }
+    A[k][k] = z{1.0, 0.0};
+#pragma unroll
+    for (int c = 0; c < 6; ++c) A[k][c] = cmul(A[k][c], inv);
+#pragma unroll
     for (int r = 0; r < 6; ++r) {
       if (r == k) continue;
       const z f = A[r][k];
-      for (int c = 0; c < 6; ++c) {
-        A[r][c] = A[r][c] - cmul(f, A[k][c]);
-        X[r][c] = X[r][c] - cmul(f, X[k][c]);
-      }
+      A[r][k] = z{0.0, 0.0};
+#pragma unroll
+      for (int c = 0; c < 6; ++c) A[r][c] = A[r][c] - cmul(f, A[k][c]);
     }
   }
-  if (singular) atomicOr(bad, 1);
+  // the row swaps, undone in reverse on the columns of the inverse
+#pragma unroll
+  for (int k = 5; k >= 0; --k)
+#pragma unroll
+    for (int r = k + 1; r < 6; ++r)
+#pragma unroll
+      for (int q = 0; q < 6; ++q) select_swap(piv[k] == r, A[q][k], A[q][r]);
+  if (singular && site < g.Vh) atomicOr(bad, 1);
   // the inverse of a Hermitian matrix is Hermitian: keep the averaged upper part
-  for (int r = 0; r < 6; ++r) {
-    X[r][r] = z{X[r][r].x, 0.0};
-    for (int c = r + 1; c < 6; ++c) X[r][c] = z{0.5 * (X[r][c].x + X[c][r].x), 0.5 * (X[r][c].y - X[c][r].y)};
-  }
-  store_block(Ainv, g.Vp, i, h, X);
+#pragma unroll
+  for (int r = 0; r < 6; ++r)
+#pragma unroll
+    for (int c = r + 1; c < 6; ++c)
+      A[r][c] = z{0.5 * (A[r][c].x + A[c][r].x), 0.5 * (A[r][c].y - A[c][r].y)};
+  // lanes past the last site store its values again (two lanes, the same bits)
+  store_block(Ainv, g.Vp, i, h, A);
+  double r[36];
+  pack_block(A, r);
+  store_inner(r, h, i, g.Vp, a32, a16, s16);
 }
 
-template <int P>
-__global__ void clover_convert_kernel(Geom g, const double2* __restrict__ C, void* out, float* scale) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= g.Vh) return;
-  double r[72];
-  for (int k = 0; k < 36; ++k) {
-    const double2 v = C[(long)k * g.Vp + i];
+__global__ void __launch_bounds__(64) clover_convert_kernel(Geom g, const double2* __restrict__ C, float4* o32,
+                                                            uint4* o16, float* scale) {
+  const int h = threadIdx.x >> 5, i = min((int)blockIdx.x * 32 + (int)(threadIdx.x & 31), g.Vh - 1);
+  double r[36];
+#pragma unroll
+  for (int k = 0; k < 18; ++k) {
+    const double2 v = C[(long)(18 * h + k) * g.Vp + i];
     r[2 * k] = v.x;
     r[2 * k + 1] = v.y;
   }
-  if constexpr (P == F32) {
-    float4* o = static_cast<float4*>(out);
-    for (int k = 0; k < 18; ++k)
-      o[(long)k * g.Vp + i] = make_float4((float)r[4 * k], (float)r[4 * k + 1], (float)r[4 * k + 2], (float)r[4 * k + 3]);
-  } else {
-    double m = 0.0;
-    for (int k = 0; k < 72; ++k) m = fmax(m, fabs(r[k]));
-    const double inv = m > 0 ? 1.0 / m : 0.0;
-    scale[i] = (float)m;
-    uint4* o = static_cast<uint4*>(out);
-    for (int k = 0; k < 9; ++k) {
-      uint4 v;
-      v.x = f2h((float)(r[8 * k + 0] * inv), (float)(r[8 * k + 1] * inv));
-      v.y = f2h((float)(r[8 * k + 2] * inv), (float)(r[8 * k + 3] * inv));
-      v.z = f2h((float)(r[8 * k + 4] * inv), (float)(r[8 * k + 5] * inv));
-      v.w = f2h((float)(r[8 * k + 6] * inv), (float)(r[8 * k + 7] * inv));
-      o[(long)k * g.Vp + i] = v;
-    }
-  }
+  store_inner(r, h, i, g.Vp, o32, o16, scale);
 }
 
 // out = A^-1 in with the slot's A^-1 field, FP64 parity fields.
@@ -356,20 +404,17 @@ hipError_t launch_clover_pack(const Geom& g, const double2* C_aos, double2* C_eo
   return hipGetLastError();
 }
 
-hipError_t launch_clover_invert(const Geom& g, const double2* C64, double m4, double2* Ainv64, int* bad,
-                                hipStream_t st) {
-  hipLaunchKernelGGL(clover_invert_kernel, dim3((g.Vh + 127) / 128, 2), dim3(128), 0, st, g, C64, m4, Ainv64, bad);
+hipError_t launch_clover_invert(const Geom& g, const double2* C64, double m4, double2* Ainv64, void* Ainv32,
+                                void* Ainv16, float* scale16, int* bad, hipStream_t st) {
+  hipLaunchKernelGGL(clover_invert_kernel, dim3((g.Vh + 31) / 32), dim3(64), 0, st, g, C64, m4, Ainv64,
+                     static_cast<float4*>(Ainv32), static_cast<uint4*>(Ainv16), scale16, bad);
   return hipGetLastError();
 }
 
-hipError_t launch_clover_convert(const Geom& g, const double2* C64, void* out, float* scale, int prec,
+hipError_t launch_clover_convert(const Geom& g, const double2* C64, void* out32, void* out16, float* scale16,
                                  hipStream_t st) {
-  const dim3 grid((g.Vh + kBlock - 1) / kBlock);
-  switch (prec) {
-    case F32: hipLaunchKernelGGL(clover_convert_kernel<F32>, grid, dim3(kBlock), 0, st, g, C64, out, scale); break;
-    case F16: hipLaunchKernelGGL(clover_convert_kernel<F16>, grid, dim3(kBlock), 0, st, g, C64, out, scale); break;
-    default: return hipErrorInvalidValue;
-  }
+  hipLaunchKernelGGL(clover_convert_kernel, dim3((g.Vh + 31) / 32), dim3(64), 0, st, g, C64,
+                     static_cast<float4*>(out32), static_cast<uint4*>(out16), scale16);
   return hipGetLastError();
 }
 

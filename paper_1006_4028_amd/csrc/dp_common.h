@@ -177,10 +177,10 @@ struct HopArgs {
 // folds next with launch_finalize(a.red, nv, *nparts, ...).
 hipError_t launch_hop(const HopArgs& a, hipStream_t stream, int* nparts);
 
-// FP64 host-layout gauge field [site][mu][3][3] (device copy) -> SoA parity fields;
-// U_aos == nullptr gives unit links
-hipError_t launch_gauge_reorder(const Geom& g, const double2* U_aos, void* U_eo[2], int prec,
-                                hipStream_t stream);
+// FP64 host-layout gauge field [site][mu][3][3] (device copy) -> SoA parity
+// fields in FP64 and, unless null, FP32 and FP16; U_aos == nullptr gives unit links
+hipError_t launch_gauge_reorder(const Geom& g, const double2* U_aos, void* const U64[2], void* const U32[2],
+                                void* const U16[2], hipStream_t stream);
 // Clover blocks from the FP64 parity links: out_eo[p] = packed C (FP64), both parities.
 hipError_t launch_clover_build(const Geom& g, const double2* U64_eo[2], double csw, double2* C_eo[2],
                                hipStream_t stream);
@@ -188,15 +188,15 @@ hipError_t launch_clover_build(const Geom& g, const double2* U64_eo[2], double c
 // nonzero on entries outside the two chiral blocks or non-Hermitian parts.
 hipError_t launch_clover_pack(const Geom& g, const double2* C_aos, double2* C_eo[2], int* bad,
                               hipStream_t stream);
-// A^-1 = (C + m4)^-1 per block (FP64 Gauss-Jordan with pivoting), packed; *bad is
-// set when a block is singular.
-hipError_t launch_clover_invert(const Geom& g, const double2* C64, double m4, double2* Ainv64, int* bad,
-                                hipStream_t stream);
+// A^-1 = (C + m4)^-1 per block (FP64 Gauss-Jordan with pivoting), packed, in
+// FP64, FP32 and FP16 (with scales); *bad is set when a block is singular.
+hipError_t launch_clover_invert(const Geom& g, const double2* C64, double m4, double2* Ainv64, void* Ainv32,
+                                void* Ainv16, float* scale16, int* bad, hipStream_t stream);
 // out = A^-1 in per slot (the slot's A^-1 field), FP64 parity fields.
 hipError_t launch_clover_apply(const Geom& g, const SlotTable& slots, SpinorRef in, SpinorRef out, int nslots,
                                hipStream_t stream);
-// Convert packed FP64 clover blocks to FP32 / FP16(+scale).
-hipError_t launch_clover_convert(const Geom& g, const double2* C64, void* out, float* scale, int prec,
+// Convert packed FP64 clover blocks to FP32 and FP16 (with scales).
+hipError_t launch_clover_convert(const Geom& g, const double2* C64, void* out32, void* out16, float* scale16,
                                  hipStream_t stream);
 
 // Host-layout spinors [slot][site][4][3] complex128 (device) <-> parity fields.
@@ -204,7 +204,7 @@ hipError_t launch_clover_convert(const Geom& g, const double2* C64, void* out, f
 // alpha_mul / alpha_div: per-slot time profiles [slot][T] (nullable); sprof:
 // the spatial profiles a_1[L1], a_2[L2], a_3[L3] one after the other (nullable)
 hipError_t launch_spinor_import(const Geom& g, const double2* aos, int nslots, long aos_slot_stride,
-                                int p, SpinorRef dst, const double* alpha_mul, const double* sprof,
+                                SpinorRef even, SpinorRef odd, const double* alpha_mul, const double* sprof,
                                 hipStream_t stream);
 hipError_t launch_spinor_export(const Geom& g, SpinorRef even, SpinorRef odd, int nslots,
                                 const double* alpha_div, const double* sprof, double2* aos, long aos_slot_stride,
@@ -225,9 +225,10 @@ hipError_t launch_sf_wall_sources(const Geom& g, const double2* U_t, int side, i
 hipError_t launch_point_sources(const Geom& g, const int site[4], int c0, int ncols, double2* out,
                                 hipStream_t stream);
 // Per-timeslice sum of |psi|^2 over both parities, written to cpp[slot][t]
-// (as -sum, t = (x0 - x0_src[slot]) mod T), FP64 fields, divided by alpha^2.
+// (as -sum, t = (x0 - x0_src[slot]) mod T), FP64 fields, divided by alpha^2;
+// mask (nullable): slots with 0 are left alone.
 hipError_t launch_cpp(const Geom& g, SpinorRef even, SpinorRef odd, int nslots, const double* alpha,
-                      const double* sprof, const int* x0_src, double* cpp, hipStream_t stream);
+                      const double* sprof, const int* x0_src, const int* mask, double* cpp, hipStream_t stream);
 
 // ------------------------------------------------------------- BLAS kernels
 // Vector kernels over the even sites of every active slot.  Krylov vectors

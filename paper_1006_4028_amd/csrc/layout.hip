@@ -19,75 +19,125 @@ __device__ __forceinline__ double space_factor(const Geom& g, const double* spro
   return sprof ? sprof[x1] * sprof[g.L1 + x2] * sprof[g.L1 + g.L2 + x3] : 1.0;
 }
 
-__device__ __forceinline__ void lex_coords(const Geom& g, long s, int& x0, int& x1, int& x2, int& x3) {
-  x3 = (int)(s % g.L3);
-  s /= g.L3;
-  x2 = (int)(s % g.L2);
-  s /= g.L2;
-  x1 = (int)(s % g.L1);
-  x0 = (int)(s / g.L1);
+// ------------------------------------------------------------ transposes
+//
+// Between the host order (all components of a site together, both parities
+// interleaved) and the parity fields (one array per component) every wave
+// transposes 64 consecutive sites through LDS, so that it reads and writes
+// whole cache lines on both sides: with a site per thread, whose 16-byte
+// accesses lie 192 (spinors) or 576 (links) bytes apart, the export of 12
+// columns at 24^3x48 took 1058 us, the two imports 652.  Extents are even, so
+// sites 2 j and 2 j + 1 have one of each parity and index j in it: lanes 0..31
+// take the even parity's sites of the 32 pairs, lanes 32..63 the odd one's.
+
+constexpr int kPairs = 32;  // site pairs of one wave
+
+// the pair's even site: x1, x2, x3 and its parity
+struct Pair {
+  int x0, x1, x2, x3, q;
+};
+__device__ __forceinline__ Pair pair_coords(const Geom& g, int i) {
+  Pair c;
+  const int row = i / g.L3h;
+  c.x3 = 2 * (i - row * g.L3h);
+  const int t = row / g.L2;
+  c.x2 = row - t * g.L2;
+  c.x0 = t / g.L1;
+  c.x1 = t - c.x0 * g.L1;
+  c.q = (c.x0 + c.x1 + c.x2) & 1;
+  return c;
 }
 
-template <int P>
-__global__ void gauge_reorder_kernel(Geom g, const double2* __restrict__ U, void* e, void* o) {
-  const long V = 2L * g.Vh;
-  const long s = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= V) return;
-  int x0, x1, x2, x3;
-  lex_coords(g, s, x0, x1, x2, x3);
-  const int p = (x0 + x1 + x2 + x3) & 1;
-  const int i = (int)(s >> 1);
-  void* dst = p ? o : e;
-  for (int mu = 0; mu < 4; ++mu)
-    for (int k = 0; k < 9; ++k) {
-      const double2 v = U ? U[(s * 4 + mu) * 9 + k] : make_double2((k % 4 == 0) ? 1.0 : 0.0, 0.0);
-      const long at = (long)(mu * 9 + k) * g.Vp + i;
-      if constexpr (P == F64) {
-        static_cast<double2*>(dst)[at] = v;
-      } else if constexpr (P == F32) {
-        static_cast<float2*>(dst)[at] = make_float2((float)v.x, (float)v.y);
-      } else {
-        static_cast<unsigned*>(dst)[at] = f2h((float)v.x, (float)v.y);
-      }
-    }
-}
-
-// host-order spinors -> FP64 parity field, optionally times beta(x)
-__global__ void spinor_import_kernel(Geom g, const double2* __restrict__ aos, long aos_ss, int p, SpinorRef dst,
-                                     const double* __restrict__ amul, const double* __restrict__ sprof) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int slot = blockIdx.y;
+// host-order links -> parity fields in the three precisions, one read for all.
+// A wave takes 16 pairs (18 KB of LDS).  LDS rows of 37 units: a column of 16
+// lanes then touches every bank group once.
+constexpr int kLinkPairs = 16;
+struct GaugeDst {
+  double2* f64[2];
+  float2* f32[2];
+  unsigned* f16[2];
+};
+__global__ void __launch_bounds__(64) gauge_reorder_kernel(Geom g, const double2* __restrict__ U, GaugeDst o) {
+  __shared__ double2 t[2 * kLinkPairs * 37];
+  const int lane = threadIdx.x, i0 = blockIdx.x * kLinkPairs;
+  const long base = 2L * i0 * 36, total = 2L * g.Vh * 36;
+#pragma unroll
+  for (int m = 0; m < 2 * kLinkPairs * 36 / 64; ++m) {
+    const int k = lane + 64 * m;
+    double2 v = make_double2(0.0, 0.0);
+    if (base + k < total) v = U ? vld<true>(U + base + k) : make_double2((k % 36) % 9 % 4 == 0 ? 1.0 : 0.0, 0.0);
+    t[(k / 36) * 37 + k % 36] = v;
+  }
+  __syncthreads();
+  // lanes: 16 pairs, 2 parities, 2 components at a time
+  const int j = lane & 15, p = (lane >> 4) & 1, i = i0 + j;
   if (i >= g.Vh) return;
-  int x0, x1, x2, x3;
-  eo_coords(g, p, i, x0, x1, x2, x3);
-  const long s = ((long)(x0 * g.L1 + x1) * g.L2 + x2) * g.L3 + x3;
-  const double f = (amul ? amul[(long)slot * g.T + x0] : 1.0) * space_factor(g, sprof, x1, x2, x3);
-  const double2* src = aos + slot * aos_ss + s * 12;
-  double2* d = static_cast<double2*>(dst.data) + slot * dst.slot_stride;
-  for (int c = 0; c < 12; ++c) {
-    const double2 v = src[c];
-    d[(long)c * g.Vp + i] = make_double2(f * v.x, f * v.y);
+  const Pair c = pair_coords(g, i);
+  const double2* src = t + (2 * j + (c.q ^ p)) * 37;
+  for (int k = lane >> 5; k < 36; k += 2) {
+    const double2 v = src[k];
+    const long at = (long)k * g.Vp + i;
+    if (o.f64[p]) o.f64[p][at] = v;
+    if (o.f32[p]) o.f32[p][at] = make_float2((float)v.x, (float)v.y);
+    if (o.f16[p]) o.f16[p][at] = f2h((float)v.x, (float)v.y);
   }
 }
 
+// host-order spinors -> FP64 parity fields (both), optionally times beta(x)
+__global__ void __launch_bounds__(64) spinor_import_kernel(Geom g, const double2* __restrict__ aos, long aos_ss,
+                                                           SpinorRef e, SpinorRef o, const double* __restrict__ amul,
+                                                           const double* __restrict__ sprof) {
+  __shared__ double2 t[2 * kPairs * 13];
+  const int lane = threadIdx.x, i0 = blockIdx.x * kPairs, slot = blockIdx.y;
+  const double2* src = aos + slot * aos_ss + 2L * i0 * 12;
+  const int n = min(kPairs, g.Vh - i0) * 24;
+#pragma unroll
+  for (int m = 0; m < 12; ++m) {
+    const int k = lane + 64 * m;
+    if (k < n) t[(k / 12) * 13 + k % 12] = vld<true>(src + k);
+  }
+  __syncthreads();
+  const int j = lane & 31, p = lane >> 5, i = i0 + j;
+  if (i >= g.Vh) return;
+  const Pair c = pair_coords(g, i);
+  const int odd = c.q ^ p;  // the pair's second site has the other parity
+  const double f = (amul ? amul[(long)slot * g.T + c.x0] : 1.0) * space_factor(g, sprof, c.x1, c.x2, c.x3 + odd);
+  const SpinorRef& d = p ? o : e;
+  double2* dst = static_cast<double2*>(d.data) + slot * d.slot_stride + i;
+  const double2* q = t + (2 * j + odd) * 13;
+#pragma unroll
+  for (int k = 0; k < 12; ++k) dst[(long)k * g.Vp] = make_double2(f * q[k].x, f * q[k].y);
+}
+
 // FP64 parity fields -> host-order spinors, optionally divided by beta(x)
-__global__ void spinor_export_kernel(Geom g, SpinorRef e, SpinorRef o, const double* __restrict__ adiv,
-                                     const double* __restrict__ sprof, double2* __restrict__ aos, long aos_ss) {
-  const long V = 2L * g.Vh;
-  const long s = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  const int slot = blockIdx.y;
-  if (s >= V) return;
-  int x0, x1, x2, x3;
-  lex_coords(g, s, x0, x1, x2, x3);
-  const int p = (x0 + x1 + x2 + x3) & 1;
-  const int i = (int)(s >> 1);
-  const SpinorRef& f = p ? o : e;
-  const double2* src = static_cast<const double2*>(f.data) + slot * f.slot_stride;
-  const double inv = 1.0 / ((adiv ? adiv[(long)slot * g.T + x0] : 1.0) * space_factor(g, sprof, x1, x2, x3));
-  double2* d = aos + slot * aos_ss + s * 12;
-  for (int c = 0; c < 12; ++c) {
-    const double2 v = src[(long)c * g.Vp + i];
-    d[c] = make_double2(v.x * inv, v.y * inv);
+__global__ void __launch_bounds__(64) spinor_export_kernel(Geom g, SpinorRef e, SpinorRef o,
+                                                           const double* __restrict__ adiv,
+                                                           const double* __restrict__ sprof,
+                                                           double2* __restrict__ aos, long aos_ss) {
+  __shared__ double2 t[2 * kPairs * 13];
+  const int lane = threadIdx.x, i0 = blockIdx.x * kPairs, slot = blockIdx.y;
+  const int j = lane & 31, p = lane >> 5, i = i0 + j;
+  if (i < g.Vh) {
+    const Pair c = pair_coords(g, i);
+    const int odd = c.q ^ p;
+    const SpinorRef& f = p ? o : e;
+    const double2* src = static_cast<const double2*>(f.data) + slot * f.slot_stride + i;
+    const double inv =
+        1.0 / ((adiv ? adiv[(long)slot * g.T + c.x0] : 1.0) * space_factor(g, sprof, c.x1, c.x2, c.x3 + odd));
+    double2* q = t + (2 * j + odd) * 13;
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
+      const double2 v = vld<true>(src + (long)k * g.Vp);
+      q[k] = make_double2(v.x * inv, v.y * inv);
+    }
+  }
+  __syncthreads();
+  double2* dst = aos + slot * aos_ss + 2L * i0 * 12;
+  const int n = min(kPairs, g.Vh - i0) * 24;
+#pragma unroll
+  for (int m = 0; m < 12; ++m) {
+    const int k = lane + 64 * m;
+    if (k < n) vst<true>(dst + k, t[(k / 12) * 13 + k % 12]);
   }
 }
 
@@ -95,8 +145,10 @@ __global__ void spinor_export_kernel(Geom g, SpinorRef e, SpinorRef o, const dou
 // (the time factor alpha^2 after the sum, the spatial ones per site).
 __global__ void __launch_bounds__(kBlock) cpp_kernel(Geom g, SpinorRef e, SpinorRef o,
                                                      const double* __restrict__ alpha, const double* __restrict__ sprof,
-                                                     const int* __restrict__ x0src, double* __restrict__ cpp) {
+                                                     const int* __restrict__ x0src, const int* __restrict__ mask,
+                                                     double* __restrict__ cpp) {
   const int x0 = blockIdx.x, slot = blockIdx.y;
+  if (mask && !mask[slot]) return;
   __shared__ double lds[kBlock / 64];
   double acc = 0.0;
   for (int par = 0; par < 2; ++par) {
@@ -202,39 +254,38 @@ hipError_t launch_point_sources(const Geom& g, const int site[4], int c0, int nc
   return hipGetLastError();
 }
 
-hipError_t launch_gauge_reorder(const Geom& g, const double2* U_aos, void* U_eo[2], int prec, hipStream_t st) {
-  const long V = 2L * g.Vh;
-  const dim3 grid((unsigned)((V + kBlock - 1) / kBlock));
-  switch (prec) {
-    case F64: hipLaunchKernelGGL(gauge_reorder_kernel<F64>, grid, dim3(kBlock), 0, st, g, U_aos, U_eo[0], U_eo[1]); break;
-    case F32: hipLaunchKernelGGL(gauge_reorder_kernel<F32>, grid, dim3(kBlock), 0, st, g, U_aos, U_eo[0], U_eo[1]); break;
-    case F16: hipLaunchKernelGGL(gauge_reorder_kernel<F16>, grid, dim3(kBlock), 0, st, g, U_aos, U_eo[0], U_eo[1]); break;
-    default: return hipErrorInvalidValue;
+hipError_t launch_gauge_reorder(const Geom& g, const double2* U_aos, void* const U64[2], void* const U32[2],
+                                void* const U16[2], hipStream_t st) {
+  GaugeDst o;
+  for (int p = 0; p < 2; ++p) {
+    o.f64[p] = static_cast<double2*>(U64[p]);
+    o.f32[p] = U32 ? static_cast<float2*>(U32[p]) : nullptr;
+    o.f16[p] = U16 ? static_cast<unsigned*>(U16[p]) : nullptr;
   }
+  hipLaunchKernelGGL(gauge_reorder_kernel, dim3((g.Vh + kLinkPairs - 1) / kLinkPairs), dim3(64), 0, st, g, U_aos, o);
   return hipGetLastError();
 }
 
-hipError_t launch_spinor_import(const Geom& g, const double2* aos, int nslots, long aos_ss, int p, SpinorRef dst,
-                                const double* alpha_mul, const double* sprof, hipStream_t st) {
-  if (dst.prec != F64 || nslots <= 0) return hipErrorInvalidValue;
-  const dim3 grid((g.Vh + kBlock - 1) / kBlock, nslots);
-  hipLaunchKernelGGL(spinor_import_kernel, grid, dim3(kBlock), 0, st, g, aos, aos_ss, p, dst, alpha_mul, sprof);
+hipError_t launch_spinor_import(const Geom& g, const double2* aos, int nslots, long aos_ss, SpinorRef even,
+                                SpinorRef odd, const double* alpha_mul, const double* sprof, hipStream_t st) {
+  if (even.prec != F64 || odd.prec != F64 || nslots <= 0) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(spinor_import_kernel, dim3((g.Vh + kPairs - 1) / kPairs, nslots), dim3(64), 0, st, g, aos, aos_ss,
+                     even, odd, alpha_mul, sprof);
   return hipGetLastError();
 }
 
 hipError_t launch_spinor_export(const Geom& g, SpinorRef even, SpinorRef odd, int nslots, const double* alpha_div,
                                 const double* sprof, double2* aos, long aos_ss, hipStream_t st) {
   if (even.prec != F64 || odd.prec != F64 || nslots <= 0) return hipErrorInvalidValue;
-  const long V = 2L * g.Vh;
-  const dim3 grid((unsigned)((V + kBlock - 1) / kBlock), nslots);
-  hipLaunchKernelGGL(spinor_export_kernel, grid, dim3(kBlock), 0, st, g, even, odd, alpha_div, sprof, aos, aos_ss);
+  hipLaunchKernelGGL(spinor_export_kernel, dim3((g.Vh + kPairs - 1) / kPairs, nslots), dim3(64), 0, st, g, even, odd,
+                     alpha_div, sprof, aos, aos_ss);
   return hipGetLastError();
 }
 
 hipError_t launch_cpp(const Geom& g, SpinorRef even, SpinorRef odd, int nslots, const double* alpha,
-                      const double* sprof, const int* x0src, double* cpp, hipStream_t st) {
+                      const double* sprof, const int* x0src, const int* mask, double* cpp, hipStream_t st) {
   if (even.prec != F64 || odd.prec != F64 || nslots <= 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(cpp_kernel, dim3(g.T, nslots), dim3(kBlock), 0, st, g, even, odd, alpha, sprof, x0src, cpp);
+  hipLaunchKernelGGL(cpp_kernel, dim3(g.T, nslots), dim3(kBlock), 0, st, g, even, odd, alpha, sprof, x0src, mask, cpp);
   return hipGetLastError();
 }
 

@@ -160,10 +160,8 @@ int mass_entry(dp_ctx* c, double M, MassEntry** out) {
   }
   DP_HIP(c, c->bad_flag.reserve(sizeof(int)));
   DP_HIP(c, hipMemsetAsync(c->bad_flag.p, 0, sizeof(int), c->stream));
-  DP_HIP(c, launch_clover_invert(g, c->C64[1].as<double2>(), 4.0 + M, m->a64.as<double2>(), c->bad_flag.as<int>(),
-                                 c->stream));
-  DP_HIP(c, launch_clover_convert(g, m->a64.as<double2>(), m->a32.p, nullptr, F32, c->stream));
-  DP_HIP(c, launch_clover_convert(g, m->a64.as<double2>(), m->a16.p, m->s16.as<float>(), F16, c->stream));
+  DP_HIP(c, launch_clover_invert(g, c->C64[1].as<double2>(), 4.0 + M, m->a64.as<double2>(), m->a32.p, m->a16.p,
+                                 m->s16.as<float>(), c->bad_flag.as<int>(), c->stream));
   int bad = 0;
   DP_HIP(c, hipMemcpyAsync(&bad, c->bad_flag.p, sizeof(int), hipMemcpyDeviceToHost, c->stream));
   DP_HIP(c, hipStreamSynchronize(c->stream));
@@ -493,8 +491,7 @@ int clover_zero(dp_ctx* c) {
 
 int clover_convert_all(dp_ctx* c) {
   for (int p = 0; p < 2; ++p) {
-    DP_HIP(c, launch_clover_convert(c->g, c->C64[p].as<double2>(), c->C32[p].p, nullptr, F32, c->stream));
-    DP_HIP(c, launch_clover_convert(c->g, c->C64[p].as<double2>(), c->C16[p].p, c->C16s[p].as<float>(), F16,
+    DP_HIP(c, launch_clover_convert(c->g, c->C64[p].as<double2>(), c->C32[p].p, c->C16[p].p, c->C16s[p].as<float>(),
                                     c->stream));
   }
   return DP_OK;
@@ -508,10 +505,12 @@ int set_gauge_common(dp_ctx* c, const double2* Udev, hipStream_t st) {
   const Geom& g = c->g;
   for (int prec = 0; prec < 3; ++prec) {
     for (int p = 0; p < 2; ++p) DP_HIP(c, c->U[prec][p].reserve((size_t)g.Vp * link_site_bytes(prec)));
-    void* dst[2] = {c->U[prec][0].p, c->U[prec][1].p};
-    DP_HIP(c, launch_gauge_reorder(g, Udev, dst, prec, st));
-    c->have_U[prec] = true;
   }
+  void* dst[3][2];
+  for (int prec = 0; prec < 3; ++prec)
+    for (int p = 0; p < 2; ++p) dst[prec][p] = c->U[prec][p].p;
+  DP_HIP(c, launch_gauge_reorder(g, Udev, dst[F64], dst[F32], dst[F16], st));
+  for (int prec = 0; prec < 3; ++prec) c->have_U[prec] = true;
   DP_HIP(c, hipStreamSynchronize(st));
   c->clover_kind = 0;
   c->csw = 0.0;
@@ -534,7 +533,7 @@ int clover_sf(dp_ctx* c, double csw) {
     DP_HIP(c, Cp[p].reserve((size_t)gp.Vp * clover_site_bytes(F64)));
   }
   void* up[2] = {Up[0].p, Up[1].p};
-  DP_HIP(c, launch_gauge_reorder(gp, c->sf_ext.as<double2>(), up, F64, c->stream));
+  DP_HIP(c, launch_gauge_reorder(gp, c->sf_ext.as<double2>(), up, nullptr, nullptr, c->stream));
   double2* cp[2] = {Cp[0].as<double2>(), Cp[1].as<double2>()};
   if (csw != 0.0) {
     const double2* u64[2] = {Up[0].as<double2>(), Up[1].as<double2>()};
@@ -841,8 +840,7 @@ int apply_run(dp_ctx* c, Workspace& w, const double2* in, double2* out, int n, i
   const int dag = (flags & DP_DAGGER) ? 1 : 0;
   const Geom& g = c->g;
   const long col = 2L * g.Vh * 12;  // double2 per column
-  DP_HIP(c, launch_spinor_import(g, in, n, col, 0, w.eta_e.ref(), nullptr, nullptr, c->stream));
-  DP_HIP(c, launch_spinor_import(g, in, n, col, 1, w.eta_o.ref(), nullptr, nullptr, c->stream));
+  DP_HIP(c, launch_spinor_import(g, in, n, col, w.eta_e.ref(), w.eta_o.ref(), nullptr, nullptr, c->stream));
   // inputs in the compute precision: even in r, odd in s (Vh sites each)
   const Field* ie = &w.eta_e;
   const Field* io = &w.eta_o;

@@ -1240,9 +1240,8 @@ extern "C" int dp_sap_precondition(dp_ctx* c, const double* r, const dp_sap_para
   const size_t bytes = (size_t)2 * g.Vh * 12 * sizeof(double2);
   DP_HIP(c, c->scratch_aos.reserve(bytes));
   DP_HIP(c, hipMemcpyAsync(c->scratch_aos.p, r, bytes, hipMemcpyHostToDevice, c->stream));
-  for (int par = 0; par < 2; ++par)
-    DP_HIP(c, launch_spinor_import(g, c->scratch_aos.as<double2>(), 1, 0, par, s.r.ref(par), nullptr, nullptr,
-                                   c->stream));
+  DP_HIP(c, launch_spinor_import(g, c->scratch_aos.as<double2>(), 1, 0, s.r.ref(0), s.r.ref(1), nullptr, nullptr,
+                                 c->stream));
   DP_TRY(precondition(c, s, b, p->ncy, p->nmr, s.r, s.z[0]));
   DP_HIP(c, launch_spinor_export(g, s.z[0].ref(0), s.z[0].ref(1), 1, nullptr, nullptr, c->scratch_aos.as<double2>(),
                                  0, c->stream));
@@ -1263,9 +1262,8 @@ int sap_solve(dp_ctx* c, const Blocking& b, const double2* eta_dev, const dp_sap
   SapState& s = *c->sap;
   const size_t bytes = (size_t)2 * g.Vh * 12 * sizeof(double2);
   // eta' = beta eta
-  for (int par = 0; par < 2; ++par)
-    DP_HIP(c, launch_spinor_import(g, eta_dev, 1, 0, par, s.eta.ref(par), s.alpha.as<double>(), space_profile(c),
-                                   c->stream));
+  DP_HIP(c, launch_spinor_import(g, eta_dev, 1, 0, s.eta.ref(0), s.eta.ref(1), s.alpha.as<double>(),
+                                 space_profile(c), c->stream));
   zc e2;
   DP_TRY(vec_dot(c, s, s.eta, s.eta, &e2));
   const double target = p->r * std::sqrt(e2.real());
@@ -1351,7 +1349,7 @@ int sap_solve(dp_ctx* c, const Blocking& b, const double2* eta_dev, const dp_sap
   }
   if (cpp) {
     DP_HIP(c, s.cpp.reserve(sizeof(double) * g.T));
-    DP_HIP(c, launch_cpp(g, s.x.ref(0), s.x.ref(1), 1, s.alpha.as<double>(), space_profile(c), nullptr,
+    DP_HIP(c, launch_cpp(g, s.x.ref(0), s.x.ref(1), 1, s.alpha.as<double>(), space_profile(c), nullptr, nullptr,
                          s.cpp.as<double>(), c->stream));
     DP_HIP(c, hipMemcpyAsync(cpp, s.cpp.p, sizeof(double) * g.T, hipMemcpyDeviceToHost, c->stream));
   }
