@@ -35,26 +35,56 @@ dp_batch::~dp_batch() {
 
 namespace {
 
-int upload_slot(dp_batch* b, int s) {
+// The tables of one request (slot_record_bytes) into its slots, one block per
+// slot.
+__global__ void __launch_bounds__(64) slot_tables_kernel(const double* __restrict__ rec, int T, double* ratio,
+                                                         double* alpha, double* m4, const void** a64,
+                                                         const void** a32, const void** a16, const float** s16,
+                                                         int* x0src) {
+  const int* ints = reinterpret_cast<const int*>(rec + 5 * T + 5);
+  const int s = ints[2 + blockIdx.x];
+  for (int t = threadIdx.x; t < T; t += 64) alpha[(long)s * T + t] = rec[t];
+  for (int t = threadIdx.x; t < 4 * T; t += 64) ratio[(long)s * 4 * T + t] = rec[T + t];
+  if (threadIdx.x == 0) {
+    m4[s] = rec[5 * T];
+    const void* const* p = reinterpret_cast<const void* const*>(rec + 5 * T + 1);
+    a64[s] = p[0];
+    a32[s] = p[1];
+    a16[s] = p[2];
+    s16[s] = static_cast<const float*>(p[3]);
+    x0src[s] = ints[0];
+  }
+}
+
+// the tables of a request (one mass, profile and source timeslice) for the
+// slots sl: one copy and one launch (a copy of its own, and waited for, for
+// each of a slot's eight entries took 1.1 of the 5.7 ms of a 12-column solve
+// at 8^3x16).  The host record is used again only after a later wait.
+int upload_slots(dp_batch* b, const std::vector<int>& sl) {
   dp_ctx* c = b->c;
   Workspace& w = b->w;
-  dp_batch::Slot& sl = b->slots[s];
-  const int T = c->g.T;
-  std::vector<double> rt(4 * T);
-  ratio_tables(T, c->bc_t, sl.alpha.data(), rt.data());
-  DP_TRY(h2d(c, w.ratio.as<double>() + (size_t)s * 4 * T, rt.data(), sizeof(double) * 4 * T));
-  DP_TRY(h2d(c, w.alpha.as<double>() + (size_t)s * T, sl.alpha.data(), sizeof(double) * T));
-  const double m4 = 4.0 + sl.me->M;
-  DP_TRY(h2d(c, w.m4.as<double>() + s, &m4, sizeof(double)));
-  const void* p3[3] = {sl.me->a64.p, sl.me->a32.p, sl.me->a16.p};
-  for (int k = 0; k < 3; ++k) {
-    DP_TRY(h2d(c, static_cast<const void**>(w.ainv_ptr[k].p) + s, &p3[k], sizeof(void*)));
-    w.h_ainv[k][s] = p3[k];
+  const dp_batch::Slot& h = b->slots[sl[0]];
+  const int T = c->g.T, n = (int)sl.size();
+  double* rec = w.h_up.as<double>();
+  std::copy(h.alpha.begin(), h.alpha.end(), rec);
+  ratio_tables(T, c->bc_t, h.alpha.data(), rec + T);
+  rec[5 * T] = 4.0 + h.me->M;
+  const void* p[4] = {h.me->a64.p, h.me->a32.p, h.me->a16.p, h.me->s16.p};
+  std::memcpy(rec + 5 * T + 1, p, sizeof p);
+  int* ints = reinterpret_cast<int*>(rec + 5 * T + 5);
+  ints[0] = h.x0;
+  ints[1] = n;
+  for (int j = 0; j < n; ++j) {
+    ints[2 + j] = sl[j];
+    for (int k = 0; k < 3; ++k) w.h_ainv[k][sl[j]] = p[k];
+    w.h_ainv_scale[sl[j]] = static_cast<const float*>(p[3]);
   }
-  const float* s16 = sl.me->s16.as<float>();
-  DP_TRY(h2d(c, static_cast<const float**>(w.ainv_scale_ptr.p) + s, &s16, sizeof(float*)));
-  w.h_ainv_scale[s] = s16;
-  DP_TRY(h2d(c, w.x0src.as<int>() + s, &sl.x0, sizeof(int)));
+  DP_HIP(c, hipMemcpyAsync(w.up.p, rec, slot_record_bytes(T, n), hipMemcpyHostToDevice, c->stream));
+  hipLaunchKernelGGL(slot_tables_kernel, dim3(n), dim3(64), 0, c->stream, w.up.as<double>(), T, w.ratio.as<double>(),
+                     w.alpha.as<double>(), w.m4.as<double>(), w.ainv_ptr[0].as<const void*>(),
+                     w.ainv_ptr[1].as<const void*>(), w.ainv_ptr[2].as<const void*>(),
+                     w.ainv_scale_ptr.as<const float*>(), w.x0src.as<int>());
+  DP_HIP(c, hipGetLastError());
   return DP_OK;
 }
 
@@ -131,10 +161,17 @@ int outer_step(dp_batch* b, const std::vector<int>& pend, std::vector<int>& fini
       q.iters = h.iters;
       q.max_iter = h.max_iter;
       q.shadow = h.has_inner && h.last_left == 2 ? 1 : 0;
-      DP_HIP(c, hipMemcpyAsync(w.sc.as<SlotScalars>() + s, &q, sizeof q, hipMemcpyHostToDevice, c->stream));
     }
   }
   if (!any_start) return DP_OK;
+  for (int s = 0; s < n;) {  // neighbouring slots in one copy
+    int e = s;
+    while (e < n && start[e]) ++e;
+    if (e > s)
+      DP_HIP(c, hipMemcpyAsync(w.sc.as<SlotScalars>() + s, hsc + s, sizeof(SlotScalars) * (e - s),
+                               hipMemcpyHostToDevice, c->stream));
+    s = e + 1;
+  }
   for (int s = 0; s < n; ++s) hscale[s] = start[s] ? 1.0 / b->slots[s].scale : 0.0;
   DP_HIP(c, hipMemcpyAsync(w.slot_scale.p, hscale, sizeof(double) * n, hipMemcpyHostToDevice, c->stream));
   b->m_outer = start;
@@ -240,20 +277,25 @@ int finish(dp_batch* b, const std::vector<int>& fin) {
   DP_TRY(hop(c, w, 0, n, F64, 1, 0, EPI_INV_SUB, 0.0, w.x64, w.to64, &w.eta_o, w.mask_outer.as<int>()));
   DP_HIP(c, launch_cpp(g, w.x64.ref(), w.to64.ref(), n, w.alpha.as<double>(), space_profile(c), w.x0src.as<int>(),
                        w.mask_outer.as<int>(), w.cpp.as<double>(), c->stream));
-  for (int s : fin) {
-    dp_batch::Slot& h = b->slots[s];
-    h.hops += 1;
-    if (h.S_dev)
-      DP_HIP(c, launch_spinor_export(g, w.x64.ref(s), w.to64.ref(s), 1, w.alpha.as<double>() + (size_t)s * g.T,
-                                     space_profile(c), static_cast<double2*>(h.S_dev), 0, c->stream));
+  const long col = 2L * g.Vh * 12;  // double2 per column
+  for (size_t k = 0; k < fin.size();) {  // neighbouring slots with neighbouring solutions in one launch
+    const int s = fin[k];
+    double2* S = static_cast<double2*>(b->slots[s].S_dev);
+    size_t m = 1;
+    while (S && k + m < fin.size() && fin[k + m] == s + (int)m && b->slots[s + m].S_dev == S + m * col) ++m;
+    if (S)
+      DP_HIP(c, launch_spinor_export(g, w.x64.ref(s), w.to64.ref(s), (int)m, w.alpha.as<double>() + (size_t)s * g.T,
+                                     space_profile(c), S, col, c->stream));
+    k += m;
   }
-  std::vector<double> all((size_t)n * g.T);
-  DP_HIP(c, hipMemcpyAsync(all.data(), w.cpp.p, sizeof(double) * g.T * n, hipMemcpyDeviceToHost, c->stream));
+  double* all = w.h_cpp.as<double>();
+  DP_HIP(c, hipMemcpyAsync(all, w.cpp.p, sizeof(double) * g.T * n, hipMemcpyDeviceToHost, c->stream));
   DP_HIP(c, hipStreamSynchronize(c->stream));
   const double t = now_s();
   for (int s : fin) {
     dp_batch::Slot& h = b->slots[s];
-    h.cpp.assign(all.begin() + (size_t)s * g.T, all.begin() + (size_t)(s + 1) * g.T);
+    h.hops += 1;
+    h.cpp.assign(all + (size_t)s * g.T, all + (size_t)(s + 1) * g.T);
     h.state = dp_batch::DONE;
     h.in_inner = false;
     h.t_done = t;
@@ -353,12 +395,18 @@ int dp_batch_admit(dp_batch* b, int ncols, const void* eta_dev, void* S_dev, dou
     h.max_iter = max_iter;
     h.x0 = x0_src;
     h.t_admit = t0;
-    DP_TRY(upload_slot(b, s));
-    const double2* src = static_cast<const double2*>(eta_dev) + (size_t)j * col;
-    const double* am = w.alpha.as<double>() + (size_t)s * g.T;
-    DP_HIP(c, launch_spinor_import(g, src, 1, 0, w.eta_e.ref(s), w.eta_o.ref(s), am, space_profile(c), c->stream));
     pend[s] = 1;
     if (slots_out) slots_out[j] = s;
+  }
+  DP_TRY(upload_slots(b, fr));
+  for (int j = 0; j < ncols;) {  // neighbouring slots in one launch
+    const int s = fr[j];
+    int m = 1;
+    while (j + m < ncols && fr[j + m] == s + m) ++m;
+    DP_HIP(c, launch_spinor_import(g, static_cast<const double2*>(eta_dev) + (size_t)j * col, m, col, w.eta_e.ref(s),
+                                   w.eta_o.ref(s), w.alpha.as<double>() + (size_t)s * g.T, space_profile(c),
+                                   c->stream));
+    j += m;
   }
   const int n = b->nslots;
   b->m_outer = pend;
@@ -368,11 +416,12 @@ int dp_batch_admit(dp_batch* b, int ncols, const void* eta_dev, void* S_dev, dou
   double* sums = w.h_sums.as<double>();
   for (int par = 0; par < 2; ++par) {
     DP_TRY(blas(c, w, 0, n, OP_NORM, F64, m_out, {nullptr, par ? &w.eta_o : &w.eta_e}, FIN_STORE));
-    DP_HIP(c, hipMemcpyAsync(sums, w.out_sums.p, sizeof(double) * 4 * n, hipMemcpyDeviceToHost, c->stream));
-    DP_HIP(c, hipStreamSynchronize(c->stream));
-    for (int s = 0; s < n; ++s)
-      if (pend[s]) b->slots[s].eta2 += sums[4 * s];
+    DP_HIP(c, hipMemcpyAsync(sums + (size_t)4 * n * par, w.out_sums.p, sizeof(double) * 4 * n, hipMemcpyDeviceToHost,
+                             c->stream));
   }
+  DP_HIP(c, hipStreamSynchronize(c->stream));
+  for (int s = 0; s < n; ++s)
+    if (pend[s]) b->slots[s].eta2 = sums[4 * s] + sums[4 * (n + s)];
   for (int s = 0; s < n; ++s)
     if (pend[s] && !std::isfinite(b->slots[s].eta2)) {
       for (int t = 0; t < n; ++t)
@@ -611,7 +660,7 @@ int dp_solve(dp_ctx* c, const double* eta, int nrhs, const dp_params* p, double*
   DP_TRY(validate_params(c, nrhs, p));
   const size_t bytes = (size_t)nrhs * 2 * c->g.Vh * 12 * sizeof(double2);
   // sources and solutions in separate halves (an FP64 retry reads a source again)
-  DP_HIP(c, c->scratch_aos.reserve(S ? 2 * bytes : bytes));
+  DP_HIP(c, reserve(c, c->scratch_aos, S ? 2 * bytes : bytes));
   double2* deta = c->scratch_aos.as<double2>();
   double2* dS = S ? deta + bytes / sizeof(double2) : nullptr;
   DP_HIP(c, hipMemcpyAsync(deta, eta, bytes, hipMemcpyHostToDevice, c->stream));

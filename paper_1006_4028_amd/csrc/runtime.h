@@ -110,7 +110,10 @@ struct Workspace {
   // per-slot device tables
   DevBuf ratio, m4, mask_inner, mask_outer, ainv_ptr[3], ainv_scale_ptr, sc, partials, out_sums, slot_scale, x0src,
       alpha, cpp;
-  HostBuf h_sc, h_sums, h_mask, h_scale;
+  HostBuf h_sc, h_sums, h_mask, h_scale, h_cpp;
+  // a request's slot tables on their way to the device (admission)
+  HostBuf h_up;
+  DevBuf up;
   // host copy of the slots' A_oo^-1 fields per precision and FP16 scales
   std::vector<const void*> h_ainv[3];
   std::vector<const float*> h_ainv_scale;
@@ -141,6 +144,11 @@ struct dp_ctx {
   double ct_tilde = 1.0;
   dp::DevBuf sf_ext;
   std::vector<dp::MassEntry*> masses;
+  // buffers of dropped inverses, taken up again by the next masses (all
+  // entries of a ctx have the same sizes): at most kMassPool, given back when
+  // an allocation fails and with the ctx
+  static constexpr size_t kMassPool = 4;
+  std::vector<dp::MassEntry*> mass_pool;
   int open_batches = 0;
 
   double M = 0.0;
@@ -246,9 +254,17 @@ struct TraceRange {
 };
 
 bool env_pad();
+// DevBuf::reserve and Field::alloc; a failure gives the ctx's pooled buffers
+// back and tries again
+hipError_t reserve(dp_ctx* c, DevBuf& b, size_t bytes);
+hipError_t alloc(dp_ctx* c, Field& f, int prec, int nslots);
 double now_s();
 void ratio_tables(int T, int bc_t, const double* alpha, double* out);
 int mass_entry(dp_ctx* c, double M, MassEntry** out);
+// bytes of the tables of one request on their way to n slots: alpha [T],
+// ratios [4][T], 4 + M, the A_oo^-1 pointers [3] and scale pointer, x0 and
+// column count (ints), the slot numbers (ints)
+inline size_t slot_record_bytes(int T, int n) { return sizeof(double) * (5 * T + 6) + sizeof(int) * n; }
 int ensure_ws(dp_ctx* c, Workspace& w, int nslots, int prec);
 int h2d(dp_ctx* c, void* dst, const void* src, size_t bytes);
 int upload_mask(dp_ctx* c, Workspace& w, DevBuf& dst, const std::vector<int>& m, int staging);

@@ -74,6 +74,26 @@ bool env_pad() {
   return v;
 }
 
+namespace {
+template <class F>
+hipError_t with_pool_released(dp_ctx* c, F f) {
+  hipError_t e = f();
+  if (e != hipErrorOutOfMemory || c->mass_pool.empty()) return e;
+  (void)hipGetLastError();
+  for (auto* m : c->mass_pool) delete m;
+  c->mass_pool.clear();
+  return f();
+}
+}  // namespace
+
+hipError_t reserve(dp_ctx* c, DevBuf& b, size_t bytes) {
+  return with_pool_released(c, [&] { return b.reserve(bytes); });
+}
+
+hipError_t alloc(dp_ctx* c, Field& f, int prec, int nslots) {
+  return with_pool_released(c, [&] { return f.alloc(c->g, prec, nslots); });
+}
+
 double now_s() {
   return std::chrono::duration<double>(std::chrono::steady_clock::now().time_since_epoch()).count();
 }
@@ -147,7 +167,13 @@ int mass_entry(dp_ctx* c, double M, MassEntry** out) {
       return DP_OK;
     }
   const Geom& g = c->g;
-  auto* m = new (std::nothrow) MassEntry;
+  MassEntry* m = nullptr;
+  if (!c->mass_pool.empty()) {
+    m = c->mass_pool.back();
+    c->mass_pool.pop_back();
+  } else {
+    m = new (std::nothrow) MassEntry;
+  }
   if (!m) return fail(c, DP_ERR_OOM, "host allocation failed");
   m->M = M;
   hipError_t e = m->a64.reserve((size_t)g.Vp * clover_site_bytes(F64));
@@ -180,31 +206,34 @@ int ensure_ws(dp_ctx* c, Workspace& w, int nslots, int prec) {
   const int n = std::max(nslots, w.nslots);
   const int px = prec == F16 ? F32 : prec;
   Field* f64s[] = {&w.eta_e, &w.eta_o, &w.b64, &w.x64, &w.r64, &w.t64, &w.to64};
-  for (Field* f : f64s) DP_HIP(c, f->alloc(g, F64, n));
+  for (Field* f : f64s) DP_HIP(c, alloc(c, *f, F64, n));
   Field* fin[] = {&w.r, &w.p, &w.v, &w.s, &w.t, &w.to};
-  for (Field* f : fin) DP_HIP(c, f->alloc(g, prec, n));
-  DP_HIP(c, w.rh.alloc(g, rh_prec(prec), n));
-  DP_HIP(c, w.x.alloc(g, px, n));
+  for (Field* f : fin) DP_HIP(c, alloc(c, *f, prec, n));
+  DP_HIP(c, alloc(c, w.rh, rh_prec(prec), n));
+  DP_HIP(c, alloc(c, w.x, px, n));
   const int nb = std::max(reduction_blocks(g), hop_blocks(g));
-  DP_HIP(c, w.ratio.reserve(sizeof(double) * 4 * g.T * n));
-  DP_HIP(c, w.m4.reserve(sizeof(double) * n));
-  DP_HIP(c, w.mask_inner.reserve(sizeof(int) * n));
-  DP_HIP(c, w.mask_outer.reserve(sizeof(int) * n));
+  DP_HIP(c, reserve(c, w.ratio, sizeof(double) * 4 * g.T * n));
+  DP_HIP(c, reserve(c, w.m4, sizeof(double) * n));
+  DP_HIP(c, reserve(c, w.mask_inner, sizeof(int) * n));
+  DP_HIP(c, reserve(c, w.mask_outer, sizeof(int) * n));
   for (int k = 0; k < 3; ++k) {
-    DP_HIP(c, w.ainv_ptr[k].reserve(sizeof(void*) * n));
+    DP_HIP(c, reserve(c, w.ainv_ptr[k], sizeof(void*) * n));
     w.h_ainv[k].assign(n, nullptr);
   }
-  DP_HIP(c, w.ainv_scale_ptr.reserve(sizeof(float*) * n));
+  DP_HIP(c, reserve(c, w.ainv_scale_ptr, sizeof(float*) * n));
   w.h_ainv_scale.assign(n, nullptr);
-  DP_HIP(c, w.sc.reserve(sizeof(SlotScalars) * n));
-  DP_HIP(c, w.partials.reserve(sizeof(double) * kRedMax * nb * n));
-  DP_HIP(c, w.out_sums.reserve(sizeof(double) * 4 * n));
-  DP_HIP(c, w.slot_scale.reserve(sizeof(double) * n));
-  DP_HIP(c, w.x0src.reserve(sizeof(int) * n));
-  DP_HIP(c, w.alpha.reserve(sizeof(double) * g.T * n));
-  DP_HIP(c, w.cpp.reserve(sizeof(double) * g.T * n));
+  DP_HIP(c, reserve(c, w.sc, sizeof(SlotScalars) * n));
+  DP_HIP(c, reserve(c, w.partials, sizeof(double) * kRedMax * nb * n));
+  DP_HIP(c, reserve(c, w.out_sums, sizeof(double) * 4 * n));
+  DP_HIP(c, reserve(c, w.slot_scale, sizeof(double) * n));
+  DP_HIP(c, reserve(c, w.x0src, sizeof(int) * n));
+  DP_HIP(c, reserve(c, w.alpha, sizeof(double) * g.T * n));
+  DP_HIP(c, reserve(c, w.cpp, sizeof(double) * g.T * n));
   DP_HIP(c, w.h_sc.reserve(sizeof(SlotScalars) * n));
-  DP_HIP(c, w.h_sums.reserve(sizeof(double) * 4 * n));
+  DP_HIP(c, w.h_sums.reserve(sizeof(double) * 8 * n));
+  DP_HIP(c, w.h_cpp.reserve(sizeof(double) * g.T * n));
+  DP_HIP(c, w.h_up.reserve(slot_record_bytes(g.T, n)));
+  DP_HIP(c, reserve(c, w.up, slot_record_bytes(g.T, n)));
   DP_HIP(c, w.h_mask.reserve(sizeof(int) * 4 * n));
   DP_HIP(c, w.h_scale.reserve(sizeof(double) * (4 * g.T + 8) * n));
   DP_HIP(c, hipMemsetAsync(w.mask_inner.p, 0, sizeof(int) * n, c->stream));
@@ -449,6 +478,7 @@ dp_ctx::~dp_ctx() {
   }
   for (auto e : ev_free) (void)hipEventDestroy(e);
   for (auto* m : masses) delete m;
+  for (auto* m : mass_pool) delete m;
   dp::sap_free(sap);
   if (stream) (void)hipStreamDestroy(stream);
 }
@@ -467,7 +497,10 @@ int drop_masses(dp_ctx* c) {
     c->solve_batch = nullptr;
   }
   if (c->open_batches > 0) return fail(c, DP_ERR_BAD_STATE, "a batch is open on this context");
-  for (auto* m : c->masses) delete m;
+  for (auto* m : c->masses) {
+    if (c->mass_pool.size() < dp_ctx::kMassPool) c->mass_pool.push_back(m);
+    else delete m;
+  }
   c->masses.clear();
   c->apply_key.clear();
   return DP_OK;
@@ -477,10 +510,10 @@ int drop_masses(dp_ctx* c) {
 int clover_zero(dp_ctx* c) {
   const Geom& g = c->g;
   for (int p = 0; p < 2; ++p) {
-    DP_HIP(c, c->C64[p].reserve((size_t)g.Vp * clover_site_bytes(F64)));
-    DP_HIP(c, c->C32[p].reserve((size_t)g.Vp * clover_site_bytes(F32)));
-    DP_HIP(c, c->C16[p].reserve((size_t)g.Vp * clover_site_bytes(F16)));
-    DP_HIP(c, c->C16s[p].reserve((size_t)g.Vp * sizeof(float)));
+    DP_HIP(c, reserve(c, c->C64[p], (size_t)g.Vp * clover_site_bytes(F64)));
+    DP_HIP(c, reserve(c, c->C32[p], (size_t)g.Vp * clover_site_bytes(F32)));
+    DP_HIP(c, reserve(c, c->C16[p], (size_t)g.Vp * clover_site_bytes(F16)));
+    DP_HIP(c, reserve(c, c->C16s[p], (size_t)g.Vp * sizeof(float)));
     DP_HIP(c, hipMemsetAsync(c->C64[p].p, 0, c->C64[p].bytes, c->stream));
     DP_HIP(c, hipMemsetAsync(c->C32[p].p, 0, c->C32[p].bytes, c->stream));
     DP_HIP(c, hipMemsetAsync(c->C16[p].p, 0, c->C16[p].bytes, c->stream));
@@ -504,7 +537,7 @@ int set_gauge_common(dp_ctx* c, const double2* Udev, hipStream_t st) {
   c->ct_tilde = 1.0;
   const Geom& g = c->g;
   for (int prec = 0; prec < 3; ++prec) {
-    for (int p = 0; p < 2; ++p) DP_HIP(c, c->U[prec][p].reserve((size_t)g.Vp * link_site_bytes(prec)));
+    for (int p = 0; p < 2; ++p) DP_HIP(c, reserve(c, c->U[prec][p], (size_t)g.Vp * link_site_bytes(prec)));
   }
   void* dst[3][2];
   for (int prec = 0; prec < 3; ++prec)
@@ -529,8 +562,8 @@ int clover_sf(dp_ctx* c, double csw) {
   gp.Vp = gp.Vh;
   DevBuf Up[2], Cp[2];
   for (int p = 0; p < 2; ++p) {
-    DP_HIP(c, Up[p].reserve((size_t)gp.Vp * link_site_bytes(F64)));
-    DP_HIP(c, Cp[p].reserve((size_t)gp.Vp * clover_site_bytes(F64)));
+    DP_HIP(c, reserve(c, Up[p], (size_t)gp.Vp * link_site_bytes(F64)));
+    DP_HIP(c, reserve(c, Cp[p], (size_t)gp.Vp * clover_site_bytes(F64)));
   }
   void* up[2] = {Up[0].p, Up[1].p};
   DP_HIP(c, launch_gauge_reorder(gp, c->sf_ext.as<double2>(), up, nullptr, nullptr, c->stream));
@@ -627,7 +660,7 @@ int dp_set_gauge(dp_ctx* c, const double* U) {
   if (!c || !U) return fail(c, DP_ERR_INVALID_ARG, "null argument");
   DP_HIP(c, hipSetDevice(c->device));
   const size_t bytes = (size_t)2 * c->g.Vh * 4 * 9 * sizeof(double2);
-  DP_HIP(c, c->scratch_aos.reserve(bytes));
+  DP_HIP(c, reserve(c, c->scratch_aos, bytes));
   DP_HIP(c, hipMemcpyAsync(c->scratch_aos.p, U, bytes, hipMemcpyHostToDevice, c->stream));
   int rc = set_gauge_common(c, c->scratch_aos.as<double2>(), c->stream);
   c->scratch_aos.release();
@@ -647,7 +680,7 @@ int dp_set_gauge_sf(dp_ctx* c, const double* U_ext, double ct_tilde) {
   DP_HIP(c, hipSetDevice(c->device));
   const Geom& g = c->g;
   const size_t per_t = (size_t)2 * g.Vsh * 4 * 9;  // double2 per timeslice
-  DP_HIP(c, c->sf_ext.reserve(sizeof(double2) * per_t * (g.T + 2)));
+  DP_HIP(c, reserve(c, c->sf_ext, sizeof(double2) * per_t * (g.T + 2)));
   DP_HIP(c, hipMemcpyAsync(c->sf_ext.p, U_ext, sizeof(double2) * per_t * (g.T + 2), hipMemcpyHostToDevice,
                            c->stream));
   // the interior links, as dp_set_gauge (which clears the SF state: set it after)
@@ -706,9 +739,9 @@ int dp_set_clover_field(dp_ctx* c, const double* Cf) {
   DP_HIP(c, hipSetDevice(c->device));
   DP_TRY(drop_masses(c));
   const size_t bytes = (size_t)2 * c->g.Vh * 144 * sizeof(double2);
-  DP_HIP(c, c->scratch_aos.reserve(bytes));
+  DP_HIP(c, reserve(c, c->scratch_aos, bytes));
   DP_HIP(c, hipMemcpyAsync(c->scratch_aos.p, Cf, bytes, hipMemcpyHostToDevice, c->stream));
-  DP_HIP(c, c->bad_flag.reserve(sizeof(int)));
+  DP_HIP(c, reserve(c, c->bad_flag, sizeof(int)));
   DP_HIP(c, hipMemsetAsync(c->bad_flag.p, 0, sizeof(int), c->stream));
   double2* C[2] = {c->C64[0].as<double2>(), c->C64[1].as<double2>()};
   DP_HIP(c, launch_clover_pack(c->g, c->scratch_aos.as<double2>(), C, c->bad_flag.as<int>(), c->stream));
@@ -813,19 +846,26 @@ int apply_core(dp_ctx* c, const double2* in, double2* out, int n, int flags, con
       ratio_tables(g.T, c->bc_t, a, all.data() + (size_t)4 * g.T * k);
       m4[k] = 4.0 + me[k]->M;
     }
-    DP_TRY(h2d(c, w.ratio.p, all.data(), sizeof(double) * all.size()));
-    DP_TRY(h2d(c, w.m4.p, m4.data(), sizeof(double) * n));
-    DP_TRY(h2d(c, w.slot_scale.p, one.data(), sizeof(double) * n));
+    // the copies are queued together and waited for once (the sources live
+    // until then)
+    const auto up = [&](void* dst, const void* src, size_t bytes) {
+      return hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, c->stream);
+    };
+    DP_HIP(c, up(w.ratio.p, all.data(), sizeof(double) * all.size()));
+    DP_HIP(c, up(w.m4.p, m4.data(), sizeof(double) * n));
+    DP_HIP(c, up(w.slot_scale.p, one.data(), sizeof(double) * n));
+    std::vector<const void*> v[3];
     for (int q = 0; q < 3; ++q) {
-      std::vector<const void*> v(n);
-      for (int k = 0; k < n; ++k) v[k] = q == 0 ? me[k]->a64.p : q == 1 ? me[k]->a32.p : me[k]->a16.p;
-      DP_TRY(h2d(c, w.ainv_ptr[q].p, v.data(), sizeof(void*) * n));
-      std::copy(v.begin(), v.end(), w.h_ainv[q].begin());
+      v[q].resize(n);
+      for (int k = 0; k < n; ++k) v[q][k] = q == 0 ? me[k]->a64.p : q == 1 ? me[k]->a32.p : me[k]->a16.p;
+      DP_HIP(c, up(w.ainv_ptr[q].p, v[q].data(), sizeof(void*) * n));
+      std::copy(v[q].begin(), v[q].end(), w.h_ainv[q].begin());
     }
     std::vector<const float*> s16(n);
     for (int k = 0; k < n; ++k) s16[k] = me[k]->s16.as<float>();
-    DP_TRY(h2d(c, w.ainv_scale_ptr.p, s16.data(), sizeof(float*) * n));
+    DP_HIP(c, up(w.ainv_scale_ptr.p, s16.data(), sizeof(float*) * n));
     std::copy(s16.begin(), s16.end(), w.h_ainv_scale.begin());
+    DP_HIP(c, hipStreamSynchronize(c->stream));
     c->apply_key = key;
   }
   return apply_run(c, w, in, out, n, flags);
@@ -1061,7 +1101,7 @@ int dp_apply(dp_ctx* c, const double* in, double* out, int flags) {
   DP_TRY(check_state(c));
   const Geom& g = c->g;
   const size_t bytes = (size_t)2 * g.Vh * 12 * sizeof(double2);
-  DP_HIP(c, c->scratch_aos.reserve(2 * bytes));
+  DP_HIP(c, reserve(c, c->scratch_aos, 2 * bytes));
   double2* din = c->scratch_aos.as<double2>();
   double2* dout = din + (size_t)2 * g.Vh * 12;
   DP_HIP(c, hipMemcpyAsync(din, in, bytes, hipMemcpyHostToDevice, c->stream));

@@ -962,23 +962,23 @@ size_t gcr_rn(int nkv) { return (size_t)2 * nkv * nkv + 4 * nkv; }
 int sap_alloc(dp_ctx* c, SapState& s, int nkv, int prec) {
   const Geom& g = c->g;
   Field* f64[] = {&s.eta, &s.x, &s.r, &s.t};
-  for (Field* f : f64) DP_HIP(c, f->alloc(g, F64, 2));
+  for (Field* f : f64) DP_HIP(c, alloc(c, *f, F64, 2));
   if ((int)s.z.size() < nkv) {
     s.z = std::vector<Field>(nkv);
     s.w = std::vector<Field>(nkv);
   }
   for (int k = 0; k < nkv; ++k) {
-    DP_HIP(c, s.z[k].alloc(g, F64, 2));
-    DP_HIP(c, s.w[k].alloc(g, F64, 2));
+    DP_HIP(c, alloc(c, s.z[k], F64, 2));
+    DP_HIP(c, alloc(c, s.w[k], F64, 2));
   }
   Field* fq[] = {&s.q_r, &s.q_psi, &s.q_rho, &s.q_a};
-  for (Field* f : fq) DP_HIP(c, f->alloc(g, prec, 2));
-  DP_HIP(c, s.ratio.reserve(sizeof(double) * 4 * g.T));
-  DP_HIP(c, s.m4.reserve(sizeof(double)));
-  DP_HIP(c, s.alpha.reserve(sizeof(double) * g.T));
-  DP_HIP(c, s.partials.reserve(sizeof(double) * 2 * kDotBlocks));
+  for (Field* f : fq) DP_HIP(c, alloc(c, *f, prec, 2));
+  DP_HIP(c, reserve(c, s.ratio, sizeof(double) * 4 * g.T));
+  DP_HIP(c, reserve(c, s.m4, sizeof(double)));
+  DP_HIP(c, reserve(c, s.alpha, sizeof(double) * g.T));
+  DP_HIP(c, reserve(c, s.partials, sizeof(double) * 2 * kDotBlocks));
   s.h_gcr.resize(gcr_len(nkv));
-  DP_HIP(c, s.gcr.reserve(sizeof(double) * s.h_gcr.size()));
+  DP_HIP(c, reserve(c, s.gcr, sizeof(double) * s.h_gcr.size()));
   s.h_part.resize(2 * kDotBlocks);
   s.g = g;
   s.nkv = nkv;
@@ -1109,11 +1109,11 @@ bool sap_fused_enabled(int prec, const Blocking& b) {
 // block-layout buffers and the links and clover gathered into them
 int sap_fused_setup(dp_ctx* c, SapState& s, const Blocking& b) {
   const long V = 2L * c->g.Vh;
-  DP_HIP(c, s.ubl.reserve(sizeof(float2) * 36 * V));
-  DP_HIP(c, s.cbl.reserve(sizeof(float4) * 18 * V));
-  DP_HIP(c, s.rbl.reserve(sizeof(float4) * 6 * V));
-  DP_HIP(c, s.pbl.reserve(sizeof(float4) * 6 * V));
-  if (b.vol > kSapThreads) DP_HIP(c, s.abl.reserve(sizeof(float4) * 6 * V));
+  DP_HIP(c, reserve(c, s.ubl, sizeof(float2) * 36 * V));
+  DP_HIP(c, reserve(c, s.cbl, sizeof(float4) * 18 * V));
+  DP_HIP(c, reserve(c, s.rbl, sizeof(float4) * 6 * V));
+  DP_HIP(c, reserve(c, s.pbl, sizeof(float4) * 6 * V));
+  if (b.vol > kSapThreads) DP_HIP(c, reserve(c, s.abl, sizeof(float4) * 6 * V));
   hipLaunchKernelGGL(sap_gather_kernel, site_grid(c->g), dim3(kBlock), 0, c->stream, c->g, b,
                      c->U[F32][0].as<float2>(), c->U[F32][1].as<float2>(), c->C32[0].as<float4>(),
                      c->C32[1].as<float4>(), s.ubl.as<float2>(), s.cbl.as<float4>());
@@ -1238,7 +1238,7 @@ extern "C" int dp_sap_precondition(dp_ctx* c, const double* r, const dp_sap_para
   DP_TRY(sap_prepare(c, p, 1, &b));
   SapState& s = *c->sap;
   const size_t bytes = (size_t)2 * g.Vh * 12 * sizeof(double2);
-  DP_HIP(c, c->scratch_aos.reserve(bytes));
+  DP_HIP(c, reserve(c, c->scratch_aos, bytes));
   DP_HIP(c, hipMemcpyAsync(c->scratch_aos.p, r, bytes, hipMemcpyHostToDevice, c->stream));
   DP_HIP(c, launch_spinor_import(g, c->scratch_aos.as<double2>(), 1, 0, s.r.ref(0), s.r.ref(1), nullptr, nullptr,
                                  c->stream));
@@ -1348,7 +1348,7 @@ int sap_solve(dp_ctx* c, const Blocking& b, const double2* eta_dev, const dp_sap
     if (S_host) DP_HIP(c, hipMemcpyAsync(S_host, S_dev, bytes, hipMemcpyDeviceToHost, c->stream));
   }
   if (cpp) {
-    DP_HIP(c, s.cpp.reserve(sizeof(double) * g.T));
+    DP_HIP(c, reserve(c, s.cpp, sizeof(double) * g.T));
     DP_HIP(c, launch_cpp(g, s.x.ref(0), s.x.ref(1), 1, s.alpha.as<double>(), space_profile(c), nullptr, nullptr,
                          s.cpp.as<double>(), c->stream));
     DP_HIP(c, hipMemcpyAsync(cpp, s.cpp.p, sizeof(double) * g.T, hipMemcpyDeviceToHost, c->stream));
@@ -1392,7 +1392,7 @@ extern "C" int dp_solve_sap(dp_ctx* c, const double* eta, const dp_sap_params* p
   // the source through the context's staging buffer, which takes the
   // solution afterwards
   const size_t bytes = (size_t)2 * c->g.Vh * 12 * sizeof(double2);
-  DP_HIP(c, c->scratch_aos.reserve(bytes));
+  DP_HIP(c, reserve(c, c->scratch_aos, bytes));
   DP_HIP(c, hipMemcpyAsync(c->scratch_aos.p, eta, bytes, hipMemcpyHostToDevice, c->stream));
   double2* st = c->scratch_aos.as<double2>();
   return sap_solve(c, b, st, p, S ? st : nullptr, S, cpp, info, t0);

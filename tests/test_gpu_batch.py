@@ -172,3 +172,34 @@ def test_batch_mass_change_after_shared_inverse():
                     S1, _, _ = solo(L2, eta[c], q["M"], alpha, q["x0"], r, "f32")
                     assert np.array_equal(S1, S_b[c]), (k, c)
             log(f"  request {k}: iters {[res['info']['iters'] for res in got[k]]}")
+
+
+def test_new_configurations_on_one_context():
+    """Links, clover and masses replaced on one context (more masses than the
+    context keeps buffers for): every Schur application equals a fresh
+    context's bitwise, so nothing of an earlier configuration's inverses is
+    read again."""
+    import torch
+    dims = (4, 4, 6, 4)
+    log("test_new_configurations_on_one_context")
+    alpha = synth.alpha_exp(dims[0], 0.2)
+    psi = torch.from_numpy(synth.random_spinor(dims, 17, nrhs=2).reshape(2, -1)).cuda()
+    out, ref = torch.empty_like(psi), torch.empty_like(psi)
+    torch.cuda.synchronize()
+    masses = [0.05, 0.1, 0.2, 0.3, 0.4, 0.5]
+    with lattice(dims) as L:
+        L.set_alpha(alpha)
+        for seed, csw in ((1, 1.6), (2, 1.2), (3, 0.0)):
+            U = synth.gauge_su3(dims, 0.4, seed)
+            L.set_gauge(U)
+            L.set_clover(csw)
+            for M in masses[: 7 - 2 * seed]:
+                L.set_mass(M)
+                L.apply_dev(psi, out, precond=True, schur=True, precision="f16" if M > 0.25 else "f32")
+                with lattice(dims) as F:
+                    F.set_gauge(U)
+                    F.set_clover(csw)
+                    F.set_mass(M)
+                    F.set_alpha(alpha)
+                    F.apply_dev(psi, ref, precond=True, schur=True, precision="f16" if M > 0.25 else "f32")
+                assert torch.equal(out, ref), (seed, M)
