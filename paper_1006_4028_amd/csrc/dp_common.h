@@ -123,6 +123,16 @@ __host__ __device__ constexpr int red_values(int red) {
   return red == RED_DOT_EXT ? 2 : red == RED_TS ? 3 : red == RED_TS4 ? 7 : red == RED_NORM ? 1 : 0;
 }
 
+// Place of value k of partial `part` of n.  Few partials lie with their values
+// side by side, one line each; many with a value's partials together, else the
+// fold of one value would read eight times its bytes through one CU.  A fold,
+// us, side by side / together: 64 partials 4.1 / 4.6, 1024 4.4 / 4.9, 5184 (mean
+// of two and seven values) 11.8 / 8.4, 16384 (one value) 14.1 / 9.2.
+constexpr int kSplitPartials = 2048;
+__host__ __device__ inline long partial_at(int n, int part, int k) {
+  return n > kSplitPartials ? (long)k * n + part : (long)part * kRedMax + k;
+}
+
 enum Fin {
   FIN_NONE = 0,
   FIN_BICG_ALPHA = 1,  // sums <rh, v>            -> alpha = rho / <rh, v>
@@ -142,7 +152,7 @@ struct ReduceRef {
   int red = RED_NONE;
   int fin = FIN_NONE;
   SpinorRef w;               // RED_DOT_EXT partner
-  double* partials = nullptr;   // [nslots][nblocks][kRedMax]
+  double* partials = nullptr;   // [nslots][kRedMax * nblocks], at partial_at within a slot
   SlotScalars* sc = nullptr;    // [nslots]
   double* out_sums = nullptr;   // FIN_STORE: [nslots][4]
   int* inner_mask = nullptr;    // [nslots] cleared when a slot leaves the inner solve

@@ -631,13 +631,12 @@ __device__ inline void end_of_iteration(const ReduceRef& red, int slot, SlotScal
   }
 }
 
-// Solver finalisers: turn the folded sums of one slot into its scalars.
-__device__ inline void run_finaliser(const ReduceRef& red, int slot, const double (&s)[kRedMax]) {
+// Solver finalisers: turn the folded sums of one slot into its scalars c.
+__device__ inline void run_finaliser(const ReduceRef& red, int slot, const double (&s)[kRedMax], SlotScalars& c) {
   if (red.fin == FIN_STORE) {
     for (int k = 0; k < 4; ++k) red.out_sums[slot * 4 + k] = s[k];
     return;
   }
-  SlotScalars& c = red.sc[slot];
   switch (red.fin) {
     case FIN_BICG_ALPHA: {
       if (s[0] == 0.0 && s[1] == 0.0) {
@@ -763,12 +762,12 @@ __device__ inline void block_reduce_store(const ReduceRef& red, int nv, double (
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    double* part = red.partials + ((long)slot * nblocks + block) * kRedMax;
+    double* part = red.partials + (long)slot * kRedMax * nblocks;
     const int nw = blockDim.x >> 6;  // blocks of 64 or kBlock threads
     for (int k = 0; k < nv; ++k) {
       double t = 0.0;
       for (int w = 0; w < nw; ++w) t += lds[k][w];
-      part[k] = t;
+      part[partial_at(nblocks, block, k)] = t;
     }
   }
   __syncthreads();

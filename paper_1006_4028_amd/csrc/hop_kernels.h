@@ -633,13 +633,13 @@ __device__ __forceinline__ void slot_work(const HopArgs& a, int slot, const Site
   }
   if constexpr (RED != RED_NONE) {
     constexpr int nv = red_values(RED);
-    double* pt = a.red.partials + ((long)slot * nparts + part) * kRedMax;
+    double* pt = a.red.partials + (long)slot * kRedMax * nparts;
     const int v = wave_row_value(lane >> 4);
     const double w = wave_sum4(red[0], red[1], red[2], red[3]);
-    if ((lane & 15) == 0 && v < nv) pt[v] = w;
+    if ((lane & 15) == 0 && v < nv) pt[partial_at(nparts, part, v)] = w;
     if constexpr (nv > 4) {
       const double w2 = wave_sum4(red[4], red[5], red[6], red[7]);
-      if ((lane & 15) == 0 && 4 + v < nv) pt[4 + v] = w2;
+      if ((lane & 15) == 0 && 4 + v < nv) pt[partial_at(nparts, part, 4 + v)] = w2;
     }
   }
 }
@@ -663,8 +663,19 @@ constexpr int shared_pf(int p) { return p == F32 ? 3 : 2; }
 constexpr int kSharedThreads = 256;
 constexpr int kSharedMinWaves = 2;
 
-// One slot: one wave per (chunk, timeslice), the slots of a chunk in
-// neighbouring blocks of the same XCD.
+// Up to so many waves, one per (chunk, timeslice, slot), several slots run as
+// one wave each too: a shared-tile workgroup would leave CUs without work and
+// take its slots one after the other.  Even / odd sites, us, one wave per slot
+// against shared tile: 768 waves (8^3x16, 12 slots) FP64 25.6 / 25.0 against
+// 30.2 / 25.2, FP32 14.1 / 13.7 against 18.8 / 19.4, FP16 9.3 / 9.6 against
+// 17.0 / 17.2; 1344 waves (12^3x24, 4 slots) FP64 28.8 / 27.8 against 26.5 / 23.6,
+// FP32 15.4 / 15.0 against 15.7 / 15.3; 2880 (36x18x20x14, 2 slots) FP32 28.4 / 27.3
+// against 34.3 / 30.0; 4032 (12^3x24, 12 slots) FP32 36.6 / 34.5 against 30.6 /
+// 31.2, FP16 21.2 / 20.6 against 26.5 / 26.0; 4096 (16^3x32, 4 slots) FP16 equal.
+constexpr int slab_max_waves(int p) { return p == F64 ? 1024 : p == F32 ? 3072 : 4096; }
+
+// One wave per (chunk, timeslice, slot), the slots of a chunk in neighbouring
+// blocks of the same XCD.
 template <int P, int EPI, int RED, bool DAG>
 __global__ void __launch_bounds__(64, slab_min_waves(P)) hop_kernel_slab(HopArgs a, SlabMap m) {
   const int j = blockIdx.x >> 3, jj = j / a.nslots, slot = j - jj * a.nslots;
@@ -775,7 +786,7 @@ hipError_t launch_one(const HopArgs& a, hipStream_t st, int* nparts_out) {
   m.tmap = tmap_knob == 0 || tmap_knob == 1 ? tmap_knob : (P != F64 && (a.nslots == 1 || P == F16) ? 1 : 0);
   const int nblocks = m.tmap ? 8 * m.tlen * m.nch : 8 * a.g.T * m.maxc;
   *nparts_out = a.g.T * m.nch;
-  if (a.nslots >= 2) {
+  if (a.nslots >= 2 && (long)a.g.T * m.nch * a.nslots > slab_max_waves(P)) {
     // waves per workgroup: the fewest rounds over the slots with at most four waves
     const int maxw = kSharedThreads / 64, rounds = (a.nslots + maxw - 1) / maxw;
     const dim3 grid(nblocks), block(64 * ((a.nslots + rounds - 1) / rounds));
