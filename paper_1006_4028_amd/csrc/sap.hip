@@ -172,26 +172,20 @@ __global__ void __launch_bounds__(kBlock) vec_convert_kernel(Geom g, SpinorRef x
   SpinorIO<PO>::store(y, p, i, g.Vp, v);
 }
 
-// op 0: y += a x (a complex);  op 1: y = x - y;  op 2: y = 0;  op 3: y = x
-// (2 and 3 do not read y, so that whatever a failed solve left in it is
-// overwritten, not carried: 0 * NaN is NaN)
-__global__ void __launch_bounds__(kBlock) vec_update_kernel(Geom g, int op, double ar, double ai, SpinorRef x,
-                                                            SpinorRef y) {
+// y = x, or y = 0 without x (y is not read, so that whatever a failed solve
+// left in it is overwritten, not carried: 0 * NaN is NaN)
+__global__ void __launch_bounds__(kBlock) vec_set_kernel(Geom g, SpinorRef x, SpinorRef y) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   const int p = blockIdx.y;
   if (i >= g.Vh) return;
-  cx<double> vx[12], vy[12];
-  if (op <= 1) SpinorIO<F64>::load(y, p, i, g.Vp, vy);
-  if (op != 2) SpinorIO<F64>::load(x, p, i, g.Vp, vx);
-  const cx<double> a{ar, ai};
+  cx<double> v[12];
+  if (x.data) {
+    SpinorIO<F64>::load(x, p, i, g.Vp, v);
+  } else {
 #pragma unroll
-  for (int c = 0; c < 12; ++c) {
-    if (op == 0) vy[c] = vy[c] + cmul(a, vx[c]);
-    else if (op == 1) vy[c] = vx[c] - vy[c];
-    else if (op == 2) vy[c] = cx<double>{0.0, 0.0};
-    else vy[c] = vx[c];
+    for (int c = 0; c < 12; ++c) v[c] = cx<double>{0.0, 0.0};
   }
-  SpinorIO<F64>::store(y, p, i, g.Vp, vy);
+  SpinorIO<F64>::store(y, p, i, g.Vp, v);
 }
 
 // block partials of <x, y> (complex) over both parities: partials[blockIdx][2]
@@ -264,35 +258,61 @@ __device__ __forceinline__ BLoc bl_locate(const Blocking& b, int x0, int x1, int
   return {colour * b.nhalf + k, s};
 }
 
+// The site of position n of the blocks in lexicographic order: its place in
+// the block layout (blk, s) and in the parity fields (p, i).  Neighbouring
+// threads are neighbouring sites of a block, so that the block layout is
+// written in whole lines, and neighbouring workgroups of an XCD (xcd_tile)
+// neighbouring blocks, which share the lines of the parity fields (a thread
+// per parity site wrote 16 scattered bytes a line: 251 us for one vector at
+// 64x32^3, 1296 us for the links and blocks).
+struct BSite {
+  int blk, s, p, i;
+};
+__device__ __forceinline__ BSite bl_site(const Geom& g, const Blocking& b, long n) {
+  int k = (int)(n / b.vol), s = (int)(n - (long)k * b.vol);
+  BSite r;
+  r.s = s;
+  const int c3 = k % b.nb[3];
+  k /= b.nb[3];
+  const int c2 = k % b.nb[2];
+  k /= b.nb[2];
+  const int c1 = k % b.nb[1], c0 = k / b.nb[1];
+  r.blk = ((c0 + c1 + c2 + c3) & 1) * b.nhalf + ((c0 * b.nb[1] + c1) * b.nb[2] + c2) * (b.nb[3] / 2) + c3 / 2;
+  const int x3 = c3 * b.bs[3] + s % b.bs[3];
+  s /= b.bs[3];
+  const int x2 = c2 * b.bs[2] + s % b.bs[2];
+  s /= b.bs[2];
+  const int x1 = c1 * b.bs[1] + s % b.bs[1], x0 = c0 * b.bs[0] + s / b.bs[1];
+  r.p = (x0 + x1 + x2 + x3) & 1;
+  r.i = eo_index(g, x0, x1, x2, x3);
+  return r;
+}
+
 // FP32 links and clover of both parities -> block layout
 __global__ void __launch_bounds__(kBlock) sap_gather_kernel(Geom g, Blocking b, const float2* __restrict__ U0,
                                                             const float2* __restrict__ U1,
                                                             const float4* __restrict__ C0,
                                                             const float4* __restrict__ C1, float2* __restrict__ ubl,
                                                             float4* __restrict__ cbl) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int p = blockIdx.y;
-  if (i >= g.Vh) return;
-  int x0, x1, x2, x3;
-  eo_coords(g, p, i, x0, x1, x2, x3);
-  const BLoc q = bl_locate(b, x0, x1, x2, x3);
-  const float2* U = p ? U1 : U0;
-  const float4* C = p ? C1 : C0;
-  for (int k = 0; k < 36; ++k) ubl[((long)q.blk * 36 + k) * b.vol + q.s] = U[(long)k * g.Vp + i];
-  for (int k = 0; k < 18; ++k) cbl[((long)q.blk * 18 + k) * b.vol + q.s] = C[(long)k * g.Vp + i];
+  const long n = (long)xcd_tile(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
+  if (n >= 2L * g.Vh) return;
+  const BSite q = bl_site(g, b, n);
+  const float2* U = q.p ? U1 : U0;
+  const float4* C = q.p ? C1 : C0;
+#pragma unroll 9
+  for (int k = 0; k < 36; ++k) ubl[((long)q.blk * 36 + k) * b.vol + q.s] = U[(long)k * g.Vp + q.i];
+#pragma unroll 9
+  for (int k = 0; k < 18; ++k) cbl[((long)q.blk * 18 + k) * b.vol + q.s] = C[(long)k * g.Vp + q.i];
 }
 
 // FP64 parity fields -> FP32 block layout
 __global__ void __launch_bounds__(kBlock) sap_to_block_kernel(Geom g, Blocking b, SpinorRef x,
                                                               float4* __restrict__ out) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int p = blockIdx.y;
-  if (i >= g.Vh) return;
-  int x0, x1, x2, x3;
-  eo_coords(g, p, i, x0, x1, x2, x3);
-  const BLoc q = bl_locate(b, x0, x1, x2, x3);
+  const long n = (long)xcd_tile(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
+  if (n >= 2L * g.Vh) return;
+  const BSite q = bl_site(g, b, n);
   cx<double> v[12];
-  SpinorIO<F64>::load(x, p, i, g.Vp, v);
+  SpinorIO<F64>::load(x, q.p, q.i, g.Vp, v);
 #pragma unroll
   for (int k = 0; k < 6; ++k)
     out[((long)q.blk * 6 + k) * b.vol + q.s] =
@@ -832,100 +852,145 @@ __global__ void __launch_bounds__(kSapBigThreads, 2) sap_block_big_kernel(SapPas
 
 constexpr int kDotBlocks = 1024;
 
-// The sum of the block partials of vec_dot_kernel in block order (the order
-// the host used), on the device: out = <x, y> (mode 0), out = (|x|, 0)
-// (mode 1), or <x, y> unless guard[0] (a norm) is zero or not finite, then 0
-// (mode 2).
-__global__ void __launch_bounds__(64) dot_finish_kernel(const double* __restrict__ partials, int mode,
-                                                        const double* __restrict__ guard, double* __restrict__ out) {
-  if (threadIdx.x != 0) return;
-  double re = 0.0, im = 0.0;
-  for (int k = 0; k < kDotBlocks; ++k) {
-    re += partials[2 * k];
-    im += partials[2 * k + 1];
-  }
-  if (mode == 1) {
-    re = sqrt(re);
-    im = 0.0;
-  } else if (mode == 2 && !(guard[0] > 0.0 && isfinite(guard[0]))) {
-    re = im = 0.0;
-  }
-  out[0] = re;
-  out[1] = im;
-}
+// ------------------------------------------------------------ GCR vectors
+//
+// The Gram-Schmidt step of GCR works on whole FP64 vectors, so what it costs is
+// how often they pass through the memory.  The coefficients against up to
+// kGcrGroup earlier vectors are formed in one pass and subtracted in a second
+// one, which also takes the new vector's norm and its product with the
+// residual (classical Gram-Schmidt within a group, modified between groups):
+// 2 k + 7 vector passes for the k-th vector against 4 k + 7 one coefficient at
+// a time.  The earlier vectors stay unnormalised, their squared norms enter
+// the coefficients.  A vector is 24 component rows (2 parities) of Vh entries,
+// Vp apart; blockIdx.y is the row, so neighbouring threads and loop steps read
+// neighbouring entries of every vector.
 
-// One Gram-Schmidt step of GCR in one pass: the update of y with its
-// coefficient on the device (op 0: y += sgn coef x, coef complex; op 1:
-// y = y / coef[0], a norm, y left alone when it is zero or not finite), then
-// the block partials of a dot product involving the updated y, as
-// vec_dot_kernel forms them (same grid, order and arithmetic): dmode 0:
-// <z, y>, 1: <y, z>, 2: <y, y>.
-__global__ void __launch_bounds__(kBlock) vec_update_dot_kernel(Geom g, int op, const double* __restrict__ coef,
-                                                                double sgn, SpinorRef x, SpinorRef y, int dmode,
-                                                                SpinorRef z, double* __restrict__ partials) {
-  __shared__ double lds[2][kBlock / 64];
-  const double c0 = coef[0], c1 = coef[1];
-  const bool skip = op == 1 && !(c0 > 0.0 && isfinite(c0));
-  double re = 0.0, im = 0.0;
-  const long n = 2L * g.Vh;
-  for (long s = (long)blockIdx.x * blockDim.x + threadIdx.x; s < n; s += (long)gridDim.x * blockDim.x) {
-    const int p = (int)(s / g.Vh), i = (int)(s - (long)p * g.Vh);
-    cx<double> vx[12], vy[12];
-    SpinorIO<F64>::load(y, p, i, g.Vp, vy);
-    if (!skip) {
-      if (op == 0) {
-        SpinorIO<F64>::load(x, p, i, g.Vp, vx);
-        const cx<double> a{sgn * c0, sgn * c1};
+constexpr int kGcrGroup = 16;
+constexpr int kGcrBlocksX = 85;  // at most 24 * 85 = 2040 blocks
+
+struct VecList {
+  const double2* v[kGcrGroup];
+};
+
+// block sums of n values -> partials[value][block]
+template <int N>
+__device__ __forceinline__ void gcr_store_sums(const double (&v)[N], double* partials) {
+  __shared__ double lds[kBlock / 64][(N + 3) / 4 * 4];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
-        for (int c = 0; c < 12; ++c) vy[c] = vy[c] + cmul(a, vx[c]);
-      } else {
-        const double ar = 1.0 / c0;
-#pragma unroll
-        for (int c = 0; c < 12; ++c) vy[c] = ar * vy[c];
-      }
-      SpinorIO<F64>::store(y, p, i, g.Vp, vy);
-    }
-    if (dmode == 2) {
-#pragma unroll
-      for (int c = 0; c < 12; ++c) {
-        re += vy[c].x * vy[c].x + vy[c].y * vy[c].y;
-        im += vy[c].x * vy[c].y - vy[c].y * vy[c].x;
-      }
-    } else {
-      SpinorIO<F64>::load(z, p, i, g.Vp, vx);
-      if (dmode == 0) {
-#pragma unroll
-        for (int c = 0; c < 12; ++c) {
-          re += vx[c].x * vy[c].x + vx[c].y * vy[c].y;
-          im += vx[c].x * vy[c].y - vx[c].y * vy[c].x;
-        }
-      } else {
-#pragma unroll
-        for (int c = 0; c < 12; ++c) {
-          re += vy[c].x * vx[c].x + vy[c].y * vx[c].y;
-          im += vy[c].x * vx[c].y - vy[c].y * vx[c].x;
-        }
-      }
-    }
-  }
-  re = wave_sum(re);
-  im = wave_sum(im);
-  if ((threadIdx.x & 63) == 0) {
-    lds[0][threadIdx.x >> 6] = re;
-    lds[1][threadIdx.x >> 6] = im;
+  for (int k = 0; k < N; k += 4) {
+    const double w = wave_sum4(v[k], k + 1 < N ? v[k + 1] : 0.0, k + 2 < N ? v[k + 2] : 0.0, k + 3 < N ? v[k + 3] : 0.0);
+    if ((lane & 15) == 0) lds[wv][k + wave_row_value(lane >> 4)] = w;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double a = 0.0, b = 0.0;
-    for (int q = 0; q < kBlock / 64; ++q) {
-      a += lds[0][q];
-      b += lds[1][q];
-    }
-    partials[2 * blockIdx.x] = a;
-    partials[2 * blockIdx.x + 1] = b;
+  const int nb = gridDim.x * gridDim.y, blk = blockIdx.y * gridDim.x + blockIdx.x;
+  if (threadIdx.x < N) {
+    double t = 0.0;
+    for (int w = 0; w < kBlock / 64; ++w) t += lds[w][threadIdx.x];
+    partials[(long)threadIdx.x * nb + blk] = t;
   }
 }
 
+// <x_j, y> for N vectors: values 2 j, 2 j + 1
+template <int N>
+__global__ void __launch_bounds__(kBlock) gcr_dots_kernel(int Vh, int Vp, VecList x, const double2* __restrict__ y,
+                                                          double* __restrict__ partials) {
+  double v[2 * N] = {};
+  const long row = (long)blockIdx.y * Vp;
+  for (int i = blockIdx.x * kBlock + threadIdx.x; i < Vh; i += gridDim.x * kBlock) {
+    const double2 b = y[row + i];
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const double2 a = x.v[j][row + i];
+      v[2 * j] = fmar(a.y, b.y, fmar(a.x, b.x, v[2 * j]));
+      v[2 * j + 1] = fmar(-a.y, b.x, fmar(a.x, b.y, v[2 * j + 1]));
+    }
+  }
+  gcr_store_sums(v, partials);
+}
+
+enum GcrPass {
+  GCR_UPDATE = 0,     // y += sum_j coef_j x_j
+  GCR_ORTHO = 1,      // ... then |y|^2 and <y, z>
+  GCR_RESIDUAL = 2,   // ... then |y|^2
+  GCR_SUBTRACT = 3,   // y = z - y, then |y|^2
+};
+
+// N vectors x_j with complex coefficients on the device
+template <int N, int MODE>
+__global__ void __launch_bounds__(kBlock) gcr_update_kernel(int Vh, int Vp, VecList x, const double* __restrict__ coef,
+                                                            double2* __restrict__ y, const double2* __restrict__ z,
+                                                            double* __restrict__ partials) {
+  constexpr int NV = MODE == GCR_ORTHO ? 3 : 1;
+  double v[NV] = {};
+  double c[2 * N + 1];
+#pragma unroll
+  for (int k = 0; k < 2 * N; ++k) c[k] = coef[k];
+  const long row = (long)blockIdx.y * Vp;
+  for (int i = blockIdx.x * kBlock + threadIdx.x; i < Vh; i += gridDim.x * kBlock) {
+    double2 t = y[row + i], q;
+    if constexpr (MODE == GCR_ORTHO || MODE == GCR_SUBTRACT) q = z[row + i];
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const double2 a = x.v[j][row + i];
+      t.x = fmar(-c[2 * j + 1], a.y, fmar(c[2 * j], a.x, t.x));
+      t.y = fmar(c[2 * j + 1], a.x, fmar(c[2 * j], a.y, t.y));
+    }
+    if constexpr (MODE == GCR_SUBTRACT) t = make_double2(q.x - t.x, q.y - t.y);
+    if constexpr (N > 0 || MODE == GCR_SUBTRACT) y[row + i] = t;
+    if constexpr (MODE != GCR_UPDATE) v[0] = fmar(t.y, t.y, fmar(t.x, t.x, v[0]));
+    if constexpr (MODE == GCR_ORTHO) {
+      v[1] = fmar(t.y, q.y, fmar(t.x, q.x, v[1]));
+      v[2] = fmar(-t.y, q.x, fmar(t.x, q.y, v[2]));
+    }
+  }
+  if constexpr (MODE != GCR_UPDATE) gcr_store_sums(v, partials);
+}
+
+// Folds the block sums in a fixed order and forms the coefficients.
+//   mode 0 (block j): c = <w_j, w_k> / |w_j| for the host, coef_j = -<w_j, w_k> / |w_j|^2
+//   mode 1: b = |w_k|, gamma = <w_k, r> / b for the host, coef_0 = -<w_k, r> / b^2,
+//           both 0 unless b is finite and positive; b2 = b^2
+//   mode 2: out = the sum
+__global__ void __launch_bounds__(kBlock) gcr_finish_kernel(const double* __restrict__ partials, int nb, int mode,
+                                                            const double* __restrict__ b2, long out_stride,
+                                                            double* __restrict__ out, double* __restrict__ out2,
+                                                            double* __restrict__ coef, double* __restrict__ b2_out) {
+  __shared__ double lds[kBlock / 64][4];
+  const int j = blockIdx.x, nv = mode == 0 ? 2 : mode == 1 ? 3 : 1;
+  const double* p = partials + (long)(mode == 0 ? 2 * j : 0) * nb;
+  double v[3] = {};
+  for (int b = threadIdx.x; b < nb; b += kBlock)
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      if (k < nv) v[k] += p[(long)k * nb + b];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const double w = wave_sum4(v[0], v[1], v[2], 0.0);
+  if ((lane & 15) == 0) lds[wv][wave_row_value(lane >> 4)] = w;
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  double s[3] = {};
+  for (int q = 0; q < kBlock / 64; ++q)
+    for (int k = 0; k < 3; ++k) s[k] += lds[q][k];
+  if (mode == 0) {
+    const double n2 = b2[j], n = sqrt(n2);
+    out[j * out_stride] = s[0] / n;
+    out[j * out_stride + 1] = s[1] / n;
+    coef[2 * j] = -s[0] / n2;
+    coef[2 * j + 1] = -s[1] / n2;
+  } else if (mode == 1) {
+    const double b = sqrt(s[0]);
+    const bool ok = b > 0.0 && isfinite(b);
+    out[0] = b;
+    out2[0] = ok ? s[1] / b : 0.0;
+    out2[1] = ok ? s[2] / b : 0.0;
+    coef[0] = ok ? -s[1] / s[0] : 0.0;
+    coef[1] = ok ? -s[2] / s[0] : 0.0;
+    *b2_out = s[0];
+  } else {
+    out[0] = s[0];
+  }
+}
 
 }  // namespace
 
@@ -940,7 +1005,8 @@ struct SapState {
   Field q_r, q_psi, q_rho, q_a;  // block-solve precision
   DevBuf ratio, m4, partials, alpha, cpp;
   // GCR coefficients on the device: c_jk [nkv][nkv], gamma_k [nkv], b_k
-  // [nkv] (complex pairs), |r|^2; and their host copy
+  // [nkv] (complex pairs), |r|^2, and their host copy; then |w_k|^2 [nkv] and
+  // the coefficients of the next update [nkv]
   DevBuf gcr;
   std::vector<double> h_gcr;
   // fused block solves: links, clover, r and psi in block layout (FP32)
@@ -958,6 +1024,9 @@ size_t gcr_cc(int nkv, int j, int k) { return (size_t)2 * (j * nkv + k); }
 size_t gcr_gam(int nkv, int k) { return (size_t)2 * nkv * nkv + 2 * k; }
 size_t gcr_bn(int nkv, int k) { return (size_t)2 * nkv * nkv + 2 * nkv + 2 * k; }
 size_t gcr_rn(int nkv) { return (size_t)2 * nkv * nkv + 4 * nkv; }
+size_t gcr_b2(int nkv, int k) { return gcr_len(nkv) + k; }
+size_t gcr_coef(int nkv) { return gcr_len(nkv) + nkv; }
+size_t gcr_dev_len(int nkv) { return gcr_len(nkv) + 3 * nkv; }
 
 int sap_alloc(dp_ctx* c, SapState& s, int nkv, int prec) {
   const Geom& g = c->g;
@@ -976,9 +1045,9 @@ int sap_alloc(dp_ctx* c, SapState& s, int nkv, int prec) {
   DP_HIP(c, reserve(c, s.ratio, sizeof(double) * 4 * g.T));
   DP_HIP(c, reserve(c, s.m4, sizeof(double)));
   DP_HIP(c, reserve(c, s.alpha, sizeof(double) * g.T));
-  DP_HIP(c, reserve(c, s.partials, sizeof(double) * 2 * kDotBlocks));
+  DP_HIP(c, reserve(c, s.partials, sizeof(double) * std::max(2 * kDotBlocks, 2 * kGcrGroup * 24 * kGcrBlocksX)));
   s.h_gcr.resize(gcr_len(nkv));
-  DP_HIP(c, reserve(c, s.gcr, sizeof(double) * s.h_gcr.size()));
+  DP_HIP(c, reserve(c, s.gcr, sizeof(double) * gcr_dev_len(nkv)));
   s.h_part.resize(2 * kDotBlocks);
   s.g = g;
   s.nkv = nkv;
@@ -1016,10 +1085,10 @@ int apply_full(dp_ctx* c, SapState& s, int prec, const Field& in, const Field& o
 }
 
 dim3 site_grid(const Geom& g) { return dim3((g.Vh + kBlock - 1) / kBlock, 2); }
+dim3 block_grid(const Geom& g) { return dim3((unsigned)((2L * g.Vh + kBlock - 1) / kBlock)); }
 
-int vec_update(dp_ctx* c, int op, zc a, const Field& x, const Field& y) {
-  hipLaunchKernelGGL(vec_update_kernel, site_grid(c->g), dim3(kBlock), 0, c->stream, c->g, op, a.real(), a.imag(),
-                     x.ref(), y.ref());
+int vec_set(dp_ctx* c, const SpinorRef& x, const Field& y) {
+  hipLaunchKernelGGL(vec_set_kernel, site_grid(c->g), dim3(kBlock), 0, c->stream, c->g, x, y.ref());
   DP_HIP(c, hipGetLastError());
   return DP_OK;
 }
@@ -1041,28 +1110,80 @@ int vec_dot(dp_ctx* c, SapState& s, const Field& x, const Field& y, zc* out) {
   return DP_OK;
 }
 
-// out = the finished <x, y> on the device (dot_finish_kernel's mode)
-int vec_dot_dev(dp_ctx* c, SapState& s, const Field& x, const Field& y, int mode, const double* guard, double* out) {
-  hipLaunchKernelGGL(vec_dot_kernel, dim3(kDotBlocks), dim3(kBlock), 0, c->stream, c->g, x.ref(), y.ref(),
-                     s.partials.as<double>());
+dim3 gcr_grid(const Geom& g) { return dim3(std::min(kGcrBlocksX, (g.Vh + kBlock - 1) / kBlock), 24); }
+int gcr_blocks(const Geom& g) { return (int)gcr_grid(g).x * 24; }
+
+// <x_j, y> for the n vectors of the list
+template <int N = 1>
+hipError_t gcr_dots(dp_ctx* c, SapState& s, int n, const VecList& x, const Field& y) {
+  if constexpr (N > kGcrGroup) {
+    return hipErrorInvalidValue;
+  } else {
+    if (n != N) return gcr_dots<N + 1>(c, s, n, x, y);
+    hipLaunchKernelGGL((gcr_dots_kernel<N>), gcr_grid(c->g), dim3(kBlock), 0, c->stream, c->g.Vh, c->g.Vp, x,
+                       y.data.as<double2>(), s.partials.as<double>());
+    return hipGetLastError();
+  }
+}
+
+template <int MODE, int N>
+hipError_t gcr_pass(dp_ctx* c, SapState& s, const VecList& x, const double* coef, const Field& y, const Field* z) {
+  hipLaunchKernelGGL((gcr_update_kernel<N, MODE>), gcr_grid(c->g), dim3(kBlock), 0, c->stream, c->g.Vh, c->g.Vp, x, coef,
+                     y.data.as<double2>(), z ? z->data.as<double2>() : nullptr, s.partials.as<double>());
+  return hipGetLastError();
+}
+
+// a pass over n vectors, 0 <= n <= kGcrGroup
+template <int MODE, int N = 0>
+hipError_t gcr_update(dp_ctx* c, SapState& s, int n, const VecList& x, const double* coef, const Field& y,
+                      const Field* z) {
+  if constexpr (N > kGcrGroup) {
+    return hipErrorInvalidValue;
+  } else {
+    return n == N ? gcr_pass<MODE, N>(c, s, x, coef, y, z) : gcr_update<MODE, N + 1>(c, s, n, x, coef, y, z);
+  }
+}
+
+// the sum of the last pass on the host
+int gcr_sum(dp_ctx* c, SapState& s, double* out) {
+  double* rn = s.gcr.as<double>() + gcr_rn(s.nkv);
+  hipLaunchKernelGGL(gcr_finish_kernel, dim3(1), dim3(kBlock), 0, c->stream, s.partials.as<double>(), gcr_blocks(c->g),
+                     2, nullptr, 0L, rn, nullptr, nullptr, nullptr);
   DP_HIP(c, hipGetLastError());
-  hipLaunchKernelGGL(dot_finish_kernel, dim3(1), dim3(64), 0, c->stream, s.partials.as<double>(), mode, guard, out);
-  DP_HIP(c, hipGetLastError());
+  DP_HIP(c, hipMemcpyAsync(out, rn, sizeof(double), hipMemcpyDeviceToHost, c->stream));
+  DP_HIP(c, hipStreamSynchronize(c->stream));
   return DP_OK;
 }
 
-// y updated by vec_update_dot_kernel's op, then out = the dot product of its
-// dmode (finished in dot_finish_kernel's fmode)
-int vec_update_dot_dev(dp_ctx* c, SapState& s, int op, const double* coef, double sgn, const Field& x,
-                       const Field& y, int dmode, const Field& z, int fmode, const double* guard, double* out) {
-  hipLaunchKernelGGL(vec_update_dot_kernel, dim3(kDotBlocks), dim3(kBlock), 0, c->stream, c->g, op, coef, sgn,
-                     x.ref(), y.ref(), dmode, z.ref(), s.partials.as<double>());
+// w_k against the earlier w_j, then b_k, gamma_k and r -= gamma_k w_k: every
+// coefficient is formed and used on the device
+int gcr_orthogonalise(dp_ctx* c, SapState& s, int k) {
+  const int nkv = s.nkv, nb = gcr_blocks(c->g);
+  double* gd = s.gcr.as<double>();
+  double* part = s.partials.as<double>();
+  double* coef = gd + gcr_coef(nkv);
+  VecList x{};
+  int n = 0;
+  for (int j0 = 0; j0 < k; j0 += n) {
+    n = std::min(kGcrGroup, k - j0);
+    for (int j = 0; j < n; ++j) x.v[j] = s.w[j0 + j].data.as<double2>();
+    DP_HIP(c, gcr_dots(c, s, n, x, s.w[k]));
+    hipLaunchKernelGGL(gcr_finish_kernel, dim3(n), dim3(kBlock), 0, c->stream, part, nb, 0, gd + gcr_b2(nkv, j0),
+                       (long)2 * nkv, gd + gcr_cc(nkv, j0, k), nullptr, coef, nullptr);
+    DP_HIP(c, hipGetLastError());
+    if (j0 + n < k) DP_HIP(c, gcr_update<GCR_UPDATE>(c, s, n, x, coef, s.w[k], nullptr));
+  }
+  DP_HIP(c, gcr_update<GCR_ORTHO>(c, s, n, x, coef, s.w[k], &s.r));
+  hipLaunchKernelGGL(gcr_finish_kernel, dim3(1), dim3(kBlock), 0, c->stream, part, nb, 1, nullptr, 0L,
+                     gd + gcr_bn(nkv, k), gd + gcr_gam(nkv, k), coef, gd + gcr_b2(nkv, k));
   DP_HIP(c, hipGetLastError());
-  hipLaunchKernelGGL(dot_finish_kernel, dim3(1), dim3(64), 0, c->stream, s.partials.as<double>(), fmode, guard, out);
+  x.v[0] = s.w[k].data.as<double2>();
+  DP_HIP(c, (gcr_pass<GCR_RESIDUAL, 1>(c, s, x, coef, s.r, nullptr)));
+  hipLaunchKernelGGL(gcr_finish_kernel, dim3(1), dim3(kBlock), 0, c->stream, part, nb, 2, nullptr, 0L,
+                     gd + gcr_rn(nkv), nullptr, nullptr, nullptr);
   DP_HIP(c, hipGetLastError());
   return DP_OK;
 }
-
 
 template <int PI, int PO>
 int convert(dp_ctx* c, const Field& x, const Field& y) {
@@ -1114,7 +1235,7 @@ int sap_fused_setup(dp_ctx* c, SapState& s, const Blocking& b) {
   DP_HIP(c, reserve(c, s.rbl, sizeof(float4) * 6 * V));
   DP_HIP(c, reserve(c, s.pbl, sizeof(float4) * 6 * V));
   if (b.vol > kSapThreads) DP_HIP(c, reserve(c, s.abl, sizeof(float4) * 6 * V));
-  hipLaunchKernelGGL(sap_gather_kernel, site_grid(c->g), dim3(kBlock), 0, c->stream, c->g, b,
+  hipLaunchKernelGGL(sap_gather_kernel, block_grid(c->g), dim3(kBlock), 0, c->stream, c->g, b,
                      c->U[F32][0].as<float2>(), c->U[F32][1].as<float2>(), c->C32[0].as<float4>(),
                      c->C32[1].as<float4>(), s.ubl.as<float2>(), s.cbl.as<float4>());
   DP_HIP(c, hipGetLastError());
@@ -1160,7 +1281,7 @@ int sap_apply_fused(dp_ctx* c, SapState& s, const Blocking& b, int ncy, int nmr)
 int precondition(dp_ctx* c, SapState& s, const Blocking& b, int ncy, int nmr, const Field& r, const Field& z) {
   TraceRange tr("sap_precondition");
   if (s.fused) {
-    hipLaunchKernelGGL(sap_to_block_kernel, site_grid(c->g), dim3(kBlock), 0, c->stream, c->g, b, r.ref(),
+    hipLaunchKernelGGL(sap_to_block_kernel, block_grid(c->g), dim3(kBlock), 0, c->stream, c->g, b, r.ref(),
                        s.rbl.as<float4>());
     DP_HIP(c, hipGetLastError());
     DP_TRY(sap_apply_fused(c, s, b, ncy, nmr));
@@ -1268,8 +1389,8 @@ int sap_solve(dp_ctx* c, const Blocking& b, const double2* eta_dev, const dp_sap
   DP_TRY(vec_dot(c, s, s.eta, s.eta, &e2));
   const double target = p->r * std::sqrt(e2.real());
   // x = 0, r = eta'
-  DP_TRY(vec_update(c, 2, zc(0.0, 0.0), s.x, s.x));
-  DP_TRY(vec_update(c, 3, zc(0.0, 0.0), s.eta, s.r));
+  DP_TRY(vec_set(c, SpinorRef(), s.x));
+  DP_TRY(vec_set(c, s.eta.ref(), s.r));
   int iters = 0, status = DP_ERR_NOT_CONVERGED, outer = 0;
   double rn = std::sqrt(e2.real());
   if (!std::isfinite(rn)) status = DP_ERR_NONFINITE;
@@ -1284,26 +1405,8 @@ int sap_solve(dp_ctx* c, const Blocking& b, const double2* eta_dev, const dp_sap
       DP_TRY(precondition(c, s, b, p->ncy, p->nmr, s.r, s.z[k]));
       DP_TRY(apply_full(c, s, F64, s.z[k], s.w[k]));
       ++iters;
-      // modified Gram-Schmidt against the earlier w_j, normalisation,
-      // gamma_k = <w_k, r> and r -= gamma_k w_k, with every coefficient
-      // formed and used on the device (each update shares its pass with the
-      // next dot product); one copy to the host per iteration
+      DP_TRY(gcr_orthogonalise(c, s, k));
       double* gd = s.gcr.as<double>();
-      double* bk = gd + gcr_bn(nkv, k);
-      double* gk = gd + gcr_gam(nkv, k);
-      if (k == 0) {
-        DP_TRY(vec_dot_dev(c, s, s.w[k], s.w[k], 1, nullptr, bk));
-      } else {
-        DP_TRY(vec_dot_dev(c, s, s.w[0], s.w[k], 0, nullptr, gd + gcr_cc(nkv, 0, k)));
-        for (int j = 1; j < k; ++j)  // w_k -= c_{j-1,k} w_{j-1}, then c_jk = <w_j, w_k>
-          DP_TRY(vec_update_dot_dev(c, s, 0, gd + gcr_cc(nkv, j - 1, k), -1.0, s.w[j - 1], s.w[k], 0, s.w[j], 0,
-                                    nullptr, gd + gcr_cc(nkv, j, k)));
-        DP_TRY(vec_update_dot_dev(c, s, 0, gd + gcr_cc(nkv, k - 1, k), -1.0, s.w[k - 1], s.w[k], 2, s.w[k], 1,
-                                  nullptr, bk));
-      }
-      // w_k /= b_k, then gamma_k = <w_k, r>; r -= gamma_k w_k, then |r|^2
-      DP_TRY(vec_update_dot_dev(c, s, 1, bk, 1.0, s.w[k], s.w[k], 1, s.r, 2, bk, gk));
-      DP_TRY(vec_update_dot_dev(c, s, 0, gk, -1.0, s.w[k], s.r, 2, s.r, 0, nullptr, gd + gcr_rn(nkv)));
       DP_HIP(c, hipMemcpyAsync(s.h_gcr.data(), gd, sizeof(double) * gcr_len(nkv), hipMemcpyDeviceToHost, c->stream));
       DP_HIP(c, hipStreamSynchronize(c->stream));
       const double* hg = s.h_gcr.data();
@@ -1330,13 +1433,21 @@ int sap_solve(dp_ctx* c, const Blocking& b, const double2* eta_dev, const dp_sap
       for (int l = j + 1; l < k; ++l) v -= cc[(size_t)j * nkv + l] * al[l];
       al[j] = v / bn[j];
     }
-    for (int j = 0; j < k; ++j) DP_TRY(vec_update(c, 0, al[j], s.z[j], s.x));
+    // x += sum_j al_j z_j
+    double* coef = s.gcr.as<double>() + gcr_coef(nkv);
+    DP_TRY(h2d(c, coef, al.data(), sizeof(zc) * k));
+    for (int j0 = 0; j0 < k; j0 += kGcrGroup) {
+      const int n = std::min(kGcrGroup, k - j0);
+      VecList x{};
+      for (int j = 0; j < n; ++j) x.v[j] = s.z[j0 + j].data.as<double2>();
+      DP_HIP(c, gcr_update<GCR_UPDATE>(c, s, n, x, coef + 2 * j0, s.x, nullptr));
+    }
     // true residual r = eta' - D' x
     DP_TRY(apply_full(c, s, F64, s.x, s.r));
-    DP_TRY(vec_update(c, 1, zc(0.0, 0.0), s.eta, s.r));
-    zc r2;
-    DP_TRY(vec_dot(c, s, s.r, s.r, &r2));
-    rn = std::sqrt(r2.real());
+    DP_HIP(c, (gcr_pass<GCR_SUBTRACT, 0>(c, s, VecList{}, coef, s.r, &s.eta)));
+    double r2 = 0.0;
+    DP_TRY(gcr_sum(c, s, &r2));
+    rn = std::sqrt(r2);
     ++outer;
     if (!std::isfinite(rn)) status = DP_ERR_NONFINITE;
     else if (rn <= target) status = DP_OK;

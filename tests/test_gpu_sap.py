@@ -242,3 +242,28 @@ def test_sap_max_iter_returns_partial_solution():
         with pytest.raises(dp.DPError) as e:
             L.sap_precondition(eta, (3, 2, 4, 2))
         assert e.value.code == -1
+
+
+@pytest.mark.parametrize("nkv", [1, 2, 16, 17, 40])
+def test_sap_gcr_group_sizes(nkv):
+    """The Gram-Schmidt step takes up to 16 earlier vectors in a pass: restart
+    lengths at and past that, with a weak preconditioner (one cycle, one
+    minimal-residual step, FP64), so that the solves run through them.  The
+    iteration count is the oracle's (one coefficient at a time) up to the
+    rounding of the last step."""
+    dims, block, M, r = (8, 4, 8, 4), (2, 2, 2, 2), 0.05, 1e-10
+    log(f"test_sap_gcr_group_sizes nkv={nkv}")
+    U = synth.gauge_su3(dims, 0.4, 45)
+    C = oracle.clover(U, 1.6)
+    eta = synth.point_sources_12(dims, (0, 0, 0, 0))[5]
+    S_or, info_or = oracle.solve_sap(U, C, M, eta, block, ncy=1, nmr=1, nkv=nkv, r=r)
+    with lattice(dims) as L:
+        L.set_gauge(U)
+        L.set_clover(1.6)
+        L.set_mass(M)
+        S, cpp, info = L.solve_sap(eta, block, r=r, ncy=1, nmr=1, nkv=nkv, precision="f64")
+    log(f"  iterations GPU {info['iters']} oracle {info_or['iters']}, restarts {info['outer']}")
+    assert info["status"] == 0 and abs(info["iters"] - info_or["iters"]) <= 1
+    assert nkv < 17 or info["iters"] > 17
+    res = eta - oracle.apply(U, C, M, S)
+    assert np.linalg.norm(res) / np.linalg.norm(eta) <= 1.0001 * r
