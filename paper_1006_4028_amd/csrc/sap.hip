@@ -224,15 +224,16 @@ __global__ void __launch_bounds__(kBlock) vec_dot_kernel(Geom g, SpinorRef x, Sp
 
 // ------------------------------------------------------- fused block solves
 //
-// For blocks of at most kSapThreads sites the whole pass over one colour (the
-// block residual, then nmr minimal-residual steps) runs as one kernel: a
-// workgroup per block and a thread per site.  Each thread keeps its site's
-// four forward links and clover blocks in registers for the pass; the block
-// residual rho lives in LDS.  Of the hops inside a block, the forward one at x
-// reads rho(x + mu) from LDS and multiplies by the thread's own link; the
-// backward one at x needs U_mu(x - mu)^+ applied to rho(x - mu), which the
-// thread of x - mu forms with its own link and leaves in LDS for x.  Hops that
-// leave the block drop (Dirichlet block boundaries).
+// The whole pass over one colour (the block residual, then nmr
+// minimal-residual steps) runs as one kernel, a workgroup per block.  Hops that
+// leave the block drop in the minimal-residual steps (Dirichlet block
+// boundaries); the residual is r - D'_B psi, with the same block operator, minus
+// the hops from the neighbour blocks, which touch only the sites of the faces.
+// Three kernels, by what of a block fits on the chip:
+//  - sap_slice_kernel: at most kSapThreads sites and a whole number of time
+//    slices in a wave; links, clover and residual stay on the chip
+//  - sap_block_kernel: at most kSapThreads sites; links and residual
+//  - sap_block_big_kernel: at most kSapBigSites sites; the residual
 //
 // The fields of the pass are stored block by block ("block layout"): the
 // blocks of colour 0 in the order of their index k, then those of colour 1;
@@ -363,27 +364,28 @@ __device__ __forceinline__ void bl_proj(const cx<float> (&v)[12], cx<float> (&h)
   }
 }
 
-// acc += c * (the full spinor whose upper half is w, of projector (1 - sg gamma_mu))
+// acc += c * (the full spinor whose upper half is w, of projector (1 - sg
+// gamma_mu)), one fused multiply-add a component
 template <int MU, int SG>
 __device__ __forceinline__ void bl_recon(cx<float> (&acc)[12], const cx<float> (&w)[6], float c) {
-  constexpr float sg = (float)SG;
+  const float d = SG > 0 ? c : -c;
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    const cx<float> w0 = c * w[a], w1 = c * w[3 + a];
-    acc[a] = acc[a] + w0;
-    acc[3 + a] = acc[3 + a] + w1;
+    const cx<float> w0 = w[a], w1 = w[3 + a];
+    rfma(acc[a], c, w0);
+    rfma(acc[3 + a], c, w1);
     if constexpr (MU == 0) {
-      acc[6 + a] = acc[6 + a] + sg * w0;
-      acc[9 + a] = acc[9 + a] + sg * w1;
+      rfma(acc[6 + a], d, w0);
+      rfma(acc[9 + a], d, w1);
     } else if constexpr (MU == 1) {
-      acc[6 + a] = acc[6 + a] - sg * ti(w1);
-      acc[9 + a] = acc[9 + a] - sg * ti(w0);
+      rfma(acc[6 + a], -d, ti(w1));
+      rfma(acc[9 + a], -d, ti(w0));
     } else if constexpr (MU == 2) {
-      acc[6 + a] = acc[6 + a] - sg * w1;
-      acc[9 + a] = acc[9 + a] + sg * w0;
+      rfma(acc[6 + a], -d, w1);
+      rfma(acc[9 + a], d, w0);
     } else {
-      acc[6 + a] = acc[6 + a] - sg * ti(w0);
-      acc[9 + a] = acc[9 + a] + sg * ti(w1);
+      rfma(acc[6 + a], -d, ti(w0));
+      rfma(acc[9 + a], d, ti(w1));
     }
   }
 }
@@ -409,39 +411,6 @@ __device__ __forceinline__ void bl_link(const cx<float> (&u)[9], const cx<float>
     }
 }
 
-// y = (C + m4) x with the site's clover blocks read from the block layout,
-// one chirality at a time
-__device__ __forceinline__ void bl_diag(const float4* C, int blk, int vol, int s, float m4, const cx<float> (&x)[12],
-                                        cx<float> (&y)[12]) {
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    float raw[36];
-#pragma unroll
-    for (int q = 0; q < 9; ++q) {
-      const float4 v = C[((long)blk * 18 + 9 * h + q) * vol + s];
-      raw[4 * q] = v.x;
-      raw[4 * q + 1] = v.y;
-      raw[4 * q + 2] = v.z;
-      raw[4 * q + 3] = v.w;
-    }
-    HermBlock<float> B;
-#pragma unroll
-    for (int q = 0; q < 6; ++q) B.d[q] = raw[q];
-#pragma unroll
-    for (int q = 0; q < 15; ++q) B.o[q] = cx<float>{raw[6 + 2 * q], raw[7 + 2 * q]};
-    herm_apply(B, m4, &x[6 * h], &y[6 * h]);
-  }
-}
-
-__device__ __forceinline__ void bl_load_spinor(const float4* f, long base, int vol, int s, cx<float> (&v)[12]) {
-#pragma unroll
-  for (int k = 0; k < 6; ++k) {
-    const float4 q = f[(base + k) * vol + s];
-    v[2 * k] = cx<float>{q.x, q.y};
-    v[2 * k + 1] = cx<float>{q.z, q.w};
-  }
-}
-
 struct SapPass {
   Geom g;
   Blocking b;
@@ -452,26 +421,95 @@ struct SapPass {
   float4* psi;
   const float2* U;
   const float4* C;
-  float4* av;            // the large-block kernel's D'_B rho between its two phases (block layout)
   const double* rt;      // time hop ratios [4][T] (fwd, bwd, ...; boundary sign folded in)
   const double* sratio;  // spatial hop ratios of the light-quark factorisation, or null
   float m4;              // 4 + M
 };
 
-// the origin of the kidx-th block of a colour
-__device__ __forceinline__ void bl_origin(const Blocking& b, int colour, int kidx, int (&o)[4]) {
+// Element s of component array k of block blk (blk is the same for the whole
+// wave): scalar base, lane offset.
+template <typename T>
+__device__ __forceinline__ const T* bl_at(const T* f, int ncomp, int blk, int k, int vol, int s) {
+  return at(scalar_base(f + ((long)blk * ncomp + k) * vol), s);
+}
+
+__device__ __forceinline__ void bl_load_spinor(const float4* f, int blk, int vol, int s, cx<float> (&v)[12]) {
+#pragma unroll
+  for (int k = 0; k < 6; ++k) {
+    const float4 q = *bl_at(f, 6, blk, k, vol, s);
+    v[2 * k] = cx<float>{q.x, q.y};
+    v[2 * k + 1] = cx<float>{q.z, q.w};
+  }
+}
+
+__device__ __forceinline__ void bl_store_spinor(float4* f, int blk, int vol, int s, const cx<float> (&v)[12]) {
+#pragma unroll
+  for (int k = 0; k < 6; ++k)
+    *const_cast<float4*>(bl_at(f, 6, blk, k, vol, s)) = make_float4(v[2 * k].x, v[2 * k].y, v[2 * k + 1].x, v[2 * k + 1].y);
+}
+
+__device__ __forceinline__ void bl_load_link(const float2* U, int blk, int mu, int vol, int s, cx<float> (&u)[9]) {
+#pragma unroll
+  for (int q = 0; q < 9; ++q) {
+    const float2 v = *bl_at(U, 36, blk, mu * 9 + q, vol, s);
+    u[q] = cx<float>{v.x, v.y};
+  }
+}
+
+__device__ __forceinline__ HermBlock<float> bl_herm(const float4 (&raw)[9]) {
+  const float f[36] = {raw[0].x, raw[0].y, raw[0].z, raw[0].w, raw[1].x, raw[1].y, raw[1].z, raw[1].w, raw[2].x,
+                       raw[2].y, raw[2].z, raw[2].w, raw[3].x, raw[3].y, raw[3].z, raw[3].w, raw[4].x, raw[4].y,
+                       raw[4].z, raw[4].w, raw[5].x, raw[5].y, raw[5].z, raw[5].w, raw[6].x, raw[6].y, raw[6].z,
+                       raw[6].w, raw[7].x, raw[7].y, raw[7].z, raw[7].w, raw[8].x, raw[8].y, raw[8].z, raw[8].w};
+  HermBlock<float> B;
+#pragma unroll
+  for (int q = 0; q < 6; ++q) B.d[q] = f[q];
+#pragma unroll
+  for (int q = 0; q < 15; ++q) B.o[q] = cx<float>{f[6 + 2 * q], f[7 + 2 * q]};
+  return B;
+}
+
+// y = (C + m4) x with the site's clover blocks read from the block layout,
+// one chirality at a time
+__device__ __forceinline__ void bl_diag(const float4* C, int blk, int vol, int s, float m4, const cx<float> (&x)[12],
+                                        cx<float> (&y)[12]) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    float4 raw[9];
+#pragma unroll
+    for (int q = 0; q < 9; ++q) raw[q] = *bl_at(C, 18, blk, 9 * h + q, vol, s);
+    herm_apply(bl_herm(raw), m4, &x[6 * h], &y[6 * h]);
+  }
+}
+
+// Coordinates (in blocks) of the kidx-th block of a colour; the last one takes
+// the parity.  The divisions run on the vector unit: back to scalar registers,
+// so that what follows from the coordinates (block indices, base addresses) is
+// scalar arithmetic.
+struct BCoord {
+  int c[4];
+};
+__device__ __forceinline__ BCoord bl_coord(const Blocking& b, int colour, int kidx) {
+  BCoord r;
   const int h3 = b.nb[3] / 2;
-  int c3 = kidx % h3;
+  r.c[3] = kidx % h3;
   kidx /= h3;
-  const int c2 = kidx % b.nb[2];
+  r.c[2] = kidx % b.nb[2];
   kidx /= b.nb[2];
-  const int c1 = kidx % b.nb[1];
-  const int c0 = kidx / b.nb[1];
-  c3 = 2 * c3 + ((colour + c0 + c1 + c2) & 1);
-  o[0] = c0 * b.bs[0];
-  o[1] = c1 * b.bs[1];
-  o[2] = c2 * b.bs[2];
-  o[3] = c3 * b.bs[3];
+  r.c[1] = kidx % b.nb[1];
+  r.c[0] = kidx / b.nb[1];
+  r.c[3] = 2 * r.c[3] + ((colour + r.c[0] + r.c[1] + r.c[2]) & 1);
+#pragma unroll
+  for (int mu = 0; mu < 4; ++mu) r.c[mu] = __builtin_amdgcn_readfirstlane(r.c[mu]);
+  return r;
+}
+// index of the block next to it in direction MU
+template <int MU, int SG>
+__device__ __forceinline__ int bl_next(const Blocking& b, const BCoord& o) {
+  int y[4] = {o.c[0], o.c[1], o.c[2], o.c[3]};
+  y[MU] = SG > 0 ? (y[MU] + 1 == b.nb[MU] ? 0 : y[MU] + 1) : (y[MU] == 0 ? b.nb[MU] - 1 : y[MU] - 1);
+  return ((y[0] + y[1] + y[2] + y[3]) & 1) * b.nhalf + ((y[0] * b.nb[1] + y[1]) * b.nb[2] + y[2]) * (b.nb[3] / 2) +
+         y[3] / 2;
 }
 
 // coordinates within its block of the block's site s
@@ -484,369 +522,557 @@ __device__ __forceinline__ void bl_local(const Blocking& b, int s, int (&l)[4]) 
   l[0] = s / b.bs[1];
 }
 
-// hop coefficients at x: time ratios, spatial ratios (or 1)
-__device__ __forceinline__ void bl_coefs(const SapPass& a, const int (&x)[4], float (&cf)[4], float (&cb)[4]) {
+// hop coefficients at site l of block o, with the -1/2 of the hops: time
+// ratios, spatial ratios (or 1)
+__device__ __forceinline__ void bl_coefs(const SapPass& a, const BCoord& o, const int (&l)[4], float (&cf)[4],
+                                         float (&cb)[4]) {
   const Geom& g = a.g;
   const int Ls[4] = {g.T, g.L1, g.L2, g.L3};
-  cf[0] = (float)a.rt[x[0]];
-  cb[0] = (float)a.rt[g.T + x[0]];
+  const int x0 = o.c[0] * a.b.bs[0] + l[0];
+  cf[0] = -0.5f * (float)a.rt[x0];
+  cb[0] = -0.5f * (float)a.rt[g.T + x0];
   int off = 0;
 #pragma unroll
   for (int mu = 1; mu < 4; ++mu) {
-    cf[mu] = a.sratio ? (float)a.sratio[off + x[mu]] : 1.f;
-    cb[mu] = a.sratio ? (float)a.sratio[off + Ls[mu] + x[mu]] : 1.f;
+    const int x = o.c[mu] * a.b.bs[mu] + l[mu];
+    cf[mu] = a.sratio ? -0.5f * (float)a.sratio[off + x] : -0.5f;
+    cb[mu] = a.sratio ? -0.5f * (float)a.sratio[off + Ls[mu] + x] : -0.5f;
     off += 4 * Ls[mu];
   }
 }
 
-__device__ __forceinline__ void bl_load_link(const float2* U, int blk, int mu, int vol, int s, cx<float> (&u)[9]) {
-#pragma unroll
-  for (int q = 0; q < 9; ++q) {
-    const float2 v = U[((long)blk * 36 + mu * 9 + q) * vol + s];
-    u[q] = cx<float>{v.x, v.y};
-  }
+// strides of a block's site index
+__device__ __forceinline__ int bl_stride(const Blocking& b, int mu) {
+  return mu == 0 ? b.bs[1] * b.bs[2] * b.bs[3] : mu == 1 ? b.bs[2] * b.bs[3] : mu == 2 ? b.bs[3] : 1;
 }
 
-// out = D' psi at site x (site s of block blk), psi from memory, every
-// neighbour inside or outside the block; with own_zero the psi of block blk is
-// zero and not read.  REG: the site's forward links are Ureg.
+// out += the hops in direction MU that reach site s of block blk from the
+// neighbour blocks (the sites of the block's faces).  REG: U holds the site's
+// forward link.
 template <bool REG, int MU>
-__device__ __forceinline__ void bl_dprime_dir(const SapPass& a, int blk, const int (&x)[4], float cfm, float cbm,
-                                              const cx<float> (&Ureg)[4][9], int s, cx<float> (&out)[12]) {
-  const Geom& g = a.g;
+__device__ __forceinline__ void bl_face(const SapPass& a, const BCoord& o, int blk, int s, const int (&l)[4],
+                                        const cx<float> (&U)[9], float cf, float cb, cx<float> (&out)[12]) {
   const Blocking& b = a.b;
-  const int L = MU == 0 ? g.T : MU == 1 ? g.L1 : MU == 2 ? g.L2 : g.L3;
+  const int span = (b.bs[MU] - 1) * bl_stride(b, MU);
   cx<float> v[12], h[6], w[6], u[9];
-  int y[4] = {x[0], x[1], x[2], x[3]};
-  y[MU] = x[MU] + 1 == L ? 0 : x[MU] + 1;
-  BLoc q = bl_locate(b, y[0], y[1], y[2], y[3]);
-  if (!(a.own_zero && q.blk == blk)) {
-    bl_load_spinor(a.psi, (long)q.blk * 6, b.vol, q.s, v);
+  if (l[MU] + 1 == b.bs[MU]) {
+    bl_load_spinor(a.psi, bl_next<MU, 1>(b, o), b.vol, s - span, v);
     bl_proj<MU, 1>(v, h);
     if constexpr (REG) {
-      bl_link<false>(Ureg[MU], h, w);
+      bl_link<false>(U, h, w);
     } else {
       bl_load_link(a.U, blk, MU, b.vol, s, u);
       bl_link<false>(u, h, w);
     }
-    bl_recon<MU, 1>(out, w, -0.5f * cfm);
+    bl_recon<MU, 1>(out, w, cf);
   }
-  y[MU] = x[MU] == 0 ? L - 1 : x[MU] - 1;
-  q = bl_locate(b, y[0], y[1], y[2], y[3]);
-  if (!(a.own_zero && q.blk == blk)) {
-    bl_load_link(a.U, q.blk, MU, b.vol, q.s, u);
-    bl_load_spinor(a.psi, (long)q.blk * 6, b.vol, q.s, v);
+  if (l[MU] == 0) {
+    const int nb = bl_next<MU, -1>(b, o);
+    bl_load_link(a.U, nb, MU, b.vol, s + span, u);
+    bl_load_spinor(a.psi, nb, b.vol, s + span, v);
     bl_proj<MU, -1>(v, h);
     bl_link<true>(u, h, w);
-    bl_recon<MU, -1>(out, w, -0.5f * cbm);
+    bl_recon<MU, -1>(out, w, cb);
   }
 }
 
-template <bool REG>
-__device__ __forceinline__ void bl_dprime(const SapPass& a, int blk, int s, const int (&x)[4], const float (&cf)[4],
-                                          const float (&cb)[4], const cx<float> (&Ureg)[4][9],
-                                          cx<float> (&out)[12]) {
-  if (!a.own_zero) {
-    cx<float> v[12];
-    bl_load_spinor(a.psi, (long)blk * 6, a.b.vol, s, v);
-    bl_diag(a.C, blk, a.b.vol, s, a.m4, v, out);
-  } else {
-#pragma unroll
-    for (int c = 0; c < 12; ++c) out[c] = cx<float>{0.f, 0.f};
-  }
-  bl_dprime_dir<REG, 0>(a, blk, x, cf[0], cb[0], Ureg, s, out);
-  bl_dprime_dir<REG, 1>(a, blk, x, cf[1], cb[1], Ureg, s, out);
-  bl_dprime_dir<REG, 2>(a, blk, x, cf[2], cb[2], Ureg, s, out);
-  bl_dprime_dir<REG, 3>(a, blk, x, cf[3], cb[3], Ureg, s, out);
-}
-
-// the minimal-residual coefficient w = <a, rho>_B / |a|^2_B from per-thread
-// FP64 partials: wave sums, then the waves in order (every thread calls it)
-template <int NT>
-__device__ __forceinline__ cx<float> bl_mr_coef(double nr, double ni, double dn, double (&red)[3][NT / 64],
-                                                double (&wsh)[2]) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  nr = wave_sum(nr);
-  ni = wave_sum(ni);
-  dn = wave_sum(dn);
-  if (lane == 0) {
-    red[0][wv] = nr;
-    red[1][wv] = ni;
-    red[2][wv] = dn;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double sr = 0.0, si = 0.0, sd = 0.0;
-    for (int q = 0; q < NT / 64; ++q) {
-      sr += red[0][q];
-      si += red[1][q];
-      sd += red[2][q];
-    }
-    wsh[0] = sd > 0.0 ? sr / sd : 0.0;
-    wsh[1] = sd > 0.0 ? si / sd : 0.0;
-  }
-  __syncthreads();
-  return cx<float>{(float)wsh[0], (float)wsh[1]};
-}
-
+// per-thread FP64 terms of <a, rho>_B and |a|^2_B
 __device__ __forceinline__ void bl_mr_sums(const cx<float> (&av)[12], const cx<float> (&rv)[12], double& nr,
                                            double& ni, double& dn) {
 #pragma unroll
   for (int c = 0; c < 12; ++c) {
-    nr += (double)av[c].x * (double)rv[c].x + (double)av[c].y * (double)rv[c].y;
-    ni += (double)av[c].x * (double)rv[c].y - (double)av[c].y * (double)rv[c].x;
-    dn += (double)av[c].x * (double)av[c].x + (double)av[c].y * (double)av[c].y;
+    const double ax = av[c].x, ay = av[c].y, rx = rv[c].x, ry = rv[c].y;
+    nr = fmar(ay, ry, fmar(ax, rx, nr));
+    ni = fmar(-ay, rx, fmar(ax, ry, ni));
+    dn = fmar(ay, ay, fmar(ax, ax, dn));
   }
 }
 
-__device__ __forceinline__ void bl_store_psi(const SapPass& a, int blk, int s, const cx<float> (&dpsi)[12]) {
-  cx<float> v[12];
-  if (a.own_zero) {
-#pragma unroll
-    for (int c = 0; c < 12; ++c) v[c] = dpsi[c];
-  } else {
-    bl_load_spinor(a.psi, (long)blk * 6, a.b.vol, s, v);
-#pragma unroll
-    for (int c = 0; c < 12; ++c) v[c] = v[c] + dpsi[c];
+// The minimal-residual coefficient w = <a, rho>_B / |a|^2_B from per-thread
+// FP64 terms: wave sums, then the waves in order.  Every thread calls it and
+// forms w itself, so there is one barrier; a second call must have a barrier
+// after the first one's return.
+template <int NW>
+__device__ __forceinline__ cx<float> bl_mr_coef(double nr, double ni, double dn, double (&red)[4][NW]) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const double v = wave_sum4(nr, ni, dn, 0.0);
+  if ((lane & 15) == 0) red[wave_row_value(lane >> 4)][wv] = v;
+  __syncthreads();
+  double sr = 0.0, si = 0.0, sd = 0.0;
+  for (int q = 0; q < nw; ++q) {
+    sr += red[0][q];
+    si += red[1][q];
+    sd += red[2][q];
   }
+  return sd > 0.0 ? cx<float>{(float)(sr / sd), (float)(si / sd)} : cx<float>{0.f, 0.f};
+}
+
+// dpsi += w rho, rho -= w a
+__device__ __forceinline__ void bl_mr_step(cx<float> w, const cx<float> (&av)[12], cx<float> (&rv)[12],
+                                           cx<float> (&dpsi)[12]) {
 #pragma unroll
-  for (int q = 0; q < 6; ++q)
-    a.psi[((long)blk * 6 + q) * a.b.vol + s] = make_float4(v[2 * q].x, v[2 * q].y, v[2 * q + 1].x, v[2 * q + 1].y);
+  for (int c = 0; c < 12; ++c) {
+    cfma(dpsi[c], w, rv[c]);
+    cfma(rv[c], cx<float>{-w.x, -w.y}, av[c]);
+  }
+}
+
+// ---- blocks with whole time slices in a wave
+//
+// A thread per site.  The spatial neighbours of a site are in the same wave, so
+// the hops 1..3 exchange half spinors by lane permutes; the hops in time hand
+// them over in LDS.  That leaves the LDS to one chirality of the clover blocks;
+// the other one, the links, the residual and psi stay in registers, so that a
+// pass reads each of them once.  The backward hop at x needs U_mu(x - mu)^+
+// applied to the spinor at x - mu, which the thread of x - mu forms with its
+// own link.  Two workgroups per CU.  (One with the clover blocks read again in
+// each step, four directions through LDS: 426 us a pass at 64x32^3 with 4^4
+// blocks, 2.8 GB past L2, half of the vector issue; this one 343 us, 1.2 GB,
+// 0.64 of the issue.)  Workgroups of an XCD take neighbouring blocks, which read
+// the same faces.
+__host__ __device__ inline size_t sap_slice_lds(int nt) { return sizeof(float4) * (9 + 6) * (size_t)nt; }
+
+// value of lane `from` / 4
+__device__ __forceinline__ void bl_permute(int from, cx<float> (&h)[6]) {
+#pragma unroll
+  for (int e = 0; e < 6; ++e) {
+    h[e].x = __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(h[e].x)));
+    h[e].y = __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(h[e].y)));
+  }
+}
+
+__device__ __forceinline__ void bl_put_half(float4* buf, int nt, int s, const cx<float> (&h)[6]) {
+#pragma unroll
+  for (int e = 0; e < 3; ++e) buf[e * nt + s] = make_float4(h[2 * e].x, h[2 * e].y, h[2 * e + 1].x, h[2 * e + 1].y);
+}
+__device__ __forceinline__ void bl_get_half(const float4* buf, int nt, int s, cx<float> (&h)[6]) {
+#pragma unroll
+  for (int e = 0; e < 3; ++e) {
+    const float4 q = buf[e * nt + s];
+    h[2 * e] = cx<float>{q.x, q.y};
+    h[2 * e + 1] = cx<float>{q.z, q.w};
+  }
+}
+
+template <int MU>
+__device__ __forceinline__ void bl_slice_hop(const Blocking& b, const int (&l)[4], const cx<float> (&U)[9],
+                                             const cx<float> (&v)[12], float cf, float cb, cx<float> (&out)[12]) {
+  const int lane = threadIdx.x & 63, st = bl_stride(b, MU);
+  cx<float> h[6], g[6], w[6];
+  bl_proj<MU, 1>(v, h);
+  bl_permute(((lane + st) & 63) << 2, h);
+  bl_proj<MU, -1>(v, g);
+  bl_link<true>(U, g, w);
+  bl_permute(((lane - st) & 63) << 2, w);
+  bl_link<false>(U, h, g);
+  bl_recon<MU, 1>(out, g, l[MU] + 1 < b.bs[MU] ? cf : 0.f);
+  bl_recon<MU, -1>(out, w, l[MU] > 0 ? cb : 0.f);
+}
+
+// The on-chip part of a site: links, clover (one chirality at cl + k nt + s),
+// coefficients (zero beyond the block's sites), buffers of the time hops.
+struct SliceSite {
+  cx<float> U[4][9];
+  float4 c0[9];
+  const float4* cl;
+  float4 *hf, *hb;
+  int l[4], s, nt;
+  float cf[4], cb[4];
+};
+
+// out = D'_B v
+__device__ __forceinline__ void bl_slice_dprime(const SapPass& a, const SliceSite& t, const cx<float> (&v)[12],
+                                                cx<float> (&out)[12]) {
+  const Blocking& b = a.b;
+  cx<float> h[6], w[6];
+  bl_proj<0, 1>(v, h);
+  bl_put_half(t.hf, t.nt, t.s, h);
+  bl_proj<0, -1>(v, h);
+  bl_link<true>(t.U[0], h, w);
+  bl_put_half(t.hb, t.nt, t.s, w);
+  herm_apply(bl_herm(t.c0), a.m4, &v[0], &out[0]);
+  {
+    float4 raw[9];
+#pragma unroll
+    for (int q = 0; q < 9; ++q) raw[q] = t.cl[q * t.nt + t.s];
+    herm_apply(bl_herm(raw), a.m4, &v[6], &out[6]);
+  }
+  bl_slice_hop<1>(b, t.l, t.U[1], v, t.cf[1], t.cb[1], out);
+  bl_slice_hop<2>(b, t.l, t.U[2], v, t.cf[2], t.cb[2], out);
+  bl_slice_hop<3>(b, t.l, t.U[3], v, t.cf[3], t.cb[3], out);
+  __syncthreads();
+  const int st = bl_stride(b, 0);
+  if (t.l[0] + 1 < b.bs[0]) {
+    bl_get_half(t.hf, t.nt, t.s + st, h);
+    bl_link<false>(t.U[0], h, w);
+    bl_recon<0, 1>(out, w, t.cf[0]);
+  }
+  if (t.l[0] > 0) {
+    bl_get_half(t.hb, t.nt, t.s - st, w);
+    bl_recon<0, -1>(out, w, t.cb[0]);
+  }
 }
 
 // One pass of the Schwarz procedure over the blocks of one colour:
 // rho = r - D' psi on the block (NB_ZERO: psi = 0 everywhere, rho = r), nmr
 // minimal-residual steps with the Dirichlet block operator, psi += the
 // accumulated correction.  Block sums in FP64, reduced in a fixed order.
-// Blocks of at most kSapThreads sites, a thread per site.
 template <bool NB_ZERO>
-__global__ void __launch_bounds__(kSapThreads, 2) sap_block_kernel(SapPass a) {
-  __shared__ float rho_l[24 * kSapThreads];
-  __shared__ float hb[4 * 12 * kSapThreads];  // backward hops handed to x + mu
-  __shared__ double red[3][kSapThreads / 64];
-  __shared__ double wsh[2];
+__global__ void __launch_bounds__(kSapThreads, 2) sap_slice_kernel(SapPass a) {
+  extern __shared__ float4 slice_lds[];
+  __shared__ double red[4][kSapThreads / 64];
   const Blocking& b = a.b;
-  const int s = threadIdx.x;
-  const bool valid = s < b.vol;
-  const int blk = a.colour * b.nhalf + blockIdx.x;
-  const int st[4] = {b.bs[1] * b.bs[2] * b.bs[3], b.bs[2] * b.bs[3], b.bs[3], 1};
-  int o[4], l[4];
-  bl_origin(b, a.colour, blockIdx.x, o);
-  bl_local(b, valid ? s : 0, l);
-  const int x[4] = {o[0] + l[0], o[1] + l[1], o[2] + l[2], o[3] + l[3]};
-  float cf[4], cb[4];
-  bl_coefs(a, x, cf, cb);
-  // the site's forward links, kept for the pass (the clover blocks are
-  // read again at each use: holding them too would halve the waves per SIMD)
-  cx<float> U[4][9];
+  const int tile = xcd_tile(blockIdx.x, gridDim.x);
+  const int blk = a.colour * b.nhalf + tile;
+  const bool valid = (int)threadIdx.x < b.vol;
+  const int s = valid ? threadIdx.x : 0;
+  const BCoord o = bl_coord(b, a.colour, tile);
+  SliceSite t;
+  t.nt = blockDim.x;
+  t.s = threadIdx.x;
+  t.hf = slice_lds + 9 * t.nt;
+  t.hb = slice_lds + 12 * t.nt;
+  t.cl = slice_lds;
+  bl_local(b, s, t.l);
+  bl_coefs(a, o, t.l, t.cf, t.cb);
 #pragma unroll
-  for (int mu = 0; mu < 4; ++mu) bl_load_link(a.U, blk, mu, b.vol, valid ? s : 0, U[mu]);
-  // block residual
+  for (int mu = 0; mu < 4; ++mu) bl_load_link(a.U, blk, mu, b.vol, s, t.U[mu]);
+#pragma unroll
+  for (int q = 0; q < 9; ++q) t.c0[q] = *bl_at(a.C, 18, blk, q, b.vol, s);
+#pragma unroll
+  for (int q = 0; q < 9; ++q) slice_lds[q * t.nt + t.s] = *bl_at(a.C, 18, blk, 9 + q, b.vol, s);
+  // beyond the block's sites: no hops, zero spinors
+  if (!valid) {
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) t.cf[mu] = t.cb[mu] = 0.f;
+  }
+  cx<float> dpsi[12], rv[12], av[12];
+#pragma unroll
+  for (int c = 0; c < 12; ++c) dpsi[c] = rv[c] = av[c] = cx<float>{0.f, 0.f};
+  if constexpr (!NB_ZERO) {
+    if (!a.own_zero) {
+      if (valid) bl_load_spinor(a.psi, blk, b.vol, s, dpsi);
+      bl_slice_dprime(a, t, dpsi, av);
+      __syncthreads();  // the buffers of the time hops are free again
+    }
+    if (valid) {
+      bl_face<true, 0>(a, o, blk, s, t.l, t.U[0], t.cf[0], t.cb[0], av);
+      bl_face<true, 1>(a, o, blk, s, t.l, t.U[1], t.cf[1], t.cb[1], av);
+      bl_face<true, 2>(a, o, blk, s, t.l, t.U[2], t.cf[2], t.cb[2], av);
+      bl_face<true, 3>(a, o, blk, s, t.l, t.U[3], t.cf[3], t.cb[3], av);
+    }
+  }
   if (valid) {
-    cx<float> rv[12];
-    bl_load_spinor(a.r, (long)blk * 6, b.vol, s, rv);
-    if constexpr (!NB_ZERO) {
-      cx<float> out[12];
-      bl_dprime<true>(a, blk, s, x, cf, cb, U, out);
+    bl_load_spinor(a.r, blk, b.vol, s, rv);
 #pragma unroll
-      for (int c = 0; c < 12; ++c) rv[c] = rv[c] - out[c];
-    }
-#pragma unroll
-    for (int c = 0; c < 12; ++c) {
-      rho_l[(2 * c) * kSapThreads + s] = rv[c].x;
-      rho_l[(2 * c + 1) * kSapThreads + s] = rv[c].y;
-    }
+    for (int c = 0; c < 12; ++c) rv[c] = rv[c] - av[c];
   }
-  cx<float> dpsi[12];
-#pragma unroll
-  for (int c = 0; c < 12; ++c) dpsi[c] = cx<float>{0.f, 0.f};
   for (int it = 0; it < a.nmr; ++it) {
-    __syncthreads();  // rho complete
-    cx<float> rv[12];
-#pragma unroll
-    for (int c = 0; c < 12; ++c)
-      rv[c] = cx<float>{rho_l[(2 * c) * kSapThreads + s], rho_l[(2 * c + 1) * kSapThreads + s]};
-    // hand the backward hops to the sites x + mu of the block
-    if (valid) {
-      cx<float> h[6], w[6];
-#define DP_SAP_PUSH(MU)                                                \
-  if (l[MU] + 1 < b.bs[MU]) {                                          \
-    bl_proj<MU, -1>(rv, h);                                            \
-    bl_link<true>(U[MU], h, w);                                        \
-    for (int e = 0; e < 6; ++e) {                                      \
-      hb[((MU * 12) + 2 * e) * kSapThreads + s + st[MU]] = w[e].x;     \
-      hb[((MU * 12) + 2 * e + 1) * kSapThreads + s + st[MU]] = w[e].y; \
-    }                                                                  \
-  }
-      DP_SAP_PUSH(0)
-      DP_SAP_PUSH(1)
-      DP_SAP_PUSH(2)
-      DP_SAP_PUSH(3)
-#undef DP_SAP_PUSH
-    }
-    __syncthreads();
-    // av = D'_B rho at x: the diagonal term, then the hops with -1/2 folded
-    // into their coefficients
-    cx<float> av[12];
+    bl_slice_dprime(a, t, rv, av);
     double nr = 0.0, ni = 0.0, dn = 0.0;
-    if (valid) {
-      cx<float> v[12], h[6], w[6];
-      bl_diag(a.C, blk, b.vol, s, a.m4, rv, av);
-#define DP_SAP_PULL(MU)                                                                                 \
-  if (l[MU] + 1 < b.bs[MU]) {                                                                           \
-    const int n = s + st[MU];                                                                           \
-    for (int c = 0; c < 12; ++c)                                                                        \
-      v[c] = cx<float>{rho_l[(2 * c) * kSapThreads + n], rho_l[(2 * c + 1) * kSapThreads + n]};         \
-    bl_proj<MU, 1>(v, h);                                                                               \
-    bl_link<false>(U[MU], h, w);                                                                        \
-    bl_recon<MU, 1>(av, w, -0.5f * cf[MU]);                                                             \
-  }                                                                                                     \
-  if (l[MU] > 0) {                                                                                      \
-    for (int e = 0; e < 6; ++e)                                                                         \
-      w[e] = cx<float>{hb[((MU * 12) + 2 * e) * kSapThreads + s], hb[((MU * 12) + 2 * e + 1) * kSapThreads + s]}; \
-    bl_recon<MU, -1>(av, w, -0.5f * cb[MU]);                                                            \
+    bl_mr_sums(av, rv, nr, ni, dn);
+    bl_mr_step(bl_mr_coef(nr, ni, dn, red), av, rv, dpsi);
   }
-      DP_SAP_PULL(0)
-      DP_SAP_PULL(1)
-      DP_SAP_PULL(2)
-      DP_SAP_PULL(3)
-#undef DP_SAP_PULL
-      bl_mr_sums(av, rv, nr, ni, dn);
-    }
-    const cx<float> w = bl_mr_coef<kSapThreads>(nr, ni, dn, red, wsh);
-    if (valid) {
-#pragma unroll
-      for (int c = 0; c < 12; ++c) {
-        dpsi[c] = dpsi[c] + cmul(w, rv[c]);
-        rv[c] = rv[c] - cmul(w, av[c]);
-        rho_l[(2 * c) * kSapThreads + s] = rv[c].x;
-        rho_l[(2 * c + 1) * kSapThreads + s] = rv[c].y;
-      }
-    }
-  }
-  if (valid) bl_store_psi(a, blk, s, dpsi);
+  if (valid) bl_store_spinor(a.psi, blk, b.vol, s, dpsi);
 }
 
-// The same pass for blocks of kSapThreads + 1 .. kSapBigSites sites:
+// ---- other blocks of at most kSapThreads sites
+//
+// A thread per site; the links in registers, the residual in LDS, where the
+// forward hops read it and the backward hops are handed over; the clover blocks
+// are read again in each step.
+
+struct BlockLds {
+  float v[24 * kSapThreads];       // the spinors D'_B is applied to
+  float hb[4 * 12 * kSapThreads];  // backward hops handed to x + mu
+};
+template <int MU>
+__device__ __forceinline__ void bl_push(const Blocking& b, BlockLds& m, int s, const int (&l)[4],
+                                        const cx<float> (&U)[9], const cx<float> (&v)[12]) {
+  if (l[MU] + 1 < b.bs[MU]) {
+    cx<float> h[6], w[6];
+    bl_proj<MU, -1>(v, h);
+    bl_link<true>(U, h, w);
+    const int n = s + bl_stride(b, MU);
+#pragma unroll
+    for (int e = 0; e < 6; ++e) {
+      m.hb[((MU * 12) + 2 * e) * kSapThreads + n] = w[e].x;
+      m.hb[((MU * 12) + 2 * e + 1) * kSapThreads + n] = w[e].y;
+    }
+  }
+}
+template <int MU>
+__device__ __forceinline__ void bl_pull(const Blocking& b, const BlockLds& m, int s, const int (&l)[4],
+                                        const cx<float> (&U)[9], float cf, float cb, cx<float> (&out)[12]) {
+  cx<float> v[12], h[6], w[6];
+  if (l[MU] + 1 < b.bs[MU]) {
+    const int n = s + bl_stride(b, MU);
+#pragma unroll
+    for (int c = 0; c < 12; ++c)
+      v[c] = cx<float>{m.v[(2 * c) * kSapThreads + n], m.v[(2 * c + 1) * kSapThreads + n]};
+    bl_proj<MU, 1>(v, h);
+    bl_link<false>(U, h, w);
+    bl_recon<MU, 1>(out, w, cf);
+  }
+  if (l[MU] > 0) {
+#pragma unroll
+    for (int e = 0; e < 6; ++e)
+      w[e] = cx<float>{m.hb[((MU * 12) + 2 * e) * kSapThreads + s], m.hb[((MU * 12) + 2 * e + 1) * kSapThreads + s]};
+    bl_recon<MU, -1>(out, w, cb);
+  }
+}
+// out = D'_B v (v: the thread's site).  Every thread calls it; a second call must
+// have a barrier after the first one's return.
+__device__ __forceinline__ void bl_block_dprime(const SapPass& a, BlockLds& m, int blk, bool valid, int s,
+                                                const int (&l)[4], const cx<float> (&U)[4][9], const float (&cf)[4],
+                                                const float (&cb)[4], const cx<float> (&v)[12],
+                                                cx<float> (&out)[12]) {
+  const Blocking& b = a.b;
+  if (valid) {
+#pragma unroll
+    for (int c = 0; c < 12; ++c) {
+      m.v[(2 * c) * kSapThreads + s] = v[c].x;
+      m.v[(2 * c + 1) * kSapThreads + s] = v[c].y;
+    }
+    bl_push<0>(b, m, s, l, U[0], v);
+    bl_push<1>(b, m, s, l, U[1], v);
+    bl_push<2>(b, m, s, l, U[2], v);
+    bl_push<3>(b, m, s, l, U[3], v);
+  }
+  __syncthreads();
+  if (valid) {
+    bl_diag(a.C, blk, b.vol, s, a.m4, v, out);
+    bl_pull<0>(b, m, s, l, U[0], cf[0], cb[0], out);
+    bl_pull<1>(b, m, s, l, U[1], cf[1], cb[1], out);
+    bl_pull<2>(b, m, s, l, U[2], cf[2], cb[2], out);
+    bl_pull<3>(b, m, s, l, U[3], cf[3], cb[3], out);
+  }
+}
+
+template <bool NB_ZERO>
+__global__ void __launch_bounds__(kSapThreads, 2) sap_block_kernel(SapPass a) {
+  __shared__ BlockLds m;
+  __shared__ double red[4][kSapThreads / 64];
+  const Blocking& b = a.b;
+  const int tile = xcd_tile(blockIdx.x, gridDim.x);
+  const int blk = a.colour * b.nhalf + tile;
+  const bool valid = (int)threadIdx.x < b.vol;
+  const int s = valid ? threadIdx.x : 0;
+  const BCoord o = bl_coord(b, a.colour, tile);
+  int l[4];
+  bl_local(b, s, l);
+  float cf[4], cb[4];
+  bl_coefs(a, o, l, cf, cb);
+  cx<float> U[4][9];
+#pragma unroll
+  for (int mu = 0; mu < 4; ++mu) bl_load_link(a.U, blk, mu, b.vol, s, U[mu]);
+  cx<float> dpsi[12], rv[12], av[12];
+#pragma unroll
+  for (int c = 0; c < 12; ++c) dpsi[c] = rv[c] = av[c] = cx<float>{0.f, 0.f};
+  if constexpr (!NB_ZERO) {
+    if (!a.own_zero) {
+      if (valid) bl_load_spinor(a.psi, blk, b.vol, s, dpsi);
+      bl_block_dprime(a, m, blk, valid, s, l, U, cf, cb, dpsi, av);
+      __syncthreads();  // the LDS buffers are free again
+    }
+    if (valid) {
+      bl_face<true, 0>(a, o, blk, s, l, U[0], cf[0], cb[0], av);
+      bl_face<true, 1>(a, o, blk, s, l, U[1], cf[1], cb[1], av);
+      bl_face<true, 2>(a, o, blk, s, l, U[2], cf[2], cb[2], av);
+      bl_face<true, 3>(a, o, blk, s, l, U[3], cf[3], cb[3], av);
+    }
+  }
+  if (valid) {
+    bl_load_spinor(a.r, blk, b.vol, s, rv);
+#pragma unroll
+    for (int c = 0; c < 12; ++c) rv[c] = rv[c] - av[c];
+  }
+  for (int it = 0; it < a.nmr; ++it) {
+    bl_block_dprime(a, m, blk, valid, s, l, U, cf, cb, rv, av);
+    double nr = 0.0, ni = 0.0, dn = 0.0;
+    if (valid) bl_mr_sums(av, rv, nr, ni, dn);
+    bl_mr_step(bl_mr_coef(nr, ni, dn, red), av, rv, dpsi);
+  }
+  if (valid) bl_store_spinor(a.psi, blk, b.vol, s, dpsi);
+}
+
+// ---- blocks of kSapThreads + 1 .. kSapBigSites sites
+//
 // kSapBigThreads threads with kSapBigPer sites each (site s = thread + q
-// kSapBigThreads); the residual in LDS as before, but the links are read at
-// each use, both hops of a site read rho from LDS (no hand-over buffer), and
-// D'_B rho and psi stay in memory between the phases of a step, so that a
-// block of up to 1536 sites fits.
+// kSapBigThreads).  The residual is in LDS, where both hops of a site read it;
+// D'_B rho and psi stay in registers, the links and clover blocks (1.1 MB for
+// 6^4 sites) are read again in each step.  (With D'_B rho and psi in memory
+// between the phases of a step: 262 us a pass at 48x24^3 with 6^4 blocks, 5.4 kB
+// a site at 5.7 TB/s; this one 229 us, 3.6 kB at 5.1 TB/s.)
 constexpr int kSapBigThreads = 512;
 constexpr int kSapBigPer = 3;
 constexpr int kSapBigSites = kSapBigThreads * kSapBigPer;
 
+template <int MU>
+__device__ __forceinline__ void bl_big_hop(const SapPass& a, const float* v_l, int blk, int s, const int (&l)[4],
+                                           float cf, float cb, cx<float> (&out)[12]) {
+  const Blocking& b = a.b;
+  cx<float> v[12], h[6], w[6], u[9];
+  if (l[MU] + 1 < b.bs[MU]) {
+    const int n = s + bl_stride(b, MU);
+    bl_load_link(a.U, blk, MU, b.vol, s, u);
+#pragma unroll
+    for (int c = 0; c < 12; ++c) v[c] = cx<float>{v_l[(2 * c) * kSapBigSites + n], v_l[(2 * c + 1) * kSapBigSites + n]};
+    bl_proj<MU, 1>(v, h);
+    bl_link<false>(u, h, w);
+    bl_recon<MU, 1>(out, w, cf);
+  }
+  if (l[MU] > 0) {
+    const int n = s - bl_stride(b, MU);
+    bl_load_link(a.U, blk, MU, b.vol, n, u);
+#pragma unroll
+    for (int c = 0; c < 12; ++c) v[c] = cx<float>{v_l[(2 * c) * kSapBigSites + n], v_l[(2 * c + 1) * kSapBigSites + n]};
+    bl_proj<MU, -1>(v, h);
+    bl_link<true>(u, h, w);
+    bl_recon<MU, -1>(out, w, cb);
+  }
+}
+
+// out is complete here: else the compiler interleaves the hops and sites and
+// spills
+__device__ __forceinline__ void bl_pin(cx<float> (&out)[12]) {
+#pragma unroll
+  for (int c = 0; c < 12; ++c) asm volatile("" : "+v"(out[c].x), "+v"(out[c].y));
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// out = D'_B at site s of the spinors in v_l; v: the site's own one
+__device__ __forceinline__ void bl_big_dprime(const SapPass& a, const float* v_l, const BCoord& o, int blk, int s,
+                                              const cx<float> (&v)[12], cx<float> (&out)[12]) {
+  // opaque: the coordinates and coefficients of kSapBigPer sites would
+  // otherwise be kept through the steps, in registers that are not there
+  asm volatile("" : "+v"(s));
+  int l[4];
+  bl_local(a.b, s, l);
+  float cf[4], cb[4];
+  bl_coefs(a, o, l, cf, cb);
+  bl_diag(a.C, blk, a.b.vol, s, a.m4, v, out);
+  bl_big_hop<0>(a, v_l, blk, s, l, cf[0], cb[0], out);
+  bl_pin(out);
+  bl_big_hop<1>(a, v_l, blk, s, l, cf[1], cb[1], out);
+  bl_pin(out);
+  bl_big_hop<2>(a, v_l, blk, s, l, cf[2], cb[2], out);
+  bl_pin(out);
+  bl_big_hop<3>(a, v_l, blk, s, l, cf[3], cb[3], out);
+  bl_pin(out);
+}
+
+__device__ __forceinline__ void bl_big_put(float* v_l, int s, const cx<float> (&v)[12]) {
+#pragma unroll
+  for (int c = 0; c < 12; ++c) {
+    v_l[(2 * c) * kSapBigSites + s] = v[c].x;
+    v_l[(2 * c + 1) * kSapBigSites + s] = v[c].y;
+  }
+}
+__device__ __forceinline__ void bl_big_get(const float* v_l, int s, cx<float> (&v)[12]) {
+#pragma unroll
+  for (int c = 0; c < 12; ++c) v[c] = cx<float>{v_l[(2 * c) * kSapBigSites + s], v_l[(2 * c + 1) * kSapBigSites + s]};
+}
+
 template <bool NB_ZERO>
 __global__ void __launch_bounds__(kSapBigThreads, 2) sap_block_big_kernel(SapPass a) {
-  __shared__ float rho_l[24 * kSapBigSites];
-  __shared__ double red[3][kSapBigThreads / 64];
-  __shared__ double wsh[2];
+  __shared__ float v_l[24 * kSapBigSites];
+  __shared__ double red[4][kSapBigThreads / 64];
   const Blocking& b = a.b;
-  const int blk = a.colour * b.nhalf + blockIdx.x;
-  const int st[4] = {b.bs[1] * b.bs[2] * b.bs[3], b.bs[2] * b.bs[3], b.bs[3], 1};
-  int o[4];
-  bl_origin(b, a.colour, blockIdx.x, o);
-  const cx<float> Unone[4][9] = {};
-  // block residual
-#pragma unroll 1
+  const int tile = xcd_tile(blockIdx.x, gridDim.x);
+  const int blk = a.colour * b.nhalf + tile;
+  const BCoord o = bl_coord(b, a.colour, tile);
+  cx<float> av[kSapBigPer][12], dpsi[kSapBigPer][12];
+#pragma unroll
+  for (int q = 0; q < kSapBigPer; ++q)
+#pragma unroll
+    for (int c = 0; c < 12; ++c) dpsi[q][c] = av[q][c] = cx<float>{0.f, 0.f};
+  if constexpr (!NB_ZERO) {
+    if (!a.own_zero) {
+#pragma unroll
+      for (int q = 0; q < kSapBigPer; ++q) {
+        const int s = threadIdx.x + q * kSapBigThreads;
+        if (s < b.vol) {
+          cx<float> pv[12];
+          bl_load_spinor(a.psi, blk, b.vol, s, pv);
+          bl_big_put(v_l, s, pv);
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < kSapBigPer; ++q) {
+        const int s = threadIdx.x + q * kSapBigThreads;
+        if (s < b.vol) {
+          cx<float> pv[12];
+          bl_big_get(v_l, s, pv);
+          bl_big_dprime(a, v_l, o, blk, s, pv, av[q]);
+        }
+      }
+      __syncthreads();  // every site's hops are done: v_l is free for rho, site by site
+    }
+#pragma unroll
+    for (int q = 0; q < kSapBigPer; ++q) {
+      int s = threadIdx.x + q * kSapBigThreads;
+      if (s < b.vol) {
+        asm volatile("" : "+v"(s));
+        int l[4];
+        bl_local(b, s, l);
+        float cf[4], cb[4];
+        bl_coefs(a, o, l, cf, cb);
+        const cx<float> none[9] = {};
+        bl_face<false, 0>(a, o, blk, s, l, none, cf[0], cb[0], av[q]);
+        bl_face<false, 1>(a, o, blk, s, l, none, cf[1], cb[1], av[q]);
+        bl_face<false, 2>(a, o, blk, s, l, none, cf[2], cb[2], av[q]);
+        bl_face<false, 3>(a, o, blk, s, l, none, cf[3], cb[3], av[q]);
+        bl_pin(av[q]);
+      }
+    }
+  }
+#pragma unroll
   for (int q = 0; q < kSapBigPer; ++q) {
     const int s = threadIdx.x + q * kSapBigThreads;
     if (s < b.vol) {
-      int l[4];
-      bl_local(b, s, l);
-      const int x[4] = {o[0] + l[0], o[1] + l[1], o[2] + l[2], o[3] + l[3]};
       cx<float> rv[12];
-      bl_load_spinor(a.r, (long)blk * 6, b.vol, s, rv);
+      bl_load_spinor(a.r, blk, b.vol, s, rv);
+#pragma unroll
+      for (int c = 0; c < 12; ++c) rv[c] = rv[c] - av[q][c];
       if constexpr (!NB_ZERO) {
-        float cf[4], cb[4];
-        bl_coefs(a, x, cf, cb);
-        cx<float> out[12];
-        bl_dprime<false>(a, blk, s, x, cf, cb, Unone, out);
-#pragma unroll
-        for (int c = 0; c < 12; ++c) rv[c] = rv[c] - out[c];
+        if (!a.own_zero) bl_big_get(v_l, s, dpsi[q]);
       }
-#pragma unroll
-      for (int c = 0; c < 12; ++c) {
-        rho_l[(2 * c) * kSapBigSites + s] = rv[c].x;
-        rho_l[(2 * c + 1) * kSapBigSites + s] = rv[c].y;
-      }
+      bl_big_put(v_l, s, rv);
+      bl_pin(dpsi[q]);
     }
   }
   for (int it = 0; it < a.nmr; ++it) {
     __syncthreads();  // rho complete
     double nr = 0.0, ni = 0.0, dn = 0.0;
-#pragma unroll 1
+#pragma unroll
     for (int q = 0; q < kSapBigPer; ++q) {
       const int s = threadIdx.x + q * kSapBigThreads;
       if (s < b.vol) {
-        int l[4];
-        bl_local(b, s, l);
-        const int x[4] = {o[0] + l[0], o[1] + l[1], o[2] + l[2], o[3] + l[3]};
-        float cf[4], cb[4];
-        bl_coefs(a, x, cf, cb);
-        cx<float> rv[12], av[12], v[12], h[6], w[6], u[9];
+        cx<float> rv[12];
+        bl_big_get(v_l, s, rv);
+        bl_big_dprime(a, v_l, o, blk, s, rv, av[q]);
+        bl_mr_sums(av[q], rv, nr, ni, dn);
+        bl_pin(av[q]);
+      }
+    }
+    const cx<float> w = bl_mr_coef(nr, ni, dn, red);
 #pragma unroll
-        for (int c = 0; c < 12; ++c)
-          rv[c] = cx<float>{rho_l[(2 * c) * kSapBigSites + s], rho_l[(2 * c + 1) * kSapBigSites + s]};
-        bl_diag(a.C, blk, b.vol, s, a.m4, rv, av);
-#define DP_SAP_BIG(MU)                                                                                   \
-  if (l[MU] + 1 < b.bs[MU]) {                                                                            \
-    const int n = s + st[MU];                                                                            \
-    for (int c = 0; c < 12; ++c)                                                                         \
-      v[c] = cx<float>{rho_l[(2 * c) * kSapBigSites + n], rho_l[(2 * c + 1) * kSapBigSites + n]};        \
-    bl_proj<MU, 1>(v, h);                                                                                \
-    bl_load_link(a.U, blk, MU, b.vol, s, u);                                                             \
-    bl_link<false>(u, h, w);                                                                             \
-    bl_recon<MU, 1>(av, w, -0.5f * cf[MU]);                                                              \
-  }                                                                                                      \
-  if (l[MU] > 0) {                                                                                       \
-    const int n = s - st[MU];                                                                            \
-    for (int c = 0; c < 12; ++c)                                                                         \
-      v[c] = cx<float>{rho_l[(2 * c) * kSapBigSites + n], rho_l[(2 * c + 1) * kSapBigSites + n]};        \
-    bl_proj<MU, -1>(v, h);                                                                               \
-    bl_load_link(a.U, blk, MU, b.vol, n, u);                                                             \
-    bl_link<true>(u, h, w);                                                                              \
-    bl_recon<MU, -1>(av, w, -0.5f * cb[MU]);                                                             \
+    for (int q = 0; q < kSapBigPer; ++q) {
+      const int s = threadIdx.x + q * kSapBigThreads;
+      if (s < b.vol) {
+        cx<float> rv[12];
+        bl_big_get(v_l, s, rv);
+        bl_mr_step(w, av[q], rv, dpsi[q]);
+        bl_big_put(v_l, s, rv);
+      }
+    }
   }
-        DP_SAP_BIG(0)
-        DP_SAP_BIG(1)
-        DP_SAP_BIG(2)
-        DP_SAP_BIG(3)
-#undef DP_SAP_BIG
-        bl_mr_sums(av, rv, nr, ni, dn);
 #pragma unroll
-        for (int e = 0; e < 6; ++e)
-          a.av[((long)blk * 6 + e) * b.vol + s] = make_float4(av[2 * e].x, av[2 * e].y, av[2 * e + 1].x, av[2 * e + 1].y);
-      }
-    }
-    const cx<float> w = bl_mr_coef<kSapBigThreads>(nr, ni, dn, red, wsh);
-#pragma unroll 1
-    for (int q = 0; q < kSapBigPer; ++q) {
-      const int s = threadIdx.x + q * kSapBigThreads;
-      if (s < b.vol) {
-        cx<float> rv[12], dp[12], av[12];
-        bl_load_spinor(a.av, (long)blk * 6, b.vol, s, av);
-#pragma unroll
-        for (int c = 0; c < 12; ++c) {
-          rv[c] = cx<float>{rho_l[(2 * c) * kSapBigSites + s], rho_l[(2 * c + 1) * kSapBigSites + s]};
-          dp[c] = cmul(w, rv[c]);
-          rv[c] = rv[c] - cmul(w, av[c]);
-          rho_l[(2 * c) * kSapBigSites + s] = rv[c].x;
-          rho_l[(2 * c + 1) * kSapBigSites + s] = rv[c].y;
-        }
-        // psi += w rho (psi of the block is read only by this workgroup)
-        if (!(a.own_zero && it == 0)) {
-          cx<float> pv[12];
-          bl_load_spinor(a.psi, (long)blk * 6, b.vol, s, pv);
-#pragma unroll
-          for (int c = 0; c < 12; ++c) dp[c] = pv[c] + dp[c];
-        }
-#pragma unroll
-        for (int e = 0; e < 6; ++e)
-          a.psi[((long)blk * 6 + e) * b.vol + s] = make_float4(dp[2 * e].x, dp[2 * e].y, dp[2 * e + 1].x, dp[2 * e + 1].y);
-      }
-    }
+  for (int q = 0; q < kSapBigPer; ++q) {
+    const int s = threadIdx.x + q * kSapBigThreads;
+    if (s < b.vol) bl_store_spinor(a.psi, blk, b.vol, s, dpsi[q]);
   }
 }
 
@@ -1011,7 +1237,7 @@ struct SapState {
   std::vector<double> h_gcr;
   // fused block solves: links, clover, r and psi in block layout (FP32)
   bool fused = false;
-  DevBuf ubl, cbl, rbl, pbl, abl;
+  DevBuf ubl, cbl, rbl, pbl;
   std::vector<double> h_part;
 };
 
@@ -1227,6 +1453,13 @@ bool sap_fused_enabled(int prec, const Blocking& b) {
   return !(e && e[0] == '0');
 }
 
+// Whole time slices in a wave: a slice of 1, 2, 4, .. or 64 sites.  The other
+// small blocks (slices across waves) would have to hand over all directions in
+// LDS, which then has no room for clover blocks.
+bool sap_slices_in_wave(const Blocking& b) {
+  return b.vol <= kSapThreads && 64 % (b.bs[1] * b.bs[2] * b.bs[3]) == 0;
+}
+
 // block-layout buffers and the links and clover gathered into them
 int sap_fused_setup(dp_ctx* c, SapState& s, const Blocking& b) {
   const long V = 2L * c->g.Vh;
@@ -1234,7 +1467,6 @@ int sap_fused_setup(dp_ctx* c, SapState& s, const Blocking& b) {
   DP_HIP(c, reserve(c, s.cbl, sizeof(float4) * 18 * V));
   DP_HIP(c, reserve(c, s.rbl, sizeof(float4) * 6 * V));
   DP_HIP(c, reserve(c, s.pbl, sizeof(float4) * 6 * V));
-  if (b.vol > kSapThreads) DP_HIP(c, reserve(c, s.abl, sizeof(float4) * 6 * V));
   hipLaunchKernelGGL(sap_gather_kernel, block_grid(c->g), dim3(kBlock), 0, c->stream, c->g, b,
                      c->U[F32][0].as<float2>(), c->U[F32][1].as<float2>(), c->C32[0].as<float4>(),
                      c->C32[1].as<float4>(), s.ubl.as<float2>(), s.cbl.as<float4>());
@@ -1252,7 +1484,6 @@ int sap_apply_fused(dp_ctx* c, SapState& s, const Blocking& b, int ncy, int nmr)
   a.psi = s.pbl.as<float4>();
   a.U = s.ubl.as<float2>();
   a.C = s.cbl.as<float4>();
-  a.av = s.abl.as<float4>();
   a.rt = s.ratio.as<double>();
   a.sratio = space_hop_ratios(c);
   a.m4 = (float)(4.0 + c->M);
@@ -1261,7 +1492,13 @@ int sap_apply_fused(dp_ctx* c, SapState& s, const Blocking& b, int ncy, int nmr)
       a.colour = colour;
       a.own_zero = cy == 0;
       const bool first = cy == 0 && colour == 0;
-      if (b.vol <= kSapThreads) {
+      if (sap_slices_in_wave(b)) {
+        const int nt = (b.vol + 63) / 64 * 64;
+        if (first)
+          hipLaunchKernelGGL(sap_slice_kernel<true>, dim3(b.nhalf), dim3(nt), sap_slice_lds(nt), c->stream, a);
+        else
+          hipLaunchKernelGGL(sap_slice_kernel<false>, dim3(b.nhalf), dim3(nt), sap_slice_lds(nt), c->stream, a);
+      } else if (b.vol <= kSapThreads) {
         if (first)
           hipLaunchKernelGGL(sap_block_kernel<true>, dim3(b.nhalf), dim3(kSapThreads), 0, c->stream, a);
         else

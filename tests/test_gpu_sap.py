@@ -267,3 +267,32 @@ def test_sap_gcr_group_sizes(nkv):
     assert nkv < 17 or info["iters"] > 17
     res = eta - oracle.apply(U, C, M, S)
     assert np.linalg.norm(res) / np.linalg.norm(eta) <= 1.0001 * r
+
+
+@pytest.mark.parametrize("dims,block,nmr", [((6, 4, 4, 4), (3, 2, 2, 2), 4),      # 8 slices a wave, 40 lanes idle
+                                            ((8, 4, 4, 4), (4, 1, 1, 1), 4),      # slices of one site, no spatial hop inside
+                                            ((4, 8, 8, 8), (1, 4, 4, 4), 3),      # one slice, no time hop inside
+                                            ((6, 8, 8, 8), (3, 4, 4, 4), 1),      # a slice a wave, 3 waves
+                                            ((32, 4, 4, 8), (16, 2, 2, 4), 4),    # 4 slices a wave, 4 waves
+                                            ((4, 10, 10, 10), (2, 5, 5, 5), 4),   # 250 sites, slices across waves
+                                            ((4, 24, 24, 2), (2, 12, 12, 1), 2)])  # 288 sites: mostly idle sites per thread
+def test_sap_block_shapes(dims, block, nmr):
+    """Blocks at the edges of what each of the fused kernels takes, with all
+    four factorisation directions, against the oracle (the FP32 bound above)."""
+    log(f"test_sap_block_shapes {dims} {block} nmr={nmr}")
+    U = synth.gauge_su3(dims, 0.4, 51)
+    C = oracle.clover(U, 1.6)
+    M = 0.05
+    beta = synth.beta_cosh_paper(dims, 0.3)
+    r = synth.random_spinor(dims, 52)
+    want = oracle.sap_apply(U, C, M, r, block, beta=beta, ncy=3, nmr=nmr)
+    with lattice(dims) as L:
+        L.set_gauge(U)
+        L.set_clover(1.6)
+        L.set_mass(M)
+        L.set_beta(beta)
+        got = L.sap_precondition(r, block, ncy=3, nmr=nmr)
+    err = np.linalg.norm(got - want) / np.linalg.norm(want)
+    worst = np.abs(got - want).max() / np.abs(want).max()
+    log(f"  relative error {err:.2e}, max {worst:.2e}")
+    assert err < 1e-5 and worst < 1e-5
