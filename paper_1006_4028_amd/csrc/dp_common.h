@@ -97,6 +97,7 @@ enum Epi {
   EPI_DIAG = 2,     // out = (C + m4) xin + sign * H in
   EPI_SUB = 3,      // out = xin - H in
   EPI_INV_SUB = 4,  // out = A^-1 (xin - H in)
+  EPI_FULL = 5,     // EPI_DIAG for both parities in one launch (see HopArgs::out2)
 };
 
 // Reductions fused into a kernel's epilogue; results land in per-slot block
@@ -168,7 +169,11 @@ struct HopArgs {
   const void* U_in;    // links at input-parity sites
   int link_prec;
   SpinorRef in, out, xin;
-  CloverRef clov;      // C of the output parity (EPI_DIAG)
+  CloverRef clov;      // C of the output parity (EPI_DIAG, EPI_FULL)
+  // EPI_FULL: output and C of the other parity, whose input is xin and whose
+  // epilogue input is in
+  SpinorRef out2;
+  CloverRef clov2;
   SlotTable slots;
   ReduceRef red;
   int nslots;

@@ -674,11 +674,40 @@ constexpr int kSharedMinWaves = 2;
 // 31.2, FP16 21.2 / 20.6 against 26.5 / 26.0; 4096 (16^3x32, 4 slots) FP16 equal.
 constexpr int slab_max_waves(int p) { return p == F64 ? 1024 : p == F32 ? 3072 : 4096; }
 
+// EPI_FULL: the two parities of an item are neighbouring items of an XCD, so
+// that a link, the forward one of a site of this parity and a backward one for
+// the other parity, is fetched once for both (one FP64 slot, two launches / one:
+// 1030 / 745 us at 64x32^3, 315 / 233 at 48x24^3, 18 / 8 at 16x8^3; 12 FP64
+// slots, which share their links in LDS: 1620 / 1620 at 48x24^3).  The arguments
+// of parity 1 - a.p if `other`.
+__device__ __forceinline__ void pick_parity(HopArgs& a, bool other) {
+  if (!other) return;
+  a.p = 1 - a.p;
+  const void* u = a.U_out;
+  a.U_out = a.U_in;
+  a.U_in = u;
+  const SpinorRef f = a.in;
+  a.in = a.xin;
+  a.xin = f;
+  a.out = a.out2;
+  a.clov = a.clov2;
+}
+// the epilogue an output parity sees, and its XCD's item
+constexpr int site_epi(int epi) { return epi == EPI_FULL ? EPI_DIAG : epi; }
+template <int EPI>
+__device__ __forceinline__ int xcd_item(HopArgs& a) {
+  const int j = blockIdx.x >> 3;
+  if constexpr (EPI != EPI_FULL) return j;
+  pick_parity(a, j & 1);
+  return j >> 1;
+}
+
 // One wave per (chunk, timeslice, slot), the slots of a chunk in neighbouring
 // blocks of the same XCD.
-template <int P, int EPI, int RED, bool DAG>
+template <int P, int EPIL, int RED, bool DAG>
 __global__ void __launch_bounds__(64, slab_min_waves(P)) hop_kernel_slab(HopArgs a, SlabMap m) {
-  const int j = blockIdx.x >> 3, jj = j / a.nslots, slot = j - jj * a.nslots;
+  constexpr int EPI = site_epi(EPIL);
+  const int j = xcd_item<EPIL>(a), jj = j / a.nslots, slot = j - jj * a.nslots;
   const Item it = map_item(m, a.g.T, blockIdx.x & 7, jj, EPI == EPI_DIAG);
   if (!it.in || (a.slots.mask && !a.slots.mask[slot])) return;
   const int sp = it.chunk * 64 + threadIdx.x;
@@ -700,14 +729,15 @@ constexpr size_t shared_tile_bytes(bool blocks) {
   return 8 * 9 * 64 * sizeof(LinkElem<P>) + (blocks ? (blk_units(P) + (P == F16)) * 64 * sizeof(unsigned) : 0);
 }
 
-template <int P, int EPI, int RED, bool DAG, bool LINV>
+template <int P, int EPIL, int RED, bool DAG, bool LINV>
 __global__ void __launch_bounds__(kSharedThreads, kSharedMinWaves) hop_kernel_shared(HopArgs a, SlabMap m) {
+  constexpr int EPI = site_epi(EPIL);
   using E = LinkElem<P>;
   extern __shared__ __align__(16) unsigned char smem[];
   E* lu = reinterpret_cast<E*>(smem);
   unsigned* lc = reinterpret_cast<unsigned*>(smem + 8 * 9 * 64 * sizeof(E));
   const Geom& g = a.g;
-  const Item it = map_item(m, g.T, blockIdx.x & 7, blockIdx.x >> 3, EPI == EPI_DIAG);
+  const Item it = map_item(m, g.T, blockIdx.x & 7, xcd_item<EPIL>(a), EPI == EPI_DIAG);
   if (!it.in) return;  // the whole workgroup, before any barrier
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
@@ -784,7 +814,7 @@ hipError_t launch_one(const HopArgs& a, hipStream_t st, int* nparts_out) {
   // one of them.
   static const int tmap_knob = env_knob("DP_HOP_TMAP", -1);
   m.tmap = tmap_knob == 0 || tmap_knob == 1 ? tmap_knob : (P != F64 && (a.nslots == 1 || P == F16) ? 1 : 0);
-  const int nblocks = m.tmap ? 8 * m.tlen * m.nch : 8 * a.g.T * m.maxc;
+  const int nblocks = (m.tmap ? 8 * m.tlen * m.nch : 8 * a.g.T * m.maxc) * (EPI == EPI_FULL ? 2 : 1);
   *nparts_out = a.g.T * m.nch;
   if (a.nslots >= 2 && (long)a.g.T * m.nch * a.nslots > slab_max_waves(P)) {
     // waves per workgroup: the fewest rounds over the slots with at most four waves
@@ -796,7 +826,7 @@ hipError_t launch_one(const HopArgs& a, hipStream_t st, int* nparts_out) {
                          st, a, m);
     else
       hipLaunchKernelGGL((hop_kernel_shared<P, EPI, RED, DAG, false>), grid, block,
-                         shared_tile_bytes<P>(shared_clover<P, EPI>()), st, a, m);
+                         shared_tile_bytes<P>(shared_clover<P, site_epi(EPI)>()), st, a, m);
   } else {
     hipLaunchKernelGGL((hop_kernel_slab<P, EPI, RED, DAG>), dim3(nblocks * a.nslots), dim3(64), 0, st, a, m);
   }
@@ -812,6 +842,7 @@ hipError_t launch_epi(const HopArgs& a, hipStream_t st, int* np) {
     case EPI_INV: return launch_one<P, EPI_INV, RED_NONE, DAG>(a, st, np);
     case EPI_SUB: return launch_one<P, EPI_SUB, RED_NONE, DAG>(a, st, np);
     case EPI_INV_SUB: return launch_one<P, EPI_INV_SUB, RED_NONE, DAG>(a, st, np);
+    case EPI_FULL: return launch_one<P, EPI_FULL, RED_NONE, DAG>(a, st, np);
     case EPI_DIAG:
       switch (a.red.red) {
         case RED_NONE: return launch_one<P, EPI_DIAG, RED_NONE, DAG>(a, st, np);

@@ -280,6 +280,9 @@ SlotTable slot_table(Workspace& w, int T, int s0, int prec, const int* mask);
 const void* common_ainv(const Workspace& w, int s0, int n, int prec, const float** scale);
 
 // launch helpers over slots [s0, s0 + n) of a workspace
+// arguments of the full operator on both parities (0: even), all but the slots
+HopArgs full_args(dp_ctx* c, int prec, int dag, const SpinorRef& in_e, const SpinorRef& in_o, const SpinorRef& out_e,
+                  const SpinorRef& out_o);
 int hop(dp_ctx* c, Workspace& w, int s0, int n, int prec, int p, int dag, int epi, double sign, const Field& in,
         const Field& out, const Field* xin, const int* mask, int red = RED_NONE, int fin = FIN_NONE,
         const Field* wv = nullptr, int* inner_mask = nullptr);

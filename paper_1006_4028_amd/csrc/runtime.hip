@@ -430,6 +430,53 @@ int hop(dp_ctx* c, Workspace& w, int s0, int n, int prec, int p, int dag, int ep
   return DP_OK;
 }
 
+HopArgs full_args(dp_ctx* c, int prec, int dag, const SpinorRef& in_e, const SpinorRef& in_o, const SpinorRef& out_e,
+                  const SpinorRef& out_o) {
+  HopArgs a;
+  a.g = c->g;
+  a.p = 0;
+  a.dag = dag;
+  a.epi = EPI_FULL;
+  a.sign = 1.0;
+  a.U_out = c->U[prec][0].p;
+  a.U_in = c->U[prec][1].p;
+  a.link_prec = prec;
+  a.in = in_o;
+  a.xin = in_e;
+  a.out = out_e;
+  a.out2 = out_o;
+  CloverRef* clov[2] = {&a.clov, &a.clov2};
+  for (int p = 0; p < 2; ++p) {
+    clov[p]->prec = prec;
+    clov[p]->data = prec == F64 ? c->C64[p].p : prec == F32 ? c->C32[p].p : c->C16[p].p;
+    clov[p]->scale = prec == F16 ? c->C16s[p].as<float>() : nullptr;
+  }
+  return a;
+}
+
+// the full operator on the first n slots, both parities in one launch
+int hop_full(dp_ctx* c, Workspace& w, int n, int prec, int dag, const Field& in_e, const Field& in_o,
+             const Field& out_e, const Field& out_o) {
+  HopArgs a = full_args(c, prec, dag, in_e.ref(0), in_o.ref(0), out_e.ref(0), out_o.ref(0));
+  a.slots = slot_table(w, c->g.T, 0, prec, nullptr);
+  a.sratio = w.sratio;
+  a.red = reduce_ref(w, 0, RED_NONE, FIN_NONE, nullptr);
+  a.nslots = n;
+  hipEvent_t ev = nullptr;
+  DP_TRY(timing_begin(c, &ev));
+  int nparts = 0;
+  DP_HIP(c, launch_hop(a, c->stream, &nparts));
+  if (c->timing) {
+    double bytes, flops;
+    hop_cost(c, prec, EPI_DIAG, RED_NONE, n, &bytes, &flops);
+    const std::string name = std::string("hop_") + prec_name(prec) + "_full" + (dag ? "_dag" : "");
+    // every link, clover block and input once for both parities
+    const double links = 8.0 * 18 * c->g.Vh * (prec == F64 ? 8 : prec == F32 ? 4 : 2);
+    DP_TRY(timing_end(c, ev, name, 2 * bytes - links, 2 * flops));
+  }
+  return DP_OK;
+}
+
 int blas(dp_ctx* c, Workspace& w, int s0, int n, int op, int prec, const int* mask,
          std::initializer_list<const Field*> v, int fin, int* inner_mask) {
   BlasArgs a;
@@ -901,8 +948,7 @@ int apply_run(dp_ctx* c, Workspace& w, const double2* in, double2* out, int n, i
     DP_TRY(schur(c, w, 0, n, prec, dag, *ie, w.to, *oe, nullptr, RED_NONE, FIN_NONE));
     DP_TRY(blas(c, w, 0, n, OP_ZERO, prec, nullptr, {oo}));
   } else {
-    DP_TRY(hop(c, w, 0, n, prec, 0, dag, EPI_DIAG, 1.0, *io, *oe, ie, nullptr));
-    DP_TRY(hop(c, w, 0, n, prec, 1, dag, EPI_DIAG, 1.0, *ie, *oo, io, nullptr));
+    DP_TRY(hop_full(c, w, n, prec, dag, *ie, *io, *oe, *oo));
   }
   if (prec != F64) {
     DP_TRY(blas(c, w, 0, n, OP_TO64, prec, nullptr, {&w.b64, oe}));

@@ -1283,30 +1283,14 @@ int sap_alloc(dp_ctx* c, SapState& s, int nkv, int prec) {
 
 // out = D' in on the whole lattice, both parities (full operator, not Schur)
 int apply_full(dp_ctx* c, SapState& s, int prec, const Field& in, const Field& out) {
-  for (int p = 0; p < 2; ++p) {
-    HopArgs a;
-    a.g = c->g;
-    a.p = p;
-    a.dag = 0;
-    a.epi = EPI_DIAG;
-    a.sign = 1.0;
-    a.U_out = c->U[prec][p].p;
-    a.U_in = c->U[prec][1 - p].p;
-    a.link_prec = prec;
-    a.in = in.ref(1 - p);
-    a.out = out.ref(p);
-    a.xin = in.ref(p);
-    a.clov.prec = prec;
-    a.clov.data = prec == F64 ? c->C64[p].p : prec == F32 ? c->C32[p].p : c->C16[p].p;
-    a.clov.scale = prec == F16 ? c->C16s[p].as<float>() : nullptr;
-    a.slots.ratio = s.ratio.as<double>();
-    a.slots.m4 = s.m4.as<double>();
-    a.red.red = RED_NONE;
-    a.nslots = 1;
-    a.sratio = space_hop_ratios(c);
-    int nparts = 0;
-    DP_HIP(c, launch_hop(a, c->stream, &nparts));
-  }
+  HopArgs a = full_args(c, prec, 0, in.ref(0), in.ref(1), out.ref(0), out.ref(1));
+  a.slots.ratio = s.ratio.as<double>();
+  a.slots.m4 = s.m4.as<double>();
+  a.red.red = RED_NONE;
+  a.nslots = 1;
+  a.sratio = space_hop_ratios(c);
+  int nparts = 0;
+  DP_HIP(c, launch_hop(a, c->stream, &nparts));
   return DP_OK;
 }
 

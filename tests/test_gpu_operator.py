@@ -273,3 +273,30 @@ def test_schur_inverse_pivots(dims):
         e = max_rel(L.apply(psi, precond=True, schur=True), oracle_schur(oracle, U, C, M, psi, alpha))
         log(f"  max-element err {e:.2e}")
         assert e < 2e-11
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32", "f16"])
+def test_shared_tile_matches_one_wave(precision):
+    """A batch above the size up to which every slot has a wave of its own (9 x
+    512 waves) runs the kernels that share a tile's links between the slots:
+    bitwise the one-slot results, full operator (both parities in one launch)
+    and Schur operator, with their adjoints."""
+    import torch
+    dims, nrhs = (16, 16, 16, 16), 9
+    log(f"test_shared_tile_matches_one_wave {precision}")
+    U = synth.gauge_su3(dims, 0.3, 32)
+    psi = synth.random_spinor(dims, 16, nrhs=nrhs)
+    with lattice(dims) as L:
+        L.set_gauge(U)
+        L.set_clover(1.6)
+        L.set_mass(0.2)
+        L.set_alpha(synth.alpha_exp(dims[0], 0.3))
+        in_t = torch.from_numpy(psi.reshape(nrhs, -1)).cuda()
+        out_t, one_t = torch.empty_like(in_t), torch.empty_like(in_t[:1])
+        torch.cuda.synchronize()
+        for schur in (False, True):
+            for dagger in (False, True):
+                L.apply_dev(in_t, out_t, precond=True, dagger=dagger, schur=schur, precision=precision)
+                for k in (0, 3, 8):
+                    L.apply_dev(in_t[k:k + 1], one_t, precond=True, dagger=dagger, schur=schur, precision=precision)
+                    assert torch.equal(out_t[k], one_t[0]), (schur, dagger, k)
