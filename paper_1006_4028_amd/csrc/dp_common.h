@@ -98,6 +98,7 @@ enum Epi {
   EPI_SUB = 3,      // out = xin - H in
   EPI_INV_SUB = 4,  // out = A^-1 (xin - H in)
   EPI_FULL = 5,     // EPI_DIAG for both parities in one launch (see HopArgs::out2)
+  EPI_FULL_HOST = 6,  // the same into a host-layout array (FP64)
 };
 
 // Reductions fused into a kernel's epilogue; results land in per-slot block
@@ -169,11 +170,13 @@ struct HopArgs {
   const void* U_in;    // links at input-parity sites
   int link_prec;
   SpinorRef in, out, xin;
-  CloverRef clov;      // C of the output parity (EPI_DIAG, EPI_FULL)
-  // EPI_FULL: output and C of the other parity, whose input is xin and whose
+  CloverRef clov;      // C of the output parity (EPI_DIAG, EPI_FULL*)
+  // EPI_FULL*: output and C of the other parity, whose input is xin and whose
   // epilogue input is in
   SpinorRef out2;
   CloverRef clov2;
+  double2* aos = nullptr;  // EPI_FULL_HOST: [slot][site][4][3], slots aos_ss elements apart
+  long aos_ss = 0;
   SlotTable slots;
   ReduceRef red;
   int nslots;

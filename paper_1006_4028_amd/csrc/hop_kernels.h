@@ -384,6 +384,68 @@ constexpr bool shared_clover() {
 }
 constexpr int blk_units(int p) { return p == F32 ? 72 : p == F16 ? 36 : 0; }
 
+// A thread's output site: its index, spatial coordinates and neighbours
+// (2 mu forward, 2 mu + 1 backward).
+struct Site {
+  int i, x1, x2, x3;
+  // of the wave (host order): its first site within the timeslice, the odd x3
+  int sp0;
+  unsigned long long odd;
+  int nb[8];
+};
+
+// the epilogue an output parity sees
+constexpr int site_epi(int epi) { return epi == EPI_FULL || epi == EPI_FULL_HOST ? EPI_DIAG : epi; }
+
+// Spinors of a wave's 64 sites, a site per lane, stored in host order: site q at
+// dst + (2 q + odd(q)) 12, odd(q) the bits of `odd` (sites of the other parity lie
+// between), the first n sites.  Register k of four and the row of 16 lanes change
+// places by register swaps (four components of site 16 k + m in the lanes m of
+// the four rows), then a permute brings the four components of a site to
+// neighbouring lanes, which store 64 bytes of it.  No LDS, which the links fill.
+// (The full operator on 12 columns at 48x24^3: 1620 us and 530 of a separate
+// export pass; 1720 with this.)  Every lane of the wave calls it.
+__device__ __forceinline__ void store_host_order(double2* dst, unsigned long long odd, int n, const cx<double> (&v)[12],
+                                                 int lane) {
+  asm volatile("" : "+v"(lane));  // or the offsets stay in registers through the slots
+  const int m = lane >> 2, r = lane & 3, from = (16 * r + m) << 2;
+  dst = scalar_base(dst);
+#pragma unroll
+  for (int c = 0; c < 12; c += 4) {
+    unsigned w[4][4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const unsigned long long x = __builtin_bit_cast(unsigned long long, v[c + k].x);
+      const unsigned long long y = __builtin_bit_cast(unsigned long long, v[c + k].y);
+      w[k][0] = (unsigned)x;
+      w[k][1] = (unsigned)(x >> 32);
+      w[k][2] = (unsigned)y;
+      w[k][3] = (unsigned)(y >> 32);
+    }
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      const auto a = __builtin_amdgcn_permlane32_swap(w[0][d], w[2][d], false, false);
+      const auto b = __builtin_amdgcn_permlane32_swap(w[1][d], w[3][d], false, false);
+      const auto e = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
+      const auto f = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+      w[0][d] = e[0];
+      w[1][d] = e[1];
+      w[2][d] = f[0];
+      w[3][d] = f[1];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      u4v u;
+      u.x = __builtin_amdgcn_ds_bpermute(from, w[k][0]);
+      u.y = __builtin_amdgcn_ds_bpermute(from, w[k][1]);
+      u.z = __builtin_amdgcn_ds_bpermute(from, w[k][2]);
+      u.w = __builtin_amdgcn_ds_bpermute(from, w[k][3]);
+      const int q = 16 * k + m;
+      if (q < n) *const_cast<u4v*>(at(reinterpret_cast<const u4v*>(dst), (2 * q + (int)((odd >> q) & 1)) * 12 + c + r)) = u;
+    }
+  }
+}
+
 // Epilogue and fused reduction terms for one slot, one chirality at a time
 // (fewer live registers).  The epilogue's own inputs and the output are
 // streamed past L2 (read or written once per launch: 3% at 24^3x48 with 12
@@ -391,9 +453,12 @@ constexpr int blk_units(int p) { return p == F32 ? 72 : p == F16 ? 36 : 0; }
 // arithmetic precision per lane and added to the FP64 partial once.
 // load() issues the streams' loads (while the last neighbours are computed),
 // finish() does the rest.
-template <int P, int EPI, int RED, bool LDSB>
+template <int P, int EPIL, int RED, bool LDSB>
 struct Epilogue {
   using R = typename Tr<P>::R;
+  static constexpr int EPI = site_epi(EPIL);
+  static constexpr bool HOST = EPIL == EPI_FULL_HOST;
+  static constexpr bool WHOLE = P == F16 || HOST;  // the output is stored when both chiralities are there
   static constexpr int PW = rh_prec(P);
   static constexpr bool XIN = EPI == EPI_DIAG || EPI == EPI_SUB || EPI == EPI_INV_SUB;
   static constexpr bool INV = EPI == EPI_INV || EPI == EPI_INV_SUB;
@@ -406,11 +471,12 @@ struct Epilogue {
     if constexpr (DOTW && P != F64) load_raw_spinor<PW, true>(a.red.w, slot, i, a.g.Vp, wr);
   }
 
+  // HOST: x0, s of the wave's sites
   __device__ __forceinline__ void finish(const HopArgs& a, int slot, int i, cx<R> (&acc)[12], double (&red)[kRedMax],
-                                         const unsigned* lc, int lane) const {
+                                         const unsigned* lc, int lane, int x0, const Site& s) const {
     const Geom& g = a.g;
     R s0 = R(0), s1 = R(0), s2 = R(0), s3 = R(0), s4 = R(0), s5 = R(0), s6 = R(0);
-    cx<R> out[P == F16 ? 12 : 6];
+    cx<R> out[WHOLE ? 12 : 6];
     R bsc = R(1);  // FP16 block scale
     if constexpr (P == F16 && (EPI == EPI_DIAG || INV)) {
       if constexpr (LDSB) {
@@ -424,7 +490,7 @@ struct Epilogue {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       __builtin_amdgcn_sched_barrier(0);
-      cx<R>* o = &out[P == F16 ? 6 * h : 0];
+      cx<R>* o = &out[WHOLE ? 6 * h : 0];
       cx<R>* ac = &acc[6 * h];
       cx<R> xh[6], wh[6];
       if constexpr (XIN) decode_half<P>(xr, h, xh);
@@ -478,7 +544,7 @@ struct Epilogue {
         }
         blk_apply<P>(B, R(0), t, o);
       }
-      if constexpr (P != F16) store_half<P>(a.out, slot, h, i, g.Vp, o);
+      if constexpr (!WHOLE) store_half<P>(a.out, slot, h, i, g.Vp, o);
       if constexpr (DOTW) {
         if constexpr (P == F64) load_half64(a.red.w, slot, h, i, g.Vp, wh);  // here: fewer live registers
         else decode_half<PW>(wr, h, wh);
@@ -497,7 +563,11 @@ struct Epilogue {
         if constexpr (RED == RED_NORM) s0 = fmar(o[c].y, o[c].y, fmar(o[c].x, o[c].x, s0));
       }
     }
-    if constexpr (P == F16) SpinorIO<P>::template store<true>(a.out, slot, i, g.Vp, out);
+    if constexpr (HOST)
+      store_host_order(a.aos + slot * a.aos_ss + 24L * ((long)x0 * g.Vsh + s.sp0),
+                       s.odd, g.Vsh - s.sp0, out, lane);
+    else if constexpr (WHOLE)
+      SpinorIO<P>::template store<true>(a.out, slot, i, g.Vp, out);
     if constexpr (RED != RED_NONE) red[0] = (double)s0;
     if constexpr (RED == RED_DOT_EXT || RED == RED_TS || RED == RED_TS4) red[1] = (double)s1;
     if constexpr (RED == RED_TS || RED == RED_TS4) red[2] = (double)s2;
@@ -559,12 +629,6 @@ __device__ __forceinline__ Item map_item(const SlabMap& m, int T, int xcd, int j
   return it;
 }
 
-// A thread's output site: its index, spatial coordinates and neighbours
-// (2 mu forward, 2 mu + 1 backward).
-struct Site {
-  int i, x1, x2, x3;
-  int nb[8];
-};
 __device__ __forceinline__ void locate(const HopArgs& a, const SlabMap& m, int x0, int sp, Site& s) {
   const Geom& g = a.g;
   const int row = div_by(sp, g.L3h, m.mL3h), h = sp - row * g.L3h;
@@ -597,7 +661,9 @@ __device__ __forceinline__ void slot_work(const HopArgs& a, int slot, const Site
   double red[kRedMax];
 #pragma unroll
   for (int q = 0; q < kRedMax; ++q) red[q] = 0.0;
-  if (valid) {
+  // stores in host order need every lane of the wave; its sites beyond the
+  // timeslice are computed as the first one and not stored
+  if (valid || EPI == EPI_FULL_HOST) {
     const double* rt = a.slots.ratio + (long)slot * 4 * g.T + (DAG ? 2 * g.T : 0);
     R coef[8] = {(R)rt[x0], (R)rt[g.T + x0], R(1), R(1), R(1), R(1), R(1), R(1)};
     if (a.sratio) {  // uniform over the launch
@@ -629,7 +695,7 @@ __device__ __forceinline__ void slot_work(const HopArgs& a, int slot, const Site
     n.template fill<0>(a, slot, i, nb);
     Epilogue<P, EPI, RED, LDSB> epi;
     n.template step<0>(a, slot, i, nb, coef, one, lu, lane, acc, epi);
-    epi.finish(a, slot, i, acc, red, lc, lane);
+    epi.finish(a, slot, i, acc, red, lc, lane, x0, s);
   }
   if constexpr (RED != RED_NONE) {
     constexpr int nv = red_values(RED);
@@ -692,12 +758,11 @@ __device__ __forceinline__ void pick_parity(HopArgs& a, bool other) {
   a.out = a.out2;
   a.clov = a.clov2;
 }
-// the epilogue an output parity sees, and its XCD's item
-constexpr int site_epi(int epi) { return epi == EPI_FULL ? EPI_DIAG : epi; }
+// the XCD's item of the block
 template <int EPI>
 __device__ __forceinline__ int xcd_item(HopArgs& a) {
   const int j = blockIdx.x >> 3;
-  if constexpr (EPI != EPI_FULL) return j;
+  if constexpr (EPI == site_epi(EPI)) return j;
   pick_parity(a, j & 1);
   return j >> 1;
 }
@@ -714,7 +779,9 @@ __global__ void __launch_bounds__(64, slab_min_waves(P)) hop_kernel_slab(HopArgs
   const bool valid = sp < a.g.Vsh;
   Site s;
   locate(a, m, it.x0, valid ? sp : 0, s);
-  slot_work<P, EPI, RED, slab_pf(P), DAG, false, false>(a, slot, s, it.x0, valid, it.x0 * m.nch + it.chunk,
+  s.sp0 = it.chunk * 64;
+  if constexpr (EPIL == EPI_FULL_HOST) s.odd = __ballot((a.p + it.x0 + s.x1 + s.x2) & 1);
+  slot_work<P, EPIL, RED, slab_pf(P), DAG, false, false>(a, slot, s, it.x0, valid, it.x0 * m.nch + it.chunk,
                                                         a.g.T * m.nch, nullptr, nullptr, threadIdx.x);
 }
 
@@ -745,6 +812,8 @@ __global__ void __launch_bounds__(kSharedThreads, kSharedMinWaves) hop_kernel_sh
   const bool valid = sp < g.Vsh;
   Site s;
   locate(a, m, it.x0, valid ? sp : 0, s);
+  s.sp0 = it.chunk * 64;
+  if constexpr (EPIL == EPI_FULL_HOST) s.odd = __ballot((a.p + it.x0 + s.x1 + s.x2) & 1);
   // fill: tasks 0..7 are the link directions, task 8 the blocks; wave w takes
   // tasks w, w + nw, ...  Read once per launch: streamed past L2 (2-3%).
   constexpr bool blocks = (shared_clover<P, EPI>() || LINV) && P != F64;
@@ -784,7 +853,7 @@ __global__ void __launch_bounds__(kSharedThreads, kSharedMinWaves) hop_kernel_sh
     // keeps the compiler from hoisting the LDS reads out of this loop into
     // (many) registers
     asm volatile("" ::: "memory");
-    slot_work<P, EPI, RED, shared_pf(P), DAG, true, blocks>(a, slot, s, it.x0, valid, part, nparts, lu, lc, lane);
+    slot_work<P, EPIL, RED, shared_pf(P), DAG, true, blocks>(a, slot, s, it.x0, valid, part, nparts, lu, lc, lane);
   }
 }
 
@@ -814,7 +883,7 @@ hipError_t launch_one(const HopArgs& a, hipStream_t st, int* nparts_out) {
   // one of them.
   static const int tmap_knob = env_knob("DP_HOP_TMAP", -1);
   m.tmap = tmap_knob == 0 || tmap_knob == 1 ? tmap_knob : (P != F64 && (a.nslots == 1 || P == F16) ? 1 : 0);
-  const int nblocks = (m.tmap ? 8 * m.tlen * m.nch : 8 * a.g.T * m.maxc) * (EPI == EPI_FULL ? 2 : 1);
+  const int nblocks = (m.tmap ? 8 * m.tlen * m.nch : 8 * a.g.T * m.maxc) * (EPI == site_epi(EPI) ? 1 : 2);
   *nparts_out = a.g.T * m.nch;
   if (a.nslots >= 2 && (long)a.g.T * m.nch * a.nslots > slab_max_waves(P)) {
     // waves per workgroup: the fewest rounds over the slots with at most four waves
@@ -843,6 +912,9 @@ hipError_t launch_epi(const HopArgs& a, hipStream_t st, int* np) {
     case EPI_SUB: return launch_one<P, EPI_SUB, RED_NONE, DAG>(a, st, np);
     case EPI_INV_SUB: return launch_one<P, EPI_INV_SUB, RED_NONE, DAG>(a, st, np);
     case EPI_FULL: return launch_one<P, EPI_FULL, RED_NONE, DAG>(a, st, np);
+    case EPI_FULL_HOST:
+      if constexpr (P == F64) return launch_one<P, EPI_FULL_HOST, RED_NONE, DAG>(a, st, np);
+      else return hipErrorInvalidValue;
     case EPI_DIAG:
       switch (a.red.red) {
         case RED_NONE: return launch_one<P, EPI_DIAG, RED_NONE, DAG>(a, st, np);

@@ -454,10 +454,16 @@ HopArgs full_args(dp_ctx* c, int prec, int dag, const SpinorRef& in_e, const Spi
   return a;
 }
 
-// the full operator on the first n slots, both parities in one launch
+// the full operator on the first n slots, both parities in one launch, into
+// parity fields or (FP64) host-layout spinors `aos`
 int hop_full(dp_ctx* c, Workspace& w, int n, int prec, int dag, const Field& in_e, const Field& in_o,
-             const Field& out_e, const Field& out_o) {
+             const Field& out_e, const Field& out_o, double2* aos, long aos_ss) {
   HopArgs a = full_args(c, prec, dag, in_e.ref(0), in_o.ref(0), out_e.ref(0), out_o.ref(0));
+  if (aos) {
+    a.epi = EPI_FULL_HOST;
+    a.aos = aos;
+    a.aos_ss = aos_ss;
+  }
   a.slots = slot_table(w, c->g.T, 0, prec, nullptr);
   a.sratio = w.sratio;
   a.red = reduce_ref(w, 0, RED_NONE, FIN_NONE, nullptr);
@@ -948,7 +954,8 @@ int apply_run(dp_ctx* c, Workspace& w, const double2* in, double2* out, int n, i
     DP_TRY(schur(c, w, 0, n, prec, dag, *ie, w.to, *oe, nullptr, RED_NONE, FIN_NONE));
     DP_TRY(blas(c, w, 0, n, OP_ZERO, prec, nullptr, {oo}));
   } else {
-    DP_TRY(hop_full(c, w, n, prec, dag, *ie, *io, *oe, *oo));
+    DP_TRY(hop_full(c, w, n, prec, dag, *ie, *io, *oe, *oo, prec == F64 ? out : nullptr, col));
+    if (prec == F64) return DP_OK;  // the hop kernel stores host-layout spinors
   }
   if (prec != F64) {
     DP_TRY(blas(c, w, 0, n, OP_TO64, prec, nullptr, {&w.b64, oe}));
