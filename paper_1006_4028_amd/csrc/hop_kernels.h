@@ -732,12 +732,13 @@ constexpr int kSharedMinWaves = 2;
 // Up to so many waves, one per (chunk, timeslice, slot), several slots run as
 // one wave each too: a shared-tile workgroup would leave CUs without work and
 // take its slots one after the other.  Even / odd sites, us, one wave per slot
-// against shared tile: 768 waves (8^3x16, 12 slots) FP64 25.6 / 25.0 against
-// 30.2 / 25.2, FP32 14.1 / 13.7 against 18.8 / 19.4, FP16 9.3 / 9.6 against
-// 17.0 / 17.2; 1344 waves (12^3x24, 4 slots) FP64 28.8 / 27.8 against 26.5 / 23.6,
-// FP32 15.4 / 15.0 against 15.7 / 15.3; 2880 (36x18x20x14, 2 slots) FP32 28.4 / 27.3
-// against 34.3 / 30.0; 4032 (12^3x24, 12 slots) FP32 36.6 / 34.5 against 30.6 /
-// 31.2, FP16 21.2 / 20.6 against 26.5 / 26.0; 4096 (16^3x32, 4 slots) FP16 equal.
+// against shared tile: 768 waves (8^3x16, 12 slots) FP64 14.8 / 15.0 against
+// 28.6 / 25.0, FP32 10.6 / 10.4 against 17.9 / 19.2, FP16 9.1 / 9.5 against
+// 17.1 / 17.3; 1344 waves (12^3x24, 4 slots) FP64 28.4 / 26.9 against 26.3 / 22.9,
+// FP32 14.8 / 14.5 against 15.9 / 15.1; 2880 (36x18x20x14, 2 slots) FP32 28.5 / 28.0
+// against 34.7 / 30.6; 4032 (12^3x24, 12 slots) FP32 31.3 / 29.6 against 30.7 /
+// 30.8, FP16 21.0 / 20.6 against 26.7 / 26.1; 4096 (16^3x32, 4 slots) FP32 35.4 /
+// 32.5 against 33.0 / 28.6, FP16 equal.
 constexpr int slab_max_waves(int p) { return p == F64 ? 1024 : p == F32 ? 3072 : 4096; }
 
 // EPI_FULL: the two parities of an item are neighbouring items of an XCD, so
@@ -876,13 +877,22 @@ hipError_t launch_one(const HopArgs& a, hipStream_t st, int* nparts_out) {
   m.mL3h = recip32(a.g.L3h);
   m.mL2 = recip32(a.g.L2);
   // XCD mapping, chosen per launch: both mappings give bitwise the same
-  // results.  Measured on MI355X: timeslice ranges 2-6% faster for one FP32
-  // or FP16 slot and for 12 FP16 slots at 24^3x48 and 32^3x64, slabs 6% faster
-  // for 12 FP32 slots; FP64 keeps the slabs (one slot: 2% faster on timeslice
-  // ranges at 24^3x48, 4-10% slower at 32^3x64).  DP_HOP_TMAP = 0 / 1 forces
-  // one of them.
+  // results.  The one that spreads the work more evenly, if the XCD with most
+  // work has 5% less of it than with the other: slabs give ceil(chunks / 8)
+  // chunks to an XCD, timeslice ranges ceil(T / 8) timeslices.  Slabs against
+  // ranges, even sites, us: 16x8^3 (4 chunks, half of the XCDs idle) with 12 slots
+  // FP64 26.4 / 15.1, FP32 14.4 / 10.7, FP16 12.4 / 9.4; 14x20x18x36 (102 chunks) FP16
+  // 65.8 / 72.8, one FP32 slot 21.0 / 21.5.  Otherwise timeslice ranges for one
+  // FP32 or FP16 slot (2-6% faster) and for FP16 (12 slots, 24^3x48 and 32^3x64),
+  // slabs for several FP32 slots (6%) and FP64 (one slot, both parities, 64x32^3
+  // 744 / 850; 12 slots at 48x24^3 1716 / 1788).  DP_HOP_TMAP = 0 / 1 forces one of
+  // them.
   static const int tmap_knob = env_knob("DP_HOP_TMAP", -1);
-  m.tmap = tmap_knob == 0 || tmap_knob == 1 ? tmap_knob : (P != F64 && (a.nslots == 1 || P == F16) ? 1 : 0);
+  const double most_slab = 8.0 * m.maxc / m.nch, most_range = 8.0 * m.tlen / a.g.T;
+  if (tmap_knob == 0 || tmap_knob == 1) m.tmap = tmap_knob;
+  else if (most_slab > 1.05 * most_range) m.tmap = 1;
+  else if (most_range > 1.05 * most_slab) m.tmap = 0;
+  else m.tmap = P != F64 && (a.nslots == 1 || P == F16) ? 1 : 0;
   const int nblocks = (m.tmap ? 8 * m.tlen * m.nch : 8 * a.g.T * m.maxc) * (EPI == site_epi(EPI) ? 1 : 2);
   *nparts_out = a.g.T * m.nch;
   if (a.nslots >= 2 && (long)a.g.T * m.nch * a.nslots > slab_max_waves(P)) {
