@@ -374,15 +374,10 @@ __device__ __forceinline__ void dot_add(R& re, R& im, cx<R> a, cx<R> b) {
   im = fmar(-a.y, b.x, fmar(a.x, b.y, im));
 }
 
-// The stored copy of the clover or A^-1 blocks the epilogue uses in LDS:
-// units of 32 bits [72 (FP32) or 36 (FP16)][64], then the FP16 scales [64].
-// FP64 blocks are read from memory (they would not fit beside the links of
-// two workgroups per CU).
-template <int P, int EPI>
-constexpr bool shared_clover() {
-  return EPI == EPI_DIAG && P != F64;
-}
-constexpr int blk_units(int p) { return p == F32 ? 72 : p == F16 ? 36 : 0; }
+// The stored copy of the clover or A^-1 blocks the epilogue uses in LDS: units of
+// 32 bits [72 (FP32) or 36 (FP16)][64], then the FP16 scales [64]; FP64:
+// double2 [36][64].
+constexpr int blk_units(int p) { return p == F64 ? 144 : p == F32 ? 72 : 36; }
 
 // A thread's output site: its index, spatial coordinates and neighbours
 // (2 mu forward, 2 mu + 1 backward).
@@ -496,7 +491,11 @@ struct Epilogue {
       if constexpr (XIN) decode_half<P>(xr, h, xh);
       Blk<P> B;
       if constexpr (EPI == EPI_DIAG || INV) {
-        if constexpr (LDSB && P != F64) {
+        if constexpr (LDSB && P == F64) {
+          const double2* l = reinterpret_cast<const double2*>(lc);
+#pragma unroll
+          for (int k = 0; k < 18; ++k) B.v[k] = l[(18 * h + k) * 64 + lane];
+        } else if constexpr (LDSB) {
           constexpr int n = blk_units(P) / 2;
 #pragma unroll
           for (int k = 0; k < n; ++k)
@@ -726,7 +725,7 @@ __device__ __forceinline__ void slot_work(const HopArgs& a, int slot, const Site
 constexpr int slab_pf(int p) { return p == F64 ? 3 : p == F32 ? 2 : 4; }
 constexpr int slab_min_waves(int p) { return p == F64 ? 1 : 3; }
 constexpr int shared_pf(int p) { return p == F32 ? 3 : 2; }
-constexpr int kSharedThreads = 256;
+constexpr int shared_threads(int p, bool blk) { return p == F64 && blk ? 384 : 256; }
 constexpr int kSharedMinWaves = 2;
 
 // Up to so many waves, one per (chunk, timeslice, slot), several slots run as
@@ -787,18 +786,21 @@ __global__ void __launch_bounds__(64, slab_min_waves(P)) hop_kernel_slab(HopArgs
 }
 
 // Several slots: one workgroup per (chunk, timeslice), its waves take the
-// slots in turn.  The links of the chunk's 64 sites in the 8 hop directions
-// (and the clover blocks of the even-site epilogue, or the A^-1 blocks of the
-// odd-site ones when all slots share one mass: LINV) are loaded once into
-// LDS, as stored, instead of once per slot.  Per-slot arithmetic and
-// reduction partials are those of the one-slot kernel: bitwise the same.
+// slots in turn.  The links of the chunk's 64 sites in the 8 hop directions and,
+// with BLK, the blocks of the epilogue that are the same for every slot (clover
+// blocks of the even sites, A^-1 blocks of the odd ones when all slots share one
+// mass) are loaded once into LDS, as stored, instead of once per slot.  Per-slot
+// arithmetic and reduction partials are those of the one-slot kernel: bitwise
+// the same.  8 waves a CU in two workgroups (FP32, FP16): with 4 or 6 of one
+// workgroup the hops of 12 slots at 48x24^3 take 15-80% longer, with 12 of two or
+// one 2-30%, since the neighbours of what is in flight have to stay in the L2s.
 template <int P>
 constexpr size_t shared_tile_bytes(bool blocks) {
   return 8 * 9 * 64 * sizeof(LinkElem<P>) + (blocks ? (blk_units(P) + (P == F16)) * 64 * sizeof(unsigned) : 0);
 }
 
-template <int P, int EPIL, int RED, bool DAG, bool LINV>
-__global__ void __launch_bounds__(kSharedThreads, kSharedMinWaves) hop_kernel_shared(HopArgs a, SlabMap m) {
+template <int P, int EPIL, int RED, bool DAG, bool BLK>
+__global__ void __launch_bounds__(shared_threads(P, BLK), kSharedMinWaves) hop_kernel_shared(HopArgs a, SlabMap m) {
   constexpr int EPI = site_epi(EPIL);
   using E = LinkElem<P>;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -817,19 +819,26 @@ __global__ void __launch_bounds__(kSharedThreads, kSharedMinWaves) hop_kernel_sh
   if constexpr (EPIL == EPI_FULL_HOST) s.odd = __ballot((a.p + it.x0 + s.x1 + s.x2) & 1);
   // fill: tasks 0..7 are the link directions, task 8 the blocks; wave w takes
   // tasks w, w + nw, ...  Read once per launch: streamed past L2 (2-3%).
-  constexpr bool blocks = (shared_clover<P, EPI>() || LINV) && P != F64;
+  constexpr bool inv = EPI == EPI_INV || EPI == EPI_INV_SUB;
   if (valid) {
 #pragma unroll
     for (int t = 0; t < 9; ++t) {
-      if (t % nw != wv || (t == 8 && !blocks)) continue;
+      if (t % nw != wv || (t == 8 && !BLK)) continue;
       if (t < 8) {
         RawLink<P> u;
         if (t & 1) load_raw_link<P, true>(a.U_in, t >> 1, s.nb[t], g.Vp, u);
         else load_raw_link<P, true>(a.U_out, t >> 1, s.i, g.Vp, u);
 #pragma unroll
         for (int k = 0; k < 9; ++k) lu[(t * 9 + k) * 64 + lane] = u.v[k];
-      } else if constexpr (blocks) {
-        const void* src = LINV ? a.slots.ainv_common : a.clov.data;
+      } else if constexpr (BLK) {
+        const void* src = inv ? a.slots.ainv_common : a.clov.data;
+        if constexpr (P == F64) {
+          const double2* q = static_cast<const double2*>(src);
+          double2* l = reinterpret_cast<double2*>(lc);
+#pragma unroll
+          for (int k = 0; k < 36; ++k) l[k * 64 + lane] = vld<true>(at(scalar_base(q + (long)k * g.Vp), s.i));
+          continue;
+        }
         const uint4* q = static_cast<const uint4*>(src);
 #pragma unroll
         for (int k = 0; k < blk_units(P) / 4; ++k) {
@@ -840,7 +849,7 @@ __global__ void __launch_bounds__(kSharedThreads, kSharedMinWaves) hop_kernel_sh
           lc[(4 * k + 3) * 64 + lane] = v.w;
         }
         if constexpr (P == F16) {
-          const float* sc = LINV ? a.slots.ainv_common_scale : a.clov.scale;
+          const float* sc = inv ? a.slots.ainv_common_scale : a.clov.scale;
           lc[blk_units(P) * 64 + lane] = __builtin_bit_cast(unsigned, vld<true>(at(sc, s.i)));
         }
       }
@@ -854,7 +863,7 @@ __global__ void __launch_bounds__(kSharedThreads, kSharedMinWaves) hop_kernel_sh
     // keeps the compiler from hoisting the LDS reads out of this loop into
     // (many) registers
     asm volatile("" ::: "memory");
-    slot_work<P, EPIL, RED, shared_pf(P), DAG, true, blocks>(a, slot, s, it.x0, valid, part, nparts, lu, lc, lane);
+    slot_work<P, EPIL, RED, shared_pf(P), DAG, true, BLK>(a, slot, s, it.x0, valid, part, nparts, lu, lc, lane);
   }
 }
 
@@ -896,16 +905,28 @@ hipError_t launch_one(const HopArgs& a, hipStream_t st, int* nparts_out) {
   const int nblocks = (m.tmap ? 8 * m.tlen * m.nch : 8 * a.g.T * m.maxc) * (EPI == site_epi(EPI) ? 1 : 2);
   *nparts_out = a.g.T * m.nch;
   if (a.nslots >= 2 && (long)a.g.T * m.nch * a.nslots > slab_max_waves(P)) {
-    // waves per workgroup: the fewest rounds over the slots with at most four waves
-    const int maxw = kSharedThreads / 64, rounds = (a.nslots + maxw - 1) / maxw;
+    constexpr bool inv = EPI == EPI_INV || EPI == EPI_INV_SUB, diag = site_epi(EPI) == EPI_DIAG;
+    // The slots' common blocks in LDS, where there are such.  FP64 blocks fit
+    // beside the links (110 KB) only with one workgroup per CU instead of two,
+    // of six waves: worth it from so many slots on.  Even sites (C), 48x24^3 /
+    // 16^3x32, us without and with: 4 slots 312 / 56.1 and 293 / 58.2, 5: 401 / 73.0
+    // and 357 / 72.8, 8: 548 / 107.7 and 500 / 95.8, 12: 775 / 152.8 and 719 / 137.6;
+    // odd sites (A^-1): 8: 496 / 99.0 and 522 / 94.6, 10: 603 / 121 and 636 / 116, 12:
+    // 703 / 133 and 735 / 130 (588 and 579 within a solve), 24: 1347 / 281 and
+    // 1202 / 250.
+    const bool blk = (diag || (inv && a.slots.ainv_common)) && (P != F64 || a.nslots >= (diag ? 5 : 12));
+    // waves per workgroup: the fewest rounds over the slots
+    const int maxw = shared_threads(P, blk) / 64, rounds = (a.nslots + maxw - 1) / maxw;
     const dim3 grid(nblocks), block(64 * ((a.nslots + rounds - 1) / rounds));
-    constexpr bool inv = EPI == EPI_INV || EPI == EPI_INV_SUB;
-    if (inv && P != F64 && a.slots.ainv_common)
-      hipLaunchKernelGGL((hop_kernel_shared<P, EPI, RED, DAG, inv && P != F64>), grid, block, shared_tile_bytes<P>(true),
-                         st, a, m);
-    else
-      hipLaunchKernelGGL((hop_kernel_shared<P, EPI, RED, DAG, false>), grid, block,
-                         shared_tile_bytes<P>(shared_clover<P, site_epi(EPI)>()), st, a, m);
+    bool done = false;
+    if constexpr (inv || diag)
+      if (blk) {
+        hipLaunchKernelGGL((hop_kernel_shared<P, EPI, RED, DAG, true>), grid, block, shared_tile_bytes<P>(true), st, a, m);
+        done = true;
+      }
+    if constexpr (!diag || P == F64)
+      if (!done)
+        hipLaunchKernelGGL((hop_kernel_shared<P, EPI, RED, DAG, false>), grid, block, shared_tile_bytes<P>(false), st, a, m);
   } else {
     hipLaunchKernelGGL((hop_kernel_slab<P, EPI, RED, DAG>), dim3(nblocks * a.nslots), dim3(64), 0, st, a, m);
   }

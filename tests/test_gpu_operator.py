@@ -275,15 +275,16 @@ def test_schur_inverse_pivots(dims):
         assert e < 2e-11
 
 
-@pytest.mark.parametrize("precision", ["f64", "f32", "f16"])
-def test_shared_tile_matches_one_wave(precision):
-    """A batch above the size up to which every slot has a wave of its own (9 x
-    512 waves) runs the kernels that share a tile's links between the slots:
-    bitwise the one-slot results, full operator (both parities in one launch)
-    and Schur operator, with their adjoints."""
+@pytest.mark.parametrize("precision,nrhs", [("f64", 3), ("f64", 9), ("f64", 13), ("f32", 9), ("f16", 9)])
+def test_shared_tile_matches_one_wave(precision, nrhs):
+    """A batch above the size up to which every slot has a wave of its own (512
+    waves a slot) runs the kernels that share a tile's links between the slots,
+    in FP64 without the blocks of the epilogue (3), with the clover blocks (9)
+    and with both kinds (13): bitwise the one-slot results, full operator (both
+    parities in one launch) and Schur operator, with their adjoints."""
     import torch
-    dims, nrhs = (16, 16, 16, 16), 9
-    log(f"test_shared_tile_matches_one_wave {precision}")
+    dims = (16, 16, 16, 16)
+    log(f"test_shared_tile_matches_one_wave {precision} nrhs={nrhs}")
     U = synth.gauge_su3(dims, 0.3, 32)
     psi = synth.random_spinor(dims, 16, nrhs=nrhs)
     with lattice(dims) as L:
@@ -297,6 +298,6 @@ def test_shared_tile_matches_one_wave(precision):
         for schur in (False, True):
             for dagger in (False, True):
                 L.apply_dev(in_t, out_t, precond=True, dagger=dagger, schur=schur, precision=precision)
-                for k in (0, 3, 8):
+                for k in (0, nrhs // 2, nrhs - 1):
                     L.apply_dev(in_t[k:k + 1], one_t, precond=True, dagger=dagger, schur=schur, precision=precision)
                     assert torch.equal(out_t[k], one_t[0]), (schur, dagger, k)
