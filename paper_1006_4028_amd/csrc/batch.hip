@@ -221,7 +221,7 @@ int inner_iteration(dp_batch* b) {
     DP_TRY(blas(c, w, 0, n, OP_BICG_XR, prec, mi, {&w.x, &w.p, &w.s, &w.r, &w.t, &w.rh}, FIN_BICG_RHO, mi));
   } else {
     DP_TRY(schur(c, w, 0, n, prec, 0, w.p, w.to, w.v, mi, RED_NORM, FIN_CG_ALPHA));
-    DP_TRY(blas(c, w, 0, n, OP_CG_XR, prec, mi, {&w.x, &w.p, &w.r, &w.v}, FIN_RR));
+    DP_TRY(blas(c, w, 0, n, OP_CG_XR, prec, mi, {&w.x, &w.p, &w.r, &w.v}, FIN_DEFER));
     DP_TRY(schur(c, w, 0, n, prec, 1, w.r, w.to, w.s, mi, RED_NORM, FIN_CG_BETA, nullptr, mi));
     DP_TRY(blas(c, w, 0, n, OP_CG_P, prec, mi, {&w.p, &w.s}));
   }

@@ -240,7 +240,12 @@ __global__ void __launch_bounds__(kFinBlock) finalize_kernel(ReduceRef red, int 
   SlotScalars c;
   if (threadIdx.x == 0 && red.fin != FIN_STORE) c = red.sc[slot];
   const double* part = red.partials + (long)slot * kRedMax * nblocks;
-  double acc[kRedMax] = {};
+  double acc[kRedMax] = {}, d[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int q = threadIdx.x + u * nt;
+    d[u] = q < red.deferred ? part[partial_at(nblocks, q, kDeferred)] : 0.0;
+  }
   int b = threadIdx.x;
   for (; b + 3 * nt < nblocks; b += 4 * nt) {
     double q[4][kRedMax];
@@ -257,6 +262,15 @@ __global__ void __launch_bounds__(kFinBlock) finalize_kernel(ReduceRef red, int 
 #pragma unroll
     for (int k = 0; k < kRedMax; ++k)
       if (k < nv) acc[k] += part[partial_at(nblocks, b, k)];
+  // deferred partials: the value after the nv ones
+  double late = 0.0;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) late += d[u];
+  for (b = threadIdx.x + 4 * nt; b < red.deferred; b += nt) late += part[partial_at(nblocks, b, kDeferred)];
+#pragma unroll
+  for (int k = 0; k < kRedMax; ++k)
+    if (k == nv) acc[k] += late;
+  if (red.deferred) nv++;
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = nt >> 6;
   const int v = wave_row_value(lane >> 4);
   double w = wave_sum4(acc[0], acc[1], acc[2], acc[3]);
@@ -329,7 +343,7 @@ hipError_t launch_blas(int op, const BlasArgs& a, hipStream_t st) {
     case F16: e = launch_p<F16>(op, a, grid, st); break;
     default: return hipErrorInvalidValue;
   }
-  if (e != hipSuccess || a.red.fin == FIN_NONE) return e;
+  if (e != hipSuccess || a.red.fin == FIN_NONE || a.red.fin == FIN_DEFER) return e;
   const int nv = op == OP_BICG_INIT                                                              ? 4
                  : op == OP_BICG_XR                                                           ? 3
                  : (op == OP_CG_XR || op == OP_SUB64 || op == OP_NORM || op == OP_BICG_XRP) ? 1

@@ -142,13 +142,18 @@ enum Fin {
   FIN_BICG_RHO = 3,    // sums <rh, r>, |r|^2     -> rho, beta, rr, breakdown
   FIN_BICG_INIT = 4,   // sums |r|^2, <rh, r>, |rh|^2 -> rho, rr, rh2, alpha = omega = 1
   FIN_CG_ALPHA = 5,    // sums |w|^2              -> cg_a = zz / |w|^2
-  FIN_CG_BETA = 6,     // sums |z|^2              -> cg_b = |z|^2 / zz, zz
+  FIN_CG_BETA = 6,     // sums |z|^2, |r|^2       -> cg_b = |z|^2 / zz, zz, rr, end of the iteration
   FIN_CG_INIT = 7,     // sums |z|^2              -> zz
-  FIN_RR = 8,          // sums |r|^2              -> rr
+  FIN_DEFER = 8,       // the partials stay, at value kDeferred of the next hop's layout, for its fold
   FIN_STORE = 9,       // raw sums                -> out_sums[slot][k]
   FIN_BICG_OMEGA_RHO = 10,  // sums <t,s>, |t|^2, <rh,s>, <rh,t> -> omega, rho = <rh, s - omega t>, beta
   FIN_BICG_RR = 11,         // sums |r|^2             -> rr, breakdown test, end of the iteration
 };
+
+// Value index of partials left for a later fold (free in RED_NORM hops, whose
+// fold takes them: one launch fewer an iteration of CG; folds 21 -> 17 us an
+// iteration with 16384 and 4096 partials, 13 -> 9 with 64).
+constexpr int kDeferred = 4;
 
 struct ReduceRef {
   int red = RED_NONE;
@@ -158,6 +163,8 @@ struct ReduceRef {
   SlotScalars* sc = nullptr;    // [nslots]
   double* out_sums = nullptr;   // FIN_STORE: [nslots][4]
   int* inner_mask = nullptr;    // [nslots] cleared when a slot leaves the inner solve
+  int layout = 0;               // FIN_DEFER: the number of partials of the fold that takes them
+  int deferred = 0;             // the fold's number of partials at kDeferred
 };
 
 struct HopArgs {
@@ -293,6 +300,8 @@ hipError_t launch_finalize(const ReduceRef& red, int nv, int nblocks, int nslots
 // (hop_blocks) use for a given geometry, to size the partials buffer.
 int reduction_blocks(const Geom& g);
 int hop_blocks(const Geom& g);
+// partials of a hop kernel per slot: one per 64-site chunk of a timeslice
+int hop_parts(const Geom& g);
 constexpr int kBlock = 256;
 
 }  // namespace dp

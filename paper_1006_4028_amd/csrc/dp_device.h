@@ -732,15 +732,13 @@ __device__ inline void run_finaliser(const ReduceRef& red, int slot, const doubl
     case FIN_CG_BETA:
       c.cg_b = c.zz > 0.0 ? s[0] / c.zz : 0.0;
       c.zz = s[0];
+      c.rr = s[1];
       end_of_iteration(red, slot, c);
       break;
     case FIN_CG_INIT:
       c.zz = s[0];
       c.breakdown = 0;
       c.left = 0;
-      break;
-    case FIN_RR:
-      c.rr = s[0];
       break;
     default:
       break;
@@ -762,12 +760,14 @@ __device__ inline void block_reduce_store(const ReduceRef& red, int nv, double (
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    double* part = red.partials + (long)slot * kRedMax * nblocks;
+    const bool defer = red.fin == FIN_DEFER;
+    const int n = defer ? red.layout : nblocks;
+    double* part = red.partials + (long)slot * kRedMax * n;
     const int nw = blockDim.x >> 6;  // blocks of 64 or kBlock threads
     for (int k = 0; k < nv; ++k) {
       double t = 0.0;
       for (int w = 0; w < nw; ++w) t += lds[k][w];
-      part[partial_at(nblocks, block, k)] = t;
+      part[partial_at(n, block, defer ? kDeferred + k : k)] = t;
     }
   }
   __syncthreads();

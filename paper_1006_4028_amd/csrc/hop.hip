@@ -11,10 +11,9 @@ hipError_t launch_hop_f16(const HopArgs& a, hipStream_t st, int* nparts);
 
 int reduction_blocks(const Geom& g) { return (g.Vh + kBlock - 1) / kBlock; }
 
-int hop_blocks(const Geom& g) {
-  const int nch = (g.Vsh + 63) / 64;
-  return std::max(reduction_blocks(g), g.T * nch);
-}
+int hop_parts(const Geom& g) { return g.T * ((g.Vsh + 63) / 64); }
+
+int hop_blocks(const Geom& g) { return std::max(reduction_blocks(g), hop_parts(g)); }
 
 hipError_t launch_hop(const HopArgs& a, hipStream_t st, int* nparts) {
   *nparts = 0;

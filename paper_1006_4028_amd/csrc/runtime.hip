@@ -408,6 +408,7 @@ int hop(dp_ctx* c, Workspace& w, int s0, int n, int prec, int p, int dag, int ep
   if (epi == EPI_INV || epi == EPI_INV_SUB) a.slots.ainv_common = common_ainv(w, s0, n, prec, &a.slots.ainv_common_scale);
   a.sratio = w.sratio;
   a.red = reduce_ref(w, s0, red, fin, inner_mask);
+  if (fin == FIN_CG_BETA) a.red.deferred = reduction_blocks(c->g);
   if (wv) a.red.w = wv->ref(s0);
   a.nslots = n;
   hipEvent_t ev = nullptr;
@@ -498,6 +499,7 @@ int blas(dp_ctx* c, Workspace& w, int s0, int n, int op, int prec, const int* ma
     ++k;
   }
   a.red = reduce_ref(w, s0, RED_NONE, fin, inner_mask);
+  a.red.layout = hop_parts(c->g);
   hipEvent_t ev = nullptr;
   DP_TRY(timing_begin(c, &ev));
   DP_HIP(c, launch_blas(op, a, c->stream));
