@@ -131,7 +131,14 @@ __device__ __forceinline__ void load_block(const double2* src, int Vh, int i, in
 __global__ void __launch_bounds__(128) clover_build_kernel(Geom g, const double2* Ue, const double2* Uo, double csw,
                                                            double2* Ce, double2* Co) {
   const long V = 2L * g.Vh;
-  const long s = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  // The kernel is bound by the links it fetches past the L2s (0.98 GB of 0.1 at
+  // 36x18x20x14 when neighbouring workgroups ran on different XCDs).  An XCD
+  // takes a contiguous range of sites where that keeps a timeslice's worth of
+  // links (576 B a site) near its 4 MB L2: 207 -> 181 us at 36x18x20x14 (2.9 MB a
+  // timeslice), 765 -> 677 at 48x24^3 (8 MB), but 1908 -> 2118 at 64x32^3 (19 MB).
+  const bool ranges = 2 * g.Vsh * 576L <= (8L << 20);
+  const int tile = ranges ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+  const long s = (long)tile * blockDim.x + threadIdx.x;
   if (s >= V) return;
   const double2* U[2] = {Ue, Uo};
   Site x;
