@@ -36,9 +36,10 @@
  *    throws; dp_last_error() gives a message for the last failure on a ctx.
  *  - Host buffers passed in are read (or written) before the call returns;
  *    the caller keeps ownership.  Device pointers (the *_dev variants) must be
- *    device memory of the ctx's GPU in the same host layout; the library
- *    enqueues its work on the given HIP stream (NULL: the ctx's own stream)
- *    and returns when the results are complete.
+ *    device memory of the ctx's GPU in the same host layout; the library waits
+ *    for the work queued on the given HIP stream (NULL: the device's default
+ *    stream), works on the ctx's own stream and returns when the results are
+ *    complete.
  *  - A ctx owns all device memory it allocates (gauge field, clover blocks,
  *    per-mass inverses, solver work space) until dp_destroy.
  *  - One host thread at a time per ctx.
@@ -212,7 +213,7 @@ int dp_apply(dp_ctx* ctx, const double* in, double* out, int flags);
  * full-lattice spinors, complex128): the same flags and operator, each
  * right-hand side a slot of the multi-RHS kernels (the links are read once per
  * launch for all of them).  in and out must not overlap.  Work already queued
- * on hip_stream (nullable) completes first; the call returns when out is
+ * on hip_stream (NULL: the default stream) completes first; the call returns when out is
  * written.  The library's launch timing (dp_set_timing) covers these kernels,
  * which makes this the operator benchmark. */
 int dp_apply_dev(dp_ctx* ctx, const void* in_dev, void* out_dev, int nrhs, int flags, void* hip_stream);
@@ -265,8 +266,8 @@ int dp_solve_sap(dp_ctx* ctx, const double* eta, const dp_sap_params* p, double*
 /* Paper: as dp_solve_sap (Table 1 and the solver it cites).
  * Same with eta and S in device memory (host layout, V x 12 complex doubles;
  * S nullable; they must not overlap, else DP_ERR_INVALID_ARG); cpp and info
- * on the host.  The library first waits for hip_stream (nullable), then works
- * on its own stream and returns when S and cpp are complete. */
+ * on the host.  The library first waits for hip_stream (NULL: the default
+ * stream), then works on its own stream and returns when S and cpp are complete. */
 int dp_solve_sap_dev(dp_ctx* ctx, const void* eta_dev, const dp_sap_params* p, void* S_dev, double* cpp,
                      dp_info* info, void* hip_stream);
 
@@ -316,7 +317,7 @@ int dp_get_timing_samples(dp_ctx* ctx, const char* name, float* ms, int max, int
  * in spin-colour component c0 + j (c = 3*spin + colour) at site = {x0, x1,
  * x2, x3} and 0 everywhere else.  Requires 0 <= c0, ncols >= 1, c0 + ncols
  * <= 12 and the site inside the lattice, else DP_ERR_INVALID_ARG.  Work queued
- * on hip_stream (nullable) completes first; returns when eta_dev is written.
+ * on hip_stream (NULL: the default stream) completes first; returns when eta_dev is written.
  * The caller owns eta_dev. */
 int dp_point_sources(dp_ctx* ctx, const int site[4], int c0, int ncols, void* eta_dev, void* hip_stream);
 
@@ -384,7 +385,8 @@ void dp_batch_close(dp_batch* b);
  * x0_src and a caller tag.  S_dev (nullable, device, host layout, ncols
  * spinors) receives the restored solutions when they finish.  slots_out
  * (nullable) receives the ncols slot indices.  DP_ERR_FULL when fewer than
- * ncols slots are free.  The sources are read before the call returns. */
+ * ncols slots are free.  The sources must be complete (the call waits for no
+ * stream of the caller's) and are read before the call returns. */
 int dp_batch_admit(dp_batch* b, int ncols, const void* eta_dev, void* S_dev, double M, const double* alpha, double r,
                    int max_iter, double delta, int x0_src, long long tag, int* slots_out);
 /* Run k inner iterations for the running slots and the outer steps that

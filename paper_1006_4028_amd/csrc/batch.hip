@@ -682,7 +682,7 @@ int dp_solve_dev(dp_ctx* c, const void* eta, int nrhs, const dp_params* p, void*
   const char* e0 = static_cast<const char*>(eta);
   const char* s0 = static_cast<const char*>(S);
   if (S && e0 < s0 + bytes && s0 < e0 + bytes) return fail(c, DP_ERR_INVALID_ARG, "eta and S overlap");
-  if (stream) DP_HIP(c, hipStreamSynchronize((hipStream_t)stream));
+  DP_TRY(wait_caller(c, stream));
   return solve_common(c, static_cast<const double2*>(eta), nrhs, *p, static_cast<double2*>(S), cpp, info);
 }
 

@@ -267,6 +267,11 @@ int mass_entry(dp_ctx* c, double M, MassEntry** out);
 inline size_t slot_record_bytes(int T, int n) { return sizeof(double) * (5 * T + 6) + sizeof(int) * n; }
 int ensure_ws(dp_ctx* c, Workspace& w, int nslots, int prec);
 int h2d(dp_ctx* c, void* dst, const void* src, size_t bytes);
+// Waits for the work queued on the caller's stream (null: the device's default
+// stream, which is what torch calls its default stream too): the ctx's stream
+// does not wait for any other by itself, and a caller's buffer may still be
+// written, or read by the work its memory was last used for.
+int wait_caller(dp_ctx* c, void* stream);
 int upload_mask(dp_ctx* c, Workspace& w, DevBuf& dst, const std::vector<int>& m, int staging);
 int timing_harvest(dp_ctx* c);
 // spatial tables of the light-quark factorisation (see dp_ctx::space)

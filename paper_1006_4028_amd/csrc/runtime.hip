@@ -252,6 +252,20 @@ int h2d(dp_ctx* c, void* dst, const void* src, size_t bytes) {
   return DP_OK;
 }
 
+int wait_caller(dp_ctx* c, void* stream) {
+  if (!stream) {
+    // not while a stream that synchronises with the default one is being
+    // captured: the wait would end that capture
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(nullptr, &st) != hipSuccess) {
+      (void)hipGetLastError();
+      return DP_OK;
+    }
+  }
+  DP_HIP(c, hipStreamSynchronize(static_cast<hipStream_t>(stream)));
+  return DP_OK;
+}
+
 // Upload a host mask through its own pinned staging row; each row is only
 // rewritten after a later stream synchronisation.
 int upload_mask(dp_ctx* c, Workspace& w, DevBuf& dst, const std::vector<int>& m, int staging) {
@@ -725,7 +739,7 @@ int dp_set_gauge(dp_ctx* c, const double* U) {
 int dp_set_gauge_dev(dp_ctx* c, const void* U, void* stream) {
   if (!c || !U) return fail(c, DP_ERR_INVALID_ARG, "null argument");
   DP_HIP(c, hipSetDevice(c->device));
-  if (stream) DP_HIP(c, hipStreamSynchronize((hipStream_t)stream));
+  DP_TRY(wait_caller(c, stream));
   return set_gauge_common(c, static_cast<const double2*>(U), c->stream);
 }
 
@@ -756,7 +770,7 @@ int dp_sf_wall_sources(dp_ctx* c, int side, int c0, int ncols, void* eta, void* 
   if (c0 < 0 || ncols < 1 || c0 + ncols > 12) return fail(c, DP_ERR_INVALID_ARG, "need 0 <= c0 and c0 + ncols <= 12");
   if (!c->sf) return fail(c, DP_ERR_BAD_STATE, "no Schroedinger-functional links set (dp_set_gauge_sf)");
   DP_HIP(c, hipSetDevice(c->device));
-  if (stream) DP_HIP(c, hipStreamSynchronize((hipStream_t)stream));
+  DP_TRY(wait_caller(c, stream));
   // the padded timeslice next to the boundary: x0 = 0 or x0 = T
   const size_t per_t = (size_t)2 * c->g.Vsh * 4 * 9;
   const double2* Ut = c->sf_ext.as<double2>() + (side == 0 ? 0 : per_t * c->g.T);
@@ -1081,7 +1095,7 @@ int dp_apply_dev_noalloc(dp_ctx* c, const void* in, void* out, int nrhs, int fla
     return fail(c, DP_ERR_BAD_STATE,
                 "the inverse clover of the current mass is not built: call dp_apply_dev (or a solve) with this "
                 "mass once before");
-  if (stream) DP_HIP(c, hipStreamSynchronize((hipStream_t)stream));
+  DP_TRY(wait_caller(c, stream));
   // views into the scratch
   Workspace& w = c->ws_noalloc;
   char* base = static_cast<char*>(c->scratch_dev);
@@ -1179,7 +1193,7 @@ int dp_apply_dev(dp_ctx* c, const void* in, void* out, int nrhs, int flags, void
   if (a < b + bytes && b < a + bytes) return fail(c, DP_ERR_INVALID_ARG, "in and out overlap");
   DP_HIP(c, hipSetDevice(c->device));
   DP_TRY(check_state(c));
-  if (stream) DP_HIP(c, hipStreamSynchronize((hipStream_t)stream));
+  DP_TRY(wait_caller(c, stream));
   DP_TRY(apply_core(c, static_cast<const double2*>(in), static_cast<double2*>(out), nrhs, flags));
   DP_HIP(c, hipStreamSynchronize(c->stream));
   DP_TRY(timing_harvest(c));
@@ -1205,7 +1219,7 @@ int dp_apply_dev_slots(dp_ctx* c, const void* in, void* out, int nrhs, int flags
   if (a < b + bytes && b < a + bytes) return fail(c, DP_ERR_INVALID_ARG, "in and out overlap");
   DP_HIP(c, hipSetDevice(c->device));
   DP_TRY(check_state(c));
-  if (stream) DP_HIP(c, hipStreamSynchronize((hipStream_t)stream));
+  DP_TRY(wait_caller(c, stream));
   DP_TRY(apply_core(c, static_cast<const double2*>(in), static_cast<double2*>(out), nrhs, flags, M, alpha));
   DP_HIP(c, hipStreamSynchronize(c->stream));
   DP_TRY(timing_harvest(c));
@@ -1218,7 +1232,7 @@ int dp_point_sources(dp_ctx* c, const int site[4], int c0, int ncols, void* eta,
   for (int k = 0; k < 4; ++k)
     if (site[k] < 0 || site[k] >= c->dims[k]) return fail(c, DP_ERR_INVALID_ARG, "site outside the lattice");
   DP_HIP(c, hipSetDevice(c->device));
-  if (stream) DP_HIP(c, hipStreamSynchronize((hipStream_t)stream));
+  DP_TRY(wait_caller(c, stream));
   DP_HIP(c, launch_point_sources(c->g, site, c0, ncols, static_cast<double2*>(eta), c->stream));
   DP_HIP(c, hipStreamSynchronize(c->stream));
   return DP_OK;

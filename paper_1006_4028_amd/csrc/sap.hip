@@ -1740,7 +1740,7 @@ extern "C" int dp_solve_sap_dev(dp_ctx* c, const void* eta_dev, const dp_sap_par
   const char* s0 = static_cast<const char*>(S_dev);
   if (S_dev && e0 < s0 + bytes && s0 < e0 + bytes) return fail(c, DP_ERR_INVALID_ARG, "eta and S overlap");
   DP_HIP(c, hipSetDevice(c->device));
-  if (hip_stream) DP_HIP(c, hipStreamSynchronize((hipStream_t)hip_stream));
+  DP_TRY(wait_caller(c, hip_stream));
   Blocking b;
   DP_TRY(sap_prepare(c, p, p->nkv, &b));
   const double t0 = now_s();
