@@ -41,7 +41,11 @@
  *    stream), works on the ctx's own stream and returns when the results are
  *    complete.
  *  - A ctx owns all device memory it allocates (gauge field, clover blocks,
- *    per-mass inverses, solver work space) until dp_destroy.
+ *    per-mass inverses, solver work space) until dp_destroy.  The buffers of
+ *    inverses that new links or a new clover term drop are kept for the next
+ *    ones: at most four and 1 GiB per ctx; those that a configuration leaves over
+ *    are freed at the next, and all of them when an allocation of the library
+ *    fails.
  *  - One host thread at a time per ctx.
  */
 #ifndef DP_H
@@ -401,7 +405,8 @@ long long dp_batch_device_bytes(const dp_batch* b);
 /* Admission gate of a server (no passage of the paper).
  * Device bytes a context would hold for the gauge field and clover of a
  * lattice, plus the solver work space for nrhs right-hand sides at the given
- * precision, plus one per-mass inverse per new mass. */
+ * precision, plus one per-mass inverse per new mass (buffers kept from an
+ * earlier configuration's inverses are taken up by the new ones first). */
 long long dp_footprint_bytes(const int dims[4], int nrhs, int precision, int new_masses);
 
 #ifdef __cplusplus

@@ -144,11 +144,6 @@ struct dp_ctx {
   double ct_tilde = 1.0;
   dp::DevBuf sf_ext;
   std::vector<dp::MassEntry*> masses;
-  // buffers of dropped inverses, taken up again by the next masses (all
-  // entries of a ctx have the same sizes): at most kMassPool, given back when
-  // an allocation fails and with the ctx
-  static constexpr size_t kMassPool = 4;
-  std::vector<dp::MassEntry*> mass_pool;
   int open_batches = 0;
 
   double M = 0.0;
@@ -254,8 +249,8 @@ struct TraceRange {
 };
 
 bool env_pad();
-// DevBuf::reserve and Field::alloc; a failure gives the ctx's pooled buffers
-// back and tries again
+// DevBuf::reserve and Field::alloc; a failure gives the buffers kept from
+// dropped inverses back (those of every ctx on the GPU) and tries again
 hipError_t reserve(dp_ctx* c, DevBuf& b, size_t bytes);
 hipError_t alloc(dp_ctx* c, Field& f, int prec, int nslots);
 double now_s();

@@ -10,9 +10,11 @@
 #include <cstdio>
 #include <cstring>
 #include <cstdlib>
+#include <iterator>
 #include <map>
 #include <mutex>
 #include <new>
+#include <utility>
 
 #include "runtime.h"
 
@@ -74,24 +76,104 @@ bool env_pad() {
   return v;
 }
 
+// ------------------------------------------------- buffers of dropped inverses
+//
+// A new configuration drops the inverses of the old one and builds as many
+// again.  Their buffers (all of a ctx have the same sizes) wait here for that
+// in between: a new configuration takes 1.83 ms at 48x24^3 with one mass and 2.44
+// with two, 2.57 and 4.1 when they are freed and allocated.  What is kept is
+// bounded per ctx (kKeptEntries inverses and kKeptBytes, 0.4% of the card's
+// memory: one inverse at 64x32^3); what a configuration leaves over is freed
+// at the next one; and all of it goes back when an allocation of any ctx on the
+// GPU fails.  The list is shared by the ctxs of the process for that alone: a ctx
+// takes only its own entries, whose last use came before on its own stream.
 namespace {
-template <class F>
-hipError_t with_pool_released(dp_ctx* c, F f) {
-  hipError_t e = f();
-  if (e != hipErrorOutOfMemory || c->mass_pool.empty()) return e;
-  (void)hipGetLastError();
-  for (auto* m : c->mass_pool) delete m;
-  c->mass_pool.clear();
-  return f();
+
+constexpr size_t kKeptEntries = 4;
+constexpr size_t kKeptBytes = (size_t)1 << 30;
+
+struct KeptInverses {
+  std::mutex mu;
+  std::vector<std::pair<dp_ctx*, MassEntry*>> v;
+};
+// never destroyed: a ctx may be destroyed after the static objects
+KeptInverses& kept() {
+  static KeptInverses* k = new KeptInverses;
+  return *k;
 }
+
+size_t inverse_bytes(const MassEntry& m) { return m.a64.bytes + m.a32.bytes + m.a16.bytes + m.s16.bytes; }
+
+// a kept entry of the ctx, or null
+MassEntry* take_inverse(dp_ctx* c) {
+  KeptInverses& k = kept();
+  std::lock_guard<std::mutex> lock(k.mu);
+  for (auto it = k.v.rbegin(); it != k.v.rend(); ++it)
+    if (it->first == c) {
+      MassEntry* m = it->second;
+      k.v.erase(std::next(it).base());
+      return m;
+    }
+  return nullptr;
+}
+
+// frees the kept entries for which f(ctx) holds (hipFree waits for work that
+// still uses them)
+template <class F>
+bool free_inverses(F f) {
+  KeptInverses& k = kept();
+  std::lock_guard<std::mutex> lock(k.mu);
+  const auto cut = std::partition(k.v.begin(), k.v.end(), [&](const auto& e) { return !f(e.first); });
+  const bool any = cut != k.v.end();
+  for (auto it = cut; it != k.v.end(); ++it) delete it->second;
+  k.v.erase(cut, k.v.end());
+  return any;
+}
+
+// the ctx's current inverses, as far as the bounds allow, in place of what it
+// had kept before; the others are freed
+void keep_inverses(dp_ctx* c) {
+  if (c->masses.empty()) return;  // links and clover of one configuration: the second call drops nothing
+  free_inverses([c](const dp_ctx* q) { return q == c; });
+  KeptInverses& k = kept();
+  size_t n = 0, bytes = 0;
+  for (MassEntry* m : c->masses) {
+    const size_t b = inverse_bytes(*m);
+    bool keep = n < kKeptEntries && bytes + b <= kKeptBytes;
+    if (keep) {
+      std::lock_guard<std::mutex> lock(k.mu);
+      try {
+        k.v.emplace_back(c, m);
+      } catch (const std::bad_alloc&) {
+        keep = false;
+      }
+    }
+    if (keep) {
+      ++n;
+      bytes += b;
+    } else {
+      delete m;
+    }
+  }
+  c->masses.clear();
+}
+
+template <class F>
+hipError_t with_inverses_freed(dp_ctx* c, F f) {
+  hipError_t e = f();
+  if (e != hipErrorOutOfMemory) return e;
+  (void)hipGetLastError();
+  return free_inverses([c](const dp_ctx* q) { return q->device == c->device; }) ? f() : e;
+}
+
 }  // namespace
 
 hipError_t reserve(dp_ctx* c, DevBuf& b, size_t bytes) {
-  return with_pool_released(c, [&] { return b.reserve(bytes); });
+  return with_inverses_freed(c, [&] { return b.reserve(bytes); });
 }
 
 hipError_t alloc(dp_ctx* c, Field& f, int prec, int nslots) {
-  return with_pool_released(c, [&] { return f.alloc(c->g, prec, nslots); });
+  return with_inverses_freed(c, [&] { return f.alloc(c->g, prec, nslots); });
 }
 
 double now_s() {
@@ -141,7 +223,7 @@ int upload_space(dp_ctx* c, const double* const a[3]) {
     off += 4 * L;
     poff += L;
   }
-  DP_HIP(c, c->space.reserve(sizeof(double) * h.size()));
+  DP_HIP(c, reserve(c, c->space, sizeof(double) * h.size()));
   DP_TRY(h2d(c, c->space.p, h.data(), sizeof(double) * h.size()));
   c->has_space = a[0] || a[1] || a[2];
   return DP_OK;
@@ -167,24 +249,19 @@ int mass_entry(dp_ctx* c, double M, MassEntry** out) {
       return DP_OK;
     }
   const Geom& g = c->g;
-  MassEntry* m = nullptr;
-  if (!c->mass_pool.empty()) {
-    m = c->mass_pool.back();
-    c->mass_pool.pop_back();
-  } else {
-    m = new (std::nothrow) MassEntry;
-  }
+  MassEntry* m = take_inverse(c);
+  if (!m) m = new (std::nothrow) MassEntry;
   if (!m) return fail(c, DP_ERR_OOM, "host allocation failed");
   m->M = M;
-  hipError_t e = m->a64.reserve((size_t)g.Vp * clover_site_bytes(F64));
-  if (e == hipSuccess) e = m->a32.reserve((size_t)g.Vp * clover_site_bytes(F32));
-  if (e == hipSuccess) e = m->a16.reserve((size_t)g.Vp * clover_site_bytes(F16));
-  if (e == hipSuccess) e = m->s16.reserve((size_t)g.Vp * sizeof(float));
+  hipError_t e = reserve(c, m->a64, (size_t)g.Vp * clover_site_bytes(F64));
+  if (e == hipSuccess) e = reserve(c, m->a32, (size_t)g.Vp * clover_site_bytes(F32));
+  if (e == hipSuccess) e = reserve(c, m->a16, (size_t)g.Vp * clover_site_bytes(F16));
+  if (e == hipSuccess) e = reserve(c, m->s16, (size_t)g.Vp * sizeof(float));
   if (e != hipSuccess) {
     delete m;
     return fail(c, DP_ERR_OOM, "out of device memory for the inverse clover");
   }
-  DP_HIP(c, c->bad_flag.reserve(sizeof(int)));
+  DP_HIP(c, reserve(c, c->bad_flag, sizeof(int)));
   DP_HIP(c, hipMemsetAsync(c->bad_flag.p, 0, sizeof(int), c->stream));
   DP_HIP(c, launch_clover_invert(g, c->C64[1].as<double2>(), 4.0 + M, m->a64.as<double2>(), m->a32.p, m->a16.p,
                                  m->s16.as<float>(), c->bad_flag.as<int>(), c->stream));
@@ -547,7 +624,7 @@ dp_ctx::~dp_ctx() {
   }
   for (auto e : ev_free) (void)hipEventDestroy(e);
   for (auto* m : masses) delete m;
-  for (auto* m : mass_pool) delete m;
+  dp::rt::free_inverses([this](const dp_ctx* q) { return q == this; });
   dp::sap_free(sap);
   if (stream) (void)hipStreamDestroy(stream);
 }
@@ -566,11 +643,7 @@ int drop_masses(dp_ctx* c) {
     c->solve_batch = nullptr;
   }
   if (c->open_batches > 0) return fail(c, DP_ERR_BAD_STATE, "a batch is open on this context");
-  for (auto* m : c->masses) {
-    if (c->mass_pool.size() < dp_ctx::kMassPool) c->mass_pool.push_back(m);
-    else delete m;
-  }
-  c->masses.clear();
+  keep_inverses(c);
   c->apply_key.clear();
   return DP_OK;
 }

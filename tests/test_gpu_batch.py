@@ -203,3 +203,43 @@ def test_new_configurations_on_one_context():
                     F.set_alpha(alpha)
                     F.apply_dev(psi, ref, precond=True, schur=True, precision="f16" if M > 0.25 else "f32")
                 assert torch.equal(out, ref), (seed, M)
+
+
+def test_dropped_inverses_held_memory_is_bounded():
+    """What a context holds of dropped inverses: at most 1 GiB, nothing that a
+    whole configuration left unused, nothing once it is closed (530 MB an
+    inverse here; 64 MB are allowed for what the allocator rounds up)."""
+    import torch
+    dims = (32, 32, 32, 32)
+    log("test_dropped_inverses_held_memory_is_bounded")
+    slack = 64 << 20
+    one = dims[0] * dims[1] * dims[2] * dims[3] // 2 * 1012
+
+    def free():
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0]
+
+    x = torch.zeros((1, 12 * 32 ** 4), dtype=torch.complex128, device="cuda")
+    y = torch.empty_like(x)
+    with lattice((4, 4, 4, 4)):  # the library's static scratch is on the device from here on
+        before = free()
+    with lattice(dims) as L:
+        def configuration(masses):
+            L.set_clover(0.0)
+            for M in masses:
+                L.set_mass(M)
+                L.apply_dev(x, y, precision="f32")
+            return free()
+
+        work = configuration([0.1]) + one  # free beside the workspace and no inverse
+        assert configuration([0.1, 0.2, 0.3, 0.4]) <= work - 4 * one + slack
+        L.set_clover(0.0)  # drops the four
+        held = work - free()
+        log(f"  held after the drop: {held / 2 ** 20:.0f} MiB")
+        assert held <= (1 << 30) + slack
+        assert configuration([0.5]) >= work - 2 * one - slack  # a kept one taken up, none allocated
+        L.set_clover(0.0)  # what the last configuration left over goes back too
+        held = work - free()
+        log(f"  held after a configuration of one mass: {held / 2 ** 20:.0f} MiB")
+        assert held <= one + slack
+    assert free() >= before - slack
