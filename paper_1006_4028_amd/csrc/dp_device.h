@@ -30,27 +30,38 @@ template <typename R>
 __device__ __forceinline__ cx<R> ti(cx<R> a) { return {-a.y, a.x}; }
 __device__ __forceinline__ float fmar(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fmar(double a, double b, double c) { return __builtin_fma(a, b, c); }
-// a += b * c.  FP32: two fused multiply-adds a component, written out (the
-// compiler's contraction within an expression takes three instructions: it
-// cannot fuse across the two products).  FP64: the pair of products is formed
-// first, three instructions with one rounding less at the magnitude of a (the
-// FP64 kernels wait for memory, not for instructions).
+// a += b * c, the pair of products formed first: three instructions a
+// component and one rounding at the magnitude of a.
 template <typename R>
 __device__ __forceinline__ void cfma(cx<R>& a, cx<R> b, cx<R> c) {
+  a.x += b.x * c.x - b.y * c.y;
+  a.y += b.x * c.y + b.y * c.x;
+}
+// a += conj(b) * c
+template <typename R>
+__device__ __forceinline__ void cjfma(cx<R>& a, cx<R> b, cx<R> c) {
+  a.x += b.x * c.x + b.y * c.y;
+  a.y += b.x * c.y - b.y * c.x;
+}
+// The same in FP32 by two fused multiply-adds a component (the compiler's
+// contraction within an expression cannot fuse across the two products), with
+// two roundings at the magnitude of a: for sums that stay below the result
+// they end in (the off-diagonal part of a block), or where the kernel is bound
+// by instructions and its error does not grow by it.  FP64 kernels wait for
+// memory: as above.
+template <typename R>
+__device__ __forceinline__ void cfma2(cx<R>& a, cx<R> b, cx<R> c) {
   if constexpr (sizeof(R) == 8) {
-    a.x += b.x * c.x - b.y * c.y;
-    a.y += b.x * c.y + b.y * c.x;
+    cfma(a, b, c);
   } else {
     a.x = fmar(-b.y, c.y, fmar(b.x, c.x, a.x));
     a.y = fmar(b.y, c.x, fmar(b.x, c.y, a.y));
   }
 }
-// a += conj(b) * c
 template <typename R>
-__device__ __forceinline__ void cjfma(cx<R>& a, cx<R> b, cx<R> c) {
+__device__ __forceinline__ void cjfma2(cx<R>& a, cx<R> b, cx<R> c) {
   if constexpr (sizeof(R) == 8) {
-    a.x += b.x * c.x + b.y * c.y;
-    a.y += b.x * c.y - b.y * c.x;
+    cjfma(a, b, c);
   } else {
     a.x = fmar(b.y, c.y, fmar(b.x, c.x, a.x));
     a.y = fmar(-b.y, c.x, fmar(b.x, c.y, a.y));
@@ -548,8 +559,8 @@ __device__ __forceinline__ void herm_apply(const HermBlock<R>& B, R shift, const
 #pragma unroll
     for (int c = r + 1; c < 6; ++c) {
       const cx<R> a = B.o[herm_off(r, c)];
-      if (r > 0 || c > 1) cfma(y[r], a, x[c]);  // A_rc x_c
-      if (r > 0) cjfma(y[c], a, x[r]);          // A_cr = conj(A_rc)
+      if (r > 0 || c > 1) cfma2(y[r], a, x[c]);  // A_rc x_c
+      if (r > 0) cjfma2(y[c], a, x[r]);          // A_cr = conj(A_rc)
     }
 #pragma unroll
   for (int r = 0; r < 6; ++r) rfma(y[r], B.d[r] + shift, x[r]);

@@ -25,7 +25,8 @@
 // One thread per output site and right-hand side ("slot").  What bounds the
 // kernels: with one slot the traffic of links and blocks; with many slots the
 // traffic of the spinors past L2 (FP64, FP32) or the instructions (FP16).
-// FP32 multiply-adds are therefore fused ones, written out; FP16 values enter
+// Multiply-adds are therefore fused ones, written out (FP32 link products but
+// for one pair, see lfma); FP16 values enter
 // the arithmetic through mixed-precision multiply-adds, which convert for
 // free; the slot and with it every base address is a scalar; links and blocks
 // stay in LDS as stored.  24^3x48, 12 slots, in the solve, odd / even sites with
@@ -138,7 +139,10 @@ __device__ __forceinline__ cx<double> elem(double2 v) { return {v.x, v.y}; }
 __device__ __forceinline__ cx<float> elem(float2 v) { return {v.x, v.y}; }
 __device__ __forceinline__ h2v elem(unsigned v) { return as_h2(v); }
 
-// t = u h, t += u h (CONJ: conj(u) h), u a stored link entry
+// t = u h, t += u h (CONJ: conj(u) h), u a stored link entry.  FP32 pairs the
+// products: with two fused multiply-adds a component the hop's error against
+// FP64 was 8.5e-8 of the result, 8.2e-8 with the pairs, at the same times (12
+// columns at 48x24^3: 87.1 ms a solve either way).
 template <bool CONJ, typename R>
 __device__ __forceinline__ cx<R> lmul(cx<R> u, cx<R> h) { return CONJ ? cjmul(u, h) : cmul(u, h); }
 template <bool CONJ, typename R>
@@ -157,6 +161,14 @@ __device__ __forceinline__ cx<float> lmul(h2v u, cx<float> h) {
   cx<float> t{0.f, 0.f};
   lfma<CONJ>(t, u, h);
   return t;
+}
+
+// the same for an entry u of a clover or A^-1 block (see cfma2)
+template <bool CONJ, typename U, typename R>
+__device__ __forceinline__ void bfma(cx<R>& t, U u, cx<R> h) {
+  if constexpr (!std::is_same<U, cx<R>>::value) lfma<CONJ>(t, u, h);
+  else if constexpr (CONJ) cjfma2(t, u, h);
+  else cfma2(t, u, h);
 }
 
 // ------------------------------------------------------------ neighbours
@@ -322,8 +334,8 @@ __device__ __forceinline__ void blk_apply(const Blk<P>& B, R shift, const cx<R>*
   for (int r = 0; r < 6; ++r)
 #pragma unroll
     for (int c = r + 1; c < 6; ++c) {
-      if (r > 0 || c > 1) lfma<false>(y[r], B.o(herm_off(r, c)), x[c]);  // A_rc x_c
-      if (r > 0) lfma<true>(y[c], B.o(herm_off(r, c)), x[r]);            // A_cr = conj(A_rc)
+      if (r > 0 || c > 1) bfma<false>(y[r], B.o(herm_off(r, c)), x[c]);  // A_rc x_c
+      if (r > 0) bfma<true>(y[c], B.o(herm_off(r, c)), x[r]);            // A_cr = conj(A_rc)
     }
 #pragma unroll
   for (int r = 0; r < 6; ++r) {
