@@ -568,9 +568,11 @@ int hop_full(dp_ctx* c, Workspace& w, int n, int prec, int dag, const Field& in_
     double bytes, flops;
     hop_cost(c, prec, EPI_DIAG, RED_NONE, n, &bytes, &flops);
     const std::string name = std::string("hop_") + prec_name(prec) + "_full" + (dag ? "_dag" : "");
-    // every link, clover block and input once for both parities
-    const double links = 8.0 * 18 * c->g.Vh * (prec == F64 ? 8 : prec == F32 ? 4 : 2);
-    DP_TRY(timing_end(c, ev, name, 2 * bytes - links, 2 * flops));
+    // both parities, but every link once, and every input, which is one
+    // parity's neighbour and the other's epilogue input
+    const double b = prec == F64 ? 8 : prec == F32 ? 4 : 2;
+    const double twice = (double)c->g.Vh * (144 * b + 2 * n * (24 * b + (prec == F16 ? 4 : 0)));
+    DP_TRY(timing_end(c, ev, name, 2 * bytes - twice, 2 * flops));
   }
   return DP_OK;
 }

@@ -324,3 +324,29 @@ def test_f32_hop_error(nrhs):
             e = float(((y - ref).norm() / ref.norm()).cpu())
             log(f"  dagger={dagger} relative error {e:.3e}")
             assert e < 8.35e-8, dagger
+
+
+@pytest.mark.parametrize("nrhs", [1, 5])
+def test_full_operator_counts_every_input_once(nrhs):
+    """The algorithmic bytes and flops of the full operator's launch: 72 link
+    and 72 clover reals a site once, 24 reals of every spinor in and out (FP16:
+    a scale of 4 bytes a spinor and a clover site); 1320 flops of the hop, 552
+    of the blocks and 48 of the sum."""
+    import torch
+    dims = (4, 4, 6, 4)
+    V = int(np.prod(dims))
+    log(f"test_full_operator_counts_every_input_once nrhs={nrhs}")
+    x = torch.from_numpy(synth.random_spinor(dims, 20, nrhs=nrhs).reshape(nrhs, -1)).cuda()
+    y = torch.empty_like(x)
+    with lattice(dims) as L:
+        L.set_gauge(synth.gauge_su3(dims, 0.3, 35))
+        L.set_clover(1.6)
+        L.set_mass(0.2)
+        for precision, b, sc in (("f64", 8, 0), ("f32", 4, 0), ("f16", 2, 4)):
+            L.set_timing(True)
+            L.apply_dev(x, y, precision=precision)
+            st = L.timing()[f"hop_{precision}_full"]
+            L.set_timing(False)
+            assert st["launches"] == 1
+            assert st["bytes"] == V * ((72 + 72) * b + sc + nrhs * 2 * (24 * b + sc)), precision
+            assert st["flops"] == V * nrhs * (1320 + 552 + 48), precision
