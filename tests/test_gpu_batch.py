@@ -243,3 +243,67 @@ def test_dropped_inverses_held_memory_is_bounded():
         log(f"  held after a configuration of one mass: {held / 2 ** 20:.0f} MiB")
         assert held <= one + slack
     assert free() >= before - slack
+
+
+@pytest.mark.parametrize("precision,nslots", [("f32", 8), ("f64", 13)])
+def test_batch_mass_change_shared_tile(precision, nslots):
+    """Slots that all hold one mass, then two masses, then one again, at 512
+    waves a slot (16^4), where the odd-site kernels read the common A_oo^-1 from
+    LDS (FP32 from 2 slots, FP64 from 12) and the captured iterations hold its
+    address: every column equals its solo solve bit for bit."""
+    import torch
+    import paper_1006_4028_amd as dp
+    from paper_1006_4028_amd.serve import point_columns, profile
+    dims, r = (16, 16, 16, 16), 1e-9
+    log(f"test_batch_mass_change_shared_tile {precision} nslots={nslots}")
+    U = synth.gauge_su3(dims, 0.3, 24)
+    # (mass, columns) of the requests of each wave of admissions
+    waves = [[(0.5, nslots)], [(0.2, nslots - 3), (0.5, 3)], [(0.2, nslots)]]
+    with lattice(dims) as L, lattice(dims) as L2:
+        for c in (L, L2):
+            c.set_gauge(U)
+            c.set_clover(1.6)
+        with dp.Batch(L, nslots, precision) as B:
+            for w, reqs in enumerate(waves):
+                done = []
+                for k, (M, cols) in enumerate(reqs):
+                    x0 = (2 * w + 3 * k) % dims[0]
+                    eta = torch.from_numpy(np.concatenate([point_columns(dims, (x0 + 12 * j) % dims[0], 12)
+                                                           for j in range(2)])[:cols].reshape(cols, -1)).cuda()
+                    S = torch.zeros_like(eta)
+                    alpha = profile(dims[0], 0.1, x0)
+                    assert B.admit(eta, S, M=M, alpha=alpha, r=r, x0_src=x0, tag=10 * w + k) is not None
+                    done.append((M, x0, eta, S, alpha))
+                while B.status()["free"] < nslots:
+                    B.step(3)
+                    B.harvest()
+                for M, x0, eta, S, alpha in done:
+                    L2.set_mass(M)
+                    L2.set_alpha(alpha)
+                    one = torch.empty_like(eta[0])
+                    for c in range(eta.shape[0]):
+                        L2.solve_dev(eta[c], one, r=r, precision=precision, x0_src=x0)
+                        assert torch.equal(S[c], one), (w, M, c)
+
+
+@pytest.mark.parametrize("precision,solver,ncols", [("f64", "bicgstab", 3), ("f64", "bicgstab", 13),
+                                                    ("f32", "bicgstab", 5), ("f16", "bicgstab", 3), ("f32", "cgnr", 3)])
+def test_solve_columns_partial_chunk(precision, solver, ncols):
+    """Fused dot products of the kernels that share a tile where a timeslice
+    does not fill its last chunk: a solve of several columns at 36x18x20x14
+    gives each the solution, C_PP and iteration count of its own solve."""
+    import torch
+    dims = (36, 18, 20, 14)
+    log(f"test_solve_columns_partial_chunk {precision} {solver} ncols={ncols}")
+    with lattice(dims) as L:
+        L.set_gauge(synth.gauge_su3(dims, 0.3, 25))
+        L.set_clover(1.6)
+        L.set_mass(0.5)
+        L.set_alpha(synth.alpha_exp_sym(dims[0], 0.05, 3))
+        eta = torch.cat([L.point_sources((3, 1, 2, 3), 0, 12), L.point_sources((3, 4, 0, 1), 0, 1)])[:ncols].contiguous()
+        S, one = torch.zeros_like(eta), torch.zeros_like(eta[0])
+        cpp, info = L.solve_dev(eta, S, r=1e-9, solver=solver, precision=precision, x0_src=3)
+        for k in range(ncols):
+            cpp1, info1 = L.solve_dev(eta[k], one, r=1e-9, solver=solver, precision=precision, x0_src=3)
+            assert info[k]["iters"] == info1[0]["iters"], k
+            assert torch.equal(S[k], one) and np.array_equal(cpp[k], cpp1[0]), k

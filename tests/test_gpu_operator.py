@@ -350,3 +350,35 @@ def test_full_operator_counts_every_input_once(nrhs):
             assert st["launches"] == 1
             assert st["bytes"] == V * ((72 + 72) * b + sc + nrhs * 2 * (24 * b + sc)), precision
             assert st["flops"] == V * nrhs * (1320 + 552 + 48), precision
+
+
+@pytest.mark.parametrize("precision,nrhs", [("f64", 3), ("f64", 5), ("f64", 13), ("f32", 3), ("f32", 13),
+                                            ("f16", 3), ("f16", 13)])
+def test_shared_tile_partial_chunk(precision, nrhs):
+    """The kernels that share a tile between the slots on a timeslice that does
+    not fill its last chunk (2520 sites of a parity: 24 in the last of 40; 1440
+    waves a slot, so three slots are enough), the slots in even and uneven
+    rounds of the workgroup's waves (13 over 4 or 5), with a profile in every
+    direction: bitwise the one-slot results, full, Schur and hop-only
+    operator with their adjoints; nothing is written outside the output."""
+    import torch
+    dims = (36, 18, 20, 14)
+    log(f"test_shared_tile_partial_chunk {precision} nrhs={nrhs}")
+    U = synth.gauge_su3(dims, 0.3, 36)
+    n, guard = 12 * int(np.prod(dims)), 4096
+    x = torch.from_numpy(synth.random_spinor(dims, 21, nrhs=nrhs).reshape(nrhs, -1)).cuda()
+    buf = torch.empty(nrhs * n + 2 * guard, dtype=torch.complex128, device="cuda")
+    out, one = buf[guard:-guard].view(nrhs, n), torch.empty_like(x[:1])
+    with lattice(dims) as L:
+        L.set_gauge(U)
+        L.set_clover(1.6)
+        L.set_mass(0.2)
+        L.set_beta(synth.beta_cosh_paper(dims, 0.1))
+        for kw in (dict(), dict(schur=True), dict(hop_only=True)):
+            for dagger in (False, True):
+                buf.fill_(7.0)
+                L.apply_dev(x, out, precond=True, dagger=dagger, precision=precision, **kw)
+                assert bool((buf[:guard] == 7.0).all()) and bool((buf[-guard:] == 7.0).all()), (kw, dagger)
+                for k in range(nrhs):
+                    L.apply_dev(x[k:k + 1], one, precond=True, dagger=dagger, precision=precision, **kw)
+                    assert torch.equal(out[k], one[0]), (kw, dagger, k)
