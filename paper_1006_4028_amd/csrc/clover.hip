@@ -132,11 +132,15 @@ __global__ void __launch_bounds__(128) clover_build_kernel(Geom g, const double2
                                                            double2* Ce, double2* Co) {
   const long V = 2L * g.Vh;
   // The kernel is bound by the links it fetches past the L2s (0.98 GB of 0.1 at
-  // 36x18x20x14 when neighbouring workgroups ran on different XCDs).  An XCD
-  // takes a contiguous range of sites where that keeps a timeslice's worth of
-  // links (576 B a site) near its 4 MB L2: 207 -> 181 us at 36x18x20x14 (2.9 MB a
-  // timeslice), 765 -> 677 at 48x24^3 (8 MB), but 1908 -> 2118 at 64x32^3 (19 MB).
-  const bool ranges = 2 * g.Vsh * 576L <= (8L << 20);
+  // 36x18x20x14 when neighbouring workgroups ran on different XCDs), so an XCD
+  // takes a contiguous range of sites.  Where the workgroups of an x2, x3 plane
+  // are a multiple of the XCDs, taking them in turn already gives an XCD the same
+  // rows of every plane, which is as good or better.  dp_set_clover, in turn /
+  // in ranges, us: 36x18x20x14 246 / 217, 48x24^3 896 / 805, 20x28^3 617 / 544,
+  // 16x40^3 1391 / 1204, 24x48^3 3610 / 3088; but 64x32^3 2285 / 2484, 32x16x32x32
+  // 581 / 632, 24x32x16x64 876 / 953; of two or more turns a plane, 16x24x32x64
+  // 920 / 950, 16x32x64x32 1308 / 1253; of one in a short x1, 32x4x32x32 148 / 155.
+  const bool ranges = g.L2 * g.L3 % (8 * (int)blockDim.x) != 0;
   const int tile = ranges ? xcd_tile(blockIdx.x, gridDim.x) : (int)blockIdx.x;
   const long s = (long)tile * blockDim.x + threadIdx.x;
   if (s >= V) return;
