@@ -42,7 +42,7 @@ __global__ void __launch_bounds__(64) slot_tables_kernel(const double* __restric
                                                          const void** a32, const void** a16, const float** s16,
                                                          int* x0src) {
   const int* ints = reinterpret_cast<const int*>(rec + 5 * T + 5);
-  const int s = ints[2 + blockIdx.x];
+  const int s = ints[1 + blockIdx.x];
   for (int t = threadIdx.x; t < T; t += 64) alpha[(long)s * T + t] = rec[t];
   for (int t = threadIdx.x; t < 4 * T; t += 64) ratio[(long)s * 4 * T + t] = rec[T + t];
   if (threadIdx.x == 0) {
@@ -73,9 +73,8 @@ int upload_slots(dp_batch* b, const std::vector<int>& sl) {
   std::memcpy(rec + 5 * T + 1, p, sizeof p);
   int* ints = reinterpret_cast<int*>(rec + 5 * T + 5);
   ints[0] = h.x0;
-  ints[1] = n;
   for (int j = 0; j < n; ++j) {
-    ints[2 + j] = sl[j];
+    ints[1 + j] = sl[j];
     for (int k = 0; k < 3; ++k) w.h_ainv[k][sl[j]] = p[k];
     w.h_ainv_scale[sl[j]] = static_cast<const float*>(p[3]);
   }

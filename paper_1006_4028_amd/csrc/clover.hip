@@ -352,7 +352,7 @@ __global__ void clover_apply_kernel(Geom g, SlotTable slots, SpinorRef in, Spino
   z a[12], b[12];
   SpinorIO<F64>::load(in, slot, i, g.Vp, a);
   HermBlock<double> B[2];
-  CloverIO<F64>::load(slots.ainv[slot], nullptr, i, g.Vp, B);
+  load_clover64(slots.ainv[slot], i, g.Vp, B);
   herm_apply(B[0], 0.0, &a[0], &b[0]);
   herm_apply(B[1], 0.0, &a[6], &b[6]);
   SpinorIO<F64>::store(out, slot, i, g.Vp, b);

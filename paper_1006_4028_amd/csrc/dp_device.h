@@ -400,47 +400,6 @@ __device__ __forceinline__ float raw_scale(const RawSpinor<P>& r) {
   else return 1.f;
 }
 
-// ------------------------------------------------------------ links
-
-template <int P>
-struct LinkIO;
-template <>
-struct LinkIO<F64> {
-  template <typename R, bool NT = false>
-  __device__ static __forceinline__ void load(const void* base, int mu, int i, int Vh, cx<R> (&u)[9]) {
-    const double2* b = static_cast<const double2*>(base) + (long)mu * 9 * Vh;
-#pragma unroll
-    for (int k = 0; k < 9; ++k) {
-      const double2 v = vld<NT>(at(b + (long)k * Vh, i));
-      u[k] = cx<R>{(R)v.x, (R)v.y};
-    }
-  }
-};
-template <>
-struct LinkIO<F32> {
-  template <typename R, bool NT = false>
-  __device__ static __forceinline__ void load(const void* base, int mu, int i, int Vh, cx<R> (&u)[9]) {
-    const float2* b = static_cast<const float2*>(base) + (long)mu * 9 * Vh;
-#pragma unroll
-    for (int k = 0; k < 9; ++k) {
-      const float2 v = vld<NT>(at(b + (long)k * Vh, i));
-      u[k] = cx<R>{(R)v.x, (R)v.y};
-    }
-  }
-};
-template <>
-struct LinkIO<F16> {
-  template <typename R, bool NT = false>
-  __device__ static __forceinline__ void load(const void* base, int mu, int i, int Vh, cx<R> (&u)[9]) {
-    const unsigned* b = static_cast<const unsigned*>(base) + (long)mu * 9 * Vh;
-#pragma unroll
-    for (int k = 0; k < 9; ++k) {
-      const float2 v = h2f(vld<NT>(at(b + (long)k * Vh, i)));
-      u[k] = cx<R>{(R)v.x, (R)v.y};
-    }
-  }
-};
-
 // ------------------------------------------------------------ clover blocks
 // Packed Hermitian 6x6: d[0..5] real diagonal, then o[k] for (i<j) row-major.
 
@@ -454,97 +413,24 @@ __host__ __device__ constexpr int herm_off(int i, int j) {  // i < j
   return i * 5 - (i * (i - 1)) / 2 + (j - i - 1);
 }
 
-template <int P>
-struct CloverIO;
-template <>
-struct CloverIO<F64> {
-  template <typename R>
-  __device__ static __forceinline__ void load(const void* base, const float*, int i, int Vh, HermBlock<R> (&B)[2]) {
-    const double2* b = static_cast<const double2*>(base);
+// both blocks of a site from an FP64 field
+__device__ __forceinline__ void load_clover64(const void* base, int i, int Vh, HermBlock<double> (&B)[2]) {
+  const double2* b = static_cast<const double2*>(base);
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
+  for (int h = 0; h < 2; ++h) {
 #pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        const double2 v = *at(b + (long)(h * 18 + k) * Vh, i);
-        B[h].d[2 * k] = (R)v.x;
-        B[h].d[2 * k + 1] = (R)v.y;
-      }
+    for (int k = 0; k < 3; ++k) {
+      const double2 v = *at(b + (long)(h * 18 + k) * Vh, i);
+      B[h].d[2 * k] = v.x;
+      B[h].d[2 * k + 1] = v.y;
+    }
 #pragma unroll
-      for (int k = 0; k < 15; ++k) {
-        const double2 v = *at(b + (long)(h * 18 + 3 + k) * Vh, i);
-        B[h].o[k] = cx<R>{(R)v.x, (R)v.y};
-      }
+    for (int k = 0; k < 15; ++k) {
+      const double2 v = *at(b + (long)(h * 18 + 3 + k) * Vh, i);
+      B[h].o[k] = cx<double>{v.x, v.y};
     }
   }
-};
-// FP32 and FP16 blocks also load in two steps: the stored values as floats
-// (with the FP16 per-site scale; 1 for FP32), then the block assembled from
-// them.  A copy of the raw values (in LDS) assembled the same way gives
-// bitwise the same block and the same arithmetic after it.
-template <>
-struct CloverIO<F32> {
-  template <bool NT = false>
-  __device__ static __forceinline__ float load_raw(const void* base, const float*, int i, int Vh, float (&r)[72]) {
-    const float4* b = static_cast<const float4*>(base);
-#pragma unroll
-    for (int k = 0; k < 18; ++k) {
-      const float4 v = vld<NT>(at(b + (long)k * Vh, i));
-      r[4 * k] = v.x; r[4 * k + 1] = v.y; r[4 * k + 2] = v.z; r[4 * k + 3] = v.w;
-    }
-    return 1.f;
-  }
-  template <typename R>
-  __device__ static __forceinline__ void assemble(const float (&r)[72], float, HermBlock<R> (&B)[2]) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-#pragma unroll
-      for (int k = 0; k < 6; ++k) B[h].d[k] = (R)r[36 * h + k];
-#pragma unroll
-      for (int k = 0; k < 15; ++k) B[h].o[k] = cx<R>{(R)r[36 * h + 6 + 2 * k], (R)r[36 * h + 7 + 2 * k]};
-    }
-  }
-  template <typename R>
-  __device__ static __forceinline__ void load(const void* base, const float* scale, int i, int Vh,
-                                              HermBlock<R> (&B)[2]) {
-    float r[72];
-    const float sc = load_raw(base, scale, i, Vh, r);
-    assemble(r, sc, B);
-  }
-};
-template <>
-struct CloverIO<F16> {
-  template <bool NT = false>
-  __device__ static __forceinline__ float load_raw(const void* base, const float* scale, int i, int Vh,
-                                                   float (&r)[72]) {
-    const uint4* b = static_cast<const uint4*>(base);
-#pragma unroll
-    for (int k = 0; k < 9; ++k) {
-      const uint4 v = vld<NT>(at(b + (long)k * Vh, i));
-      float2 a0 = h2f(v.x), a1 = h2f(v.y), a2 = h2f(v.z), a3 = h2f(v.w);
-      r[8 * k + 0] = a0.x; r[8 * k + 1] = a0.y; r[8 * k + 2] = a1.x; r[8 * k + 3] = a1.y;
-      r[8 * k + 4] = a2.x; r[8 * k + 5] = a2.y; r[8 * k + 6] = a3.x; r[8 * k + 7] = a3.y;
-    }
-    return vld<NT>(at(scale, i));
-  }
-  template <typename R>
-  __device__ static __forceinline__ void assemble(const float (&r)[72], float sc, HermBlock<R> (&B)[2]) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-#pragma unroll
-      for (int k = 0; k < 6; ++k) B[h].d[k] = (R)(r[36 * h + k] * sc);
-#pragma unroll
-      for (int k = 0; k < 15; ++k)
-        B[h].o[k] = cx<R>{(R)(r[36 * h + 6 + 2 * k] * sc), (R)(r[36 * h + 7 + 2 * k] * sc)};
-    }
-  }
-  template <typename R>
-  __device__ static __forceinline__ void load(const void* base, const float* scale, int i, int Vh,
-                                              HermBlock<R> (&B)[2]) {
-    float r[72];
-    const float sc = load_raw(base, scale, i, Vh, r);
-    assemble(r, sc, B);
-  }
-};
+}
 
 // y = (B + shift) x on one chirality block (components 6h .. 6h+5 of the
 // spinor); the diagonal, the largest term, is added last (the sum of the

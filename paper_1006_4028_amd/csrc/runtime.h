@@ -257,9 +257,9 @@ double now_s();
 void ratio_tables(int T, int bc_t, const double* alpha, double* out);
 int mass_entry(dp_ctx* c, double M, MassEntry** out);
 // bytes of the tables of one request on their way to n slots: alpha [T],
-// ratios [4][T], 4 + M, the A_oo^-1 pointers [3] and scale pointer, x0 and
-// column count (ints), the slot numbers (ints)
-inline size_t slot_record_bytes(int T, int n) { return sizeof(double) * (5 * T + 6) + sizeof(int) * n; }
+// ratios [4][T], 4 + M, the A_oo^-1 pointers [3] and scale pointer, x0 (int),
+// the slot numbers (ints)
+inline size_t slot_record_bytes(int T, int n) { return sizeof(double) * (5 * T + 5) + sizeof(int) * (n + 1); }
 int ensure_ws(dp_ctx* c, Workspace& w, int nslots, int prec);
 int h2d(dp_ctx* c, void* dst, const void* src, size_t bytes);
 // Waits for the work queued on the caller's stream (null: the device's default
