@@ -127,9 +127,10 @@ __host__ __device__ constexpr int red_values(int red) {
 
 // Place of value k of partial `part` of n.  Few partials lie with their values
 // side by side, one line each; many with a value's partials together, else the
-// fold of one value would read eight times its bytes through one CU.  A fold,
-// us, side by side / together: 64 partials 4.1 / 4.6, 1024 4.4 / 4.9, 5184 (mean
-// of two and seven values) 11.8 / 8.4, 16384 (one value) 14.1 / 9.2.
+// fold of one value would read eight times its bytes through one CU.  Mean fold
+// of a solve, us, side by side / together: 1024 partials 4.8 / 4.9, 5184 (one to
+// seven values) 8.8 / 6.6, 16384 (CG: one and two values) 19.6 / 8.3; with 64 they
+// differ by less than runs do (3.2 .. 4.6).
 constexpr int kSplitPartials = 2048;
 __host__ __device__ inline long partial_at(int n, int part, int k) {
   return n > kSplitPartials ? (long)k * n + part : (long)part * kRedMax + k;

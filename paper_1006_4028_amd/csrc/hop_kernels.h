@@ -26,17 +26,16 @@
 // kernels: with one slot the traffic of links and blocks; with many slots the
 // traffic of the spinors past L2 (FP64, FP32) or the instructions (FP16).
 // Multiply-adds are therefore fused ones, written out (FP32 link products but
-// for one pair, see lfma); FP16 values enter
-// the arithmetic through mixed-precision multiply-adds, which convert for
-// free; the slot and with it every base address is a scalar; links and blocks
-// stay in LDS as stored.  24^3x48, 12 slots, in the solve, odd / even sites with
-// one and with four dot products, before -> with these: FP16 250 / 320 / 347 ->
-// 186 / 227 / 237 us (2040 .. 2510 -> 1330 .. 1680 instructions a wave and slot,
-// 0.74 of the issue rate), FP32 306 / 375 / 406 -> 300 / 371 / 379 us (5.1 .. 5.6
-// TB/s fetched and written).  FP64 took two launches' worth of link reads per
-// pair of slots from L2 at one or two waves per SIMD and runs the shared-tile
-// kernel now: 784 / 992 / 999 -> 645 / 849 / 864 us (6.7 TB/s past L2, of which
-// 40% are neighbours fetched again).
+// for one pair, see lfma); FP16 values enter the arithmetic through
+// mixed-precision multiply-adds, which convert for free; the slot and with it
+// every base address is a scalar; links and blocks stay in LDS as stored.
+// 24^3x48, 12 slots, median launch of the solve, odd / even sites with one and
+// with four dot products, before -> with these: FP16 247 / 317 / 344 -> 185 / 229 /
+// 241 us (2040 .. 2510 -> 1330 .. 1680 instructions a wave and slot, 0.74 of the
+// issue rate), FP32 305 / 373 / 402 -> 297 / 368 / 376 us (5.1 .. 5.6 TB/s fetched
+// and written).  FP64 read its links from L2 once per slot (even sites) or pair
+// of slots, and now once per launch (shared tile, the common blocks in LDS too):
+// 787 / 1007 / 1011 -> 637 / 804 / 809 us.
 #pragma once
 #include <algorithm>
 #include <cstdlib>
@@ -724,14 +723,15 @@ __device__ __forceinline__ void slot_work(const HopArgs& a, int slot, const Site
 // ------------------------------------------------------------ kernels
 
 // Neighbours in flight (ring depth) and waves per SIMD the registers must
-// allow, per precision.  Measured on MI355X, even / odd sites, us:
-//   one slot, 32^3x64: FP64 1 neighbour 505 / 500, 2: 496 / 487, 3 at one
-//   wave: 487 / 459; FP32 2 at three waves 243 / 230, 3 at three 244 / 219, 4 at
-//   two 248 / 230, 6: 274 / 261; FP16 1 to 8: 131 .. 134 / 120 .. 125;
-//   12 slots, 24^3x48: FP64 1 or 2: 750 / 680, 3 (spills): 854 / 765; FP32 2: 336 /
-//   346, 3: 340 / 334, 4: 349 / 343, 6: 340 / 336; FP16 2: 208 / 208, 4: 212 / 213, 8:
-//   244 / 226.
-// Neither depth nor waves matter much: the kernels are bound by what the L2
+// allow, per precision.  Even / odd sites, us, by depth at the waves below:
+//   hop_kernel_slab, one slot, 32^3x64: FP64 1: 510 / 507, 2: 501 / 496, 3: 486 /
+//   489, 4: 480 / 484, 6 (spills): 818 / 878; FP32 1: 250 / 231, 2 or 3: 243 / 228, 4
+//   (spills): 369 / 326; FP16 1 to 6: 132 .. 134 / 123 .. 127;
+//   hop_kernel_shared, 12 slots, 24^3x48, the operator by itself: FP64 1: 682 /
+//   679, 2: 679 / 667, 3 (spills): 783 / 790; FP32 1: 330 / 340, 2: 331 / 342, 3:
+//   337 / 329, 4: 340 / 340, 6: 337 / 346; FP16 1: 219 / 203, 2: 204 / 204, 3: 203 /
+//   207, 4: 207 / 209, 6: 213 / 223.
+// Without spills the depth matters little: the kernels are bound by what the L2
 // fetches (FP64, FP32) or by instruction issue (FP16).  Fetching the next
 // slot's first neighbours during the epilogue was 5-20% slower.
 constexpr int slab_pf(int p) { return p == F64 ? 3 : p == F32 ? 2 : 4; }
@@ -922,10 +922,13 @@ hipError_t launch_one(const HopArgs& a, hipStream_t st, int* nparts_out) {
     // beside the links (110 KB) only with one workgroup per CU instead of two,
     // of six waves: worth it from so many slots on.  Even sites (C), 48x24^3 /
     // 16^3x32, us without and with: 4 slots 312 / 56.1 and 293 / 58.2, 5: 401 / 73.0
-    // and 357 / 72.8, 8: 548 / 107.7 and 500 / 95.8, 12: 775 / 152.8 and 719 / 137.6;
-    // odd sites (A^-1): 8: 496 / 99.0 and 522 / 94.6, 10: 603 / 121 and 636 / 116, 12:
-    // 703 / 133 and 735 / 130 (588 and 579 within a solve), 24: 1347 / 281 and
-    // 1202 / 250.
+    // and 357 / 72.8, 8: 548 / 107.7 and 500 / 95.8, 12: 775 / 152.8 and 719 / 137.6.
+    // Odd sites (A^-1) follow an even-site kernel that has them in LDS; a whole
+    // solve, ms without and with: 48x24^3 8 columns 75.9 and 77.1, 10: 94.8 and
+    // 95.7, 11: 103.4 and 103.6, 12: 110.1 and 109.4, 14: 126.3 and 124.4, 24: 211.7
+    // and 205.9; 36x18x20x14 8: 19.85 and 20.57, 11: 26.7 and 26.8, 12: 28.6 and
+    // 28.4, 24: 53.9 and 52.6; 16^3x32 8: 14.0 and 14.3, 12: 19.9 and 20.0, 18: 28.6
+    // and 28.2, 24: 37.3 and 36.3.
     const bool blk = (diag || (inv && a.slots.ainv_common)) && (P != F64 || a.nslots >= (diag ? 5 : 12));
     // waves per workgroup: the fewest rounds over the slots
     const int maxw = shared_threads(P, blk) / 64, rounds = (a.nslots + maxw - 1) / maxw;

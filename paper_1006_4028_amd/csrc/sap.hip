@@ -629,7 +629,7 @@ __device__ __forceinline__ void bl_mr_step(cx<float> w, const cx<float> (&av)[12
 // applied to the spinor at x - mu, which the thread of x - mu forms with its
 // own link.  Two workgroups per CU.  (One with the clover blocks read again in
 // each step, four directions through LDS: 426 us a pass at 64x32^3 with 4^4
-// blocks, 2.8 GB past L2, half of the vector issue; this one 343 us, 1.2 GB,
+// blocks, 2.8 GB past L2, half of the vector issue; this one 348 us, 1.2 GB,
 // 0.64 of the issue.)  Workgroups of an XCD take neighbouring blocks, which read
 // the same faces.
 __host__ __device__ inline size_t sap_slice_lds(int nt) { return sizeof(float4) * (9 + 6) * (size_t)nt; }
@@ -905,7 +905,7 @@ __global__ void __launch_bounds__(kSapThreads, 2) sap_block_kernel(SapPass a) {
 // D'_B rho and psi stay in registers, the links and clover blocks (1.1 MB for
 // 6^4 sites) are read again in each step.  (With D'_B rho and psi in memory
 // between the phases of a step: 262 us a pass at 48x24^3 with 6^4 blocks, 5.4 kB
-// a site at 5.7 TB/s; this one 229 us, 3.6 kB at 5.1 TB/s.)
+// a site at 5.7 TB/s; this one 230 us, 3.6 kB at 5.1 TB/s.)
 constexpr int kSapBigThreads = 512;
 constexpr int kSapBigPer = 3;
 constexpr int kSapBigSites = kSapBigThreads * kSapBigPer;
@@ -1088,8 +1088,11 @@ constexpr int kDotBlocks = 1024;
 // one, which also takes the new vector's norm and its product with the
 // residual (classical Gram-Schmidt within a group, modified between groups):
 // 2 k + 7 vector passes for the k-th vector against 4 k + 7 one coefficient at
-// a time.  The earlier vectors stay unnormalised, their squared norms enter
-// the coefficients.  A vector is 24 component rows (2 parities) of Vh entries,
+// a time.  No solve needs more iterations for it: restart lengths 16, 40 and
+// 64, residues 1e-10 and 1e-13, masses from 0.05 to where 600 iterations do not
+// converge, strong and weak preconditioners, 16x8^3 and 32x16^3, all counts equal.
+// The earlier vectors stay unnormalised, their squared norms enter the
+// coefficients.  A vector is 24 component rows (2 parities) of Vh entries,
 // Vp apart; blockIdx.y is the row, so neighbouring threads and loop steps read
 // neighbouring entries of every vector.
 
