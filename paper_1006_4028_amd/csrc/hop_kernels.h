@@ -734,15 +734,17 @@ __device__ __forceinline__ void slot_work(const HopArgs& a, int slot, const Site
 // Without spills the depth matters little: the kernels are bound by what the L2
 // fetches (FP64, FP32) or by instruction issue (FP16).  Fetching the next
 // slot's first neighbours during the epilogue was 5-20% slower.
-constexpr int slab_pf(int p) { return p == F64 ? 3 : p == F32 ? 2 : 4; }
+constexpr int slab_pf(int p, int waves) { return p == F64 ? (waves == 1 ? 3 : 2) : p == F32 ? 2 : 4; }
 constexpr int slab_min_waves(int p) { return p == F64 ? 1 : 3; }
 constexpr int shared_pf(int p) { return p == F32 ? 3 : 2; }
 constexpr int shared_threads(int p, bool blk) { return p == F64 && blk ? 384 : 256; }
 constexpr int kSharedMinWaves = 2;
 
+constexpr int kCus = 256, kSimds = 4 * kCus;
 // Up to so many waves, one per (chunk, timeslice, slot), several slots run as
-// one wave each too: a shared-tile workgroup would leave CUs without work and
-// take its slots one after the other.  Even / odd sites, us, one wave per slot
+// one wave each too (FP64 in some cases beyond, see one_wave_per_slot): a
+// shared-tile workgroup would leave CUs without work and take its slots one
+// after the other.  Even / odd sites, us, one wave per slot
 // against shared tile: 768 waves (8^3x16, 12 slots) FP64 14.8 / 15.0 against
 // 28.6 / 25.0, FP32 10.6 / 10.4 against 17.9 / 19.2, FP16 9.1 / 9.5 against
 // 17.1 / 17.3; 1344 waves (12^3x24, 4 slots) FP64 28.4 / 26.9 against 26.3 / 22.9,
@@ -780,9 +782,9 @@ __device__ __forceinline__ int xcd_item(HopArgs& a) {
 }
 
 // One wave per (chunk, timeslice, slot), the slots of a chunk in neighbouring
-// blocks of the same XCD.
-template <int P, int EPIL, int RED, bool DAG>
-__global__ void __launch_bounds__(64, slab_min_waves(P)) hop_kernel_slab(HopArgs a, SlabMap m) {
+// blocks of the same XCD; W waves per SIMD.
+template <int P, int EPIL, int RED, bool DAG, int W>
+__global__ void __launch_bounds__(64, W) hop_kernel_slab(HopArgs a, SlabMap m) {
   constexpr int EPI = site_epi(EPIL);
   const int j = xcd_item<EPIL>(a), jj = j / a.nslots, slot = j - jj * a.nslots;
   const Item it = map_item(m, a.g.T, blockIdx.x & 7, jj, EPI == EPI_DIAG);
@@ -793,7 +795,7 @@ __global__ void __launch_bounds__(64, slab_min_waves(P)) hop_kernel_slab(HopArgs
   locate(a, m, it.x0, valid ? sp : 0, s);
   s.sp0 = it.chunk * 64;
   if constexpr (EPIL == EPI_FULL_HOST) s.odd = __ballot((a.p + it.x0 + s.x1 + s.x2) & 1);
-  slot_work<P, EPIL, RED, slab_pf(P), DAG, false, false>(a, slot, s, it.x0, valid, it.x0 * m.nch + it.chunk,
+  slot_work<P, EPIL, RED, slab_pf(P, W), DAG, false, false>(a, slot, s, it.x0, valid, it.x0 * m.nch + it.chunk,
                                                         a.g.T * m.nch, nullptr, nullptr, threadIdx.x);
 }
 
@@ -889,6 +891,35 @@ unsigned recip32(int d) {
   return (unsigned)std::min<unsigned long long>(m, 0xffffffffULL);
 }
 
+// The slots of a launch as one wave each, or sharing a tile (see slab_max_waves).
+// FP64 launches of one parity beyond that limit: with at most half as many tiles
+// as CUs the slots stay waves of their own, and also up to two waves a SIMD
+// unless the tiles fill the CUs evenly (512 workgroups run at once, 256 with the
+// blocks in LDS).  Schur operator, both kernels, us, waves of their own (two a
+// SIMD, see fp64_two_waves) against shared: 64 tiles (2x16^3) 24 slots 45 / 80, 32:
+// 56 / 101; 80 (10^4) 16: 46 / 65, 24: 62 / 92; 96 (24x8^3) 32: 77 / 108; 112 (8x12^3)
+// 12: 47 / 54, 32: 95 / 115; 128 (4x16^3) 16: 56 / 62, 32: 100 / 111; but 140 (10x12^3)
+// 16: 74 / 66.  280 (20x12^3) 4: 43 / 49; 576 (18x16^3) 2: 47 / 62; 768 (24x16^3) 2: 58 /
+// 68; 336 (24x12^3) 6: 58 / 64; tiles that fill the CUs: 256 (8x16^3) 6: 47 / 45, 512
+// (16^4) 3: 53 / 50.
+template <int P, bool FULL>
+bool one_wave_per_slot(int items, int nslots) {
+  const long waves = (long)items * nslots;
+  if (nslots == 1 || waves <= slab_max_waves(P)) return true;
+  if (P != F64 || FULL) return false;
+  return 2 * items <= kCus || (waves < 2 * kSimds && items % (nslots >= 5 ? kCus : 2 * kCus) != 0);
+}
+
+// FP64 waves of their own: registers for two a SIMD (a shorter ring) where one a
+// SIMD would need a second, mostly empty round.  Schur operator, us, one / two a
+// SIMD: one slot 1080 waves 65.9 / 58.1, 1280 75.0 / 68.7, 1536 86.4 / 82.9, but 1792
+// 98.0 / 98.0 and 2048 107 / 116; several slots 1120 50 / 41, 1280 60 / 50, 1792 61 /
+// 54 (112 tiles) and 66 / 67 (896), 2016 61 / 58, 2304 73 / 69.  Full operator: one slot
+// 1152 waves 32 / 27, 1536 36 / 35; several 1536 28 .. 31 / 23 .. 26.
+inline bool fp64_two_waves(long waves, int nslots) {
+  return waves > kSimds && (nslots > 1 || 2 * waves <= 3 * kSimds);
+}
+
 template <int P, int EPI, int RED, bool DAG>
 hipError_t launch_one(const HopArgs& a, hipStream_t st, int* nparts_out) {
   SlabMap m;
@@ -916,7 +947,8 @@ hipError_t launch_one(const HopArgs& a, hipStream_t st, int* nparts_out) {
   else m.tmap = P != F64 && (a.nslots == 1 || P == F16) ? 1 : 0;
   const int nblocks = (m.tmap ? 8 * m.tlen * m.nch : 8 * a.g.T * m.maxc) * (EPI == site_epi(EPI) ? 1 : 2);
   *nparts_out = a.g.T * m.nch;
-  if (a.nslots >= 2 && (long)a.g.T * m.nch * a.nslots > slab_max_waves(P)) {
+  constexpr bool full = EPI != site_epi(EPI);
+  if (!one_wave_per_slot<P, full>(a.g.T * m.nch, a.nslots)) {
     constexpr bool inv = EPI == EPI_INV || EPI == EPI_INV_SUB, diag = site_epi(EPI) == EPI_DIAG;
     // The slots' common blocks in LDS, where there are such.  FP64 blocks fit
     // beside the links (110 KB) only with one workgroup per CU instead of two,
@@ -943,7 +975,14 @@ hipError_t launch_one(const HopArgs& a, hipStream_t st, int* nparts_out) {
       if (!done)
         hipLaunchKernelGGL((hop_kernel_shared<P, EPI, RED, DAG, false>), grid, block, shared_tile_bytes<P>(false), st, a, m);
   } else {
-    hipLaunchKernelGGL((hop_kernel_slab<P, EPI, RED, DAG>), dim3(nblocks * a.nslots), dim3(64), 0, st, a, m);
+    const dim3 grid(nblocks * a.nslots);
+    bool done = false;
+    if constexpr (P == F64)
+      if (fp64_two_waves((long)a.g.T * m.nch * a.nslots * (full ? 2 : 1), a.nslots)) {
+        hipLaunchKernelGGL((hop_kernel_slab<P, EPI, RED, DAG, 2>), grid, dim3(64), 0, st, a, m);
+        done = true;
+      }
+    if (!done) hipLaunchKernelGGL((hop_kernel_slab<P, EPI, RED, DAG, slab_min_waves(P)>), grid, dim3(64), 0, st, a, m);
   }
   return hipGetLastError();
 }

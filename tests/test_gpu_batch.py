@@ -307,3 +307,25 @@ def test_solve_columns_partial_chunk(precision, solver, ncols):
             cpp1, info1 = L.solve_dev(eta[k], one, r=1e-9, solver=solver, precision=precision, x0_src=3)
             assert info[k]["iters"] == info1[0]["iters"], k
             assert torch.equal(S[k], one) and np.array_equal(cpp[k], cpp1[0]), k
+
+
+@pytest.mark.parametrize("solver", ["bicgstab", "cgnr"])
+def test_solve_columns_two_waves_per_simd(solver):
+    """Fused dot products where FP64 slots are waves of their own, two a SIMD (13
+    columns at 10^4: 1040 waves): each column's solution, C_PP and iteration
+    count are those of its own solve."""
+    import torch
+    dims = (10, 10, 10, 10)
+    log(f"test_solve_columns_two_waves_per_simd {solver}")
+    with lattice(dims) as L:
+        L.set_gauge(synth.gauge_su3(dims, 0.3, 26))
+        L.set_clover(1.6)
+        L.set_mass(0.5)
+        L.set_alpha(synth.alpha_exp_sym(dims[0], 0.05, 3))
+        eta = torch.cat([L.point_sources((3, 1, 2, 3), 0, 12), L.point_sources((3, 4, 0, 1), 0, 1)]).contiguous()
+        S, one = torch.zeros_like(eta), torch.zeros_like(eta[0])
+        cpp, info = L.solve_dev(eta, S, r=1e-9, solver=solver, precision="f64", x0_src=3)
+        for k in range(eta.shape[0]):
+            cpp1, info1 = L.solve_dev(eta[k], one, r=1e-9, solver=solver, precision="f64", x0_src=3)
+            assert info[k]["iters"] == info1[0]["iters"], k
+            assert torch.equal(S[k], one) and np.array_equal(cpp[k], cpp1[0]), k

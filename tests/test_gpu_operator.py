@@ -382,3 +382,67 @@ def test_shared_tile_partial_chunk(precision, nrhs):
                 for k in range(nrhs):
                     L.apply_dev(x[k:k + 1], one, precond=True, dagger=dagger, precision=precision, **kw)
                     assert torch.equal(out[k], one[0]), (kw, dagger, k)
+
+
+@pytest.mark.parametrize("dims,nrhs", [((10, 10, 10, 10), 8), ((10, 10, 10, 10), 13), ((10, 10, 10, 10), 26),
+                                       ((36, 14, 14, 12), 2), ((60, 14, 14, 12), 2)])
+def test_f64_two_waves_per_simd(dims, nrhs):
+    """FP64 slots as waves of their own, two a SIMD: launches of more than 1024
+    waves with 80 (timeslice, chunk) tiles at any slot count (10^4: 52 sites in
+    the last chunk of 8; 13 slots of one parity, 8 of both), and with more tiles
+    (684: two slots; 1140: one slot, and two slots that share a tile).  Bitwise
+    the one-slot results, full, Schur and hop-only operator with their
+    adjoints; nothing is written outside the output."""
+    import torch
+    log(f"test_f64_two_waves_per_simd {dims} nrhs={nrhs}")
+    U = synth.gauge_su3(dims, 0.3, 37)
+    n, guard = 12 * int(np.prod(dims)), 4096
+    x = torch.from_numpy(synth.random_spinor(dims, 22, nrhs=nrhs).reshape(nrhs, -1)).cuda()
+    buf = torch.empty(nrhs * n + 2 * guard, dtype=torch.complex128, device="cuda")
+    out, one = buf[guard:-guard].view(nrhs, n), torch.empty_like(x[:1])
+    with lattice(dims) as L:
+        L.set_gauge(U)
+        L.set_clover(1.6)
+        L.set_mass(0.2)
+        L.set_beta(synth.beta_cosh_paper(dims, 0.1))
+        for kw in (dict(), dict(schur=True), dict(hop_only=True)):
+            for dagger in (False, True):
+                buf.fill_(7.0)
+                L.apply_dev(x, out, precond=True, dagger=dagger, **kw)
+                assert bool((buf[:guard] == 7.0).all()) and bool((buf[-guard:] == 7.0).all()), (kw, dagger)
+                for k in range(nrhs):
+                    L.apply_dev(x[k:k + 1], one, precond=True, dagger=dagger, **kw)
+                    assert torch.equal(out[k], one[0]), (kw, dagger, k)
+
+
+@pytest.mark.parametrize("dims,nrhs,dims0,nrhs0", [((2, 16, 16, 16), 24, (2, 16, 16, 16), 16),
+                                                   ((10, 10, 10, 10), 16, (10, 10, 10, 10), 12),
+                                                   ((18, 16, 16, 16), 2, (16, 16, 16, 16), 2),
+                                                   ((36, 16, 16, 16), 1, (32, 16, 16, 16), 1)])
+def test_f64_operator_time_follows_the_work(dims, nrhs, dims0, nrhs0):
+    """Just beyond the 1024 waves that run at once, one a SIMD, the FP64 Schur
+    operator takes no step in time: it grows by at most 10% more than the work
+    (13 to 50% here), where one wave a SIMD or a few shared tiles took 17 to 68%
+    more."""
+    import torch
+    log(f"test_f64_operator_time_follows_the_work {dims} x {nrhs} against {dims0} x {nrhs0}")
+
+    def us(d, n):
+        x = torch.from_numpy(synth.random_spinor(d, 23).reshape(1, -1)).cuda().repeat(n, 1)
+        y = torch.empty_like(x)
+        best = np.inf
+        with lattice(d) as L:
+            L.set_gauge(synth.gauge_su3(d, 0.3, 38))
+            L.set_mass(0.5)
+            for _ in range(4):
+                L.set_timing(True)
+                for _ in range(40):
+                    L.apply_dev(x, y, precond=True, schur=True)
+                best = min(best, sum(np.median(L.timing_samples(f"hop_f64_{q}")) for q in ("inv", "diag")))
+                L.set_timing(False)
+        return 1e3 * best
+
+    t, t0 = us(dims, nrhs), us(dims0, nrhs0)
+    work = np.prod(dims) * nrhs / (np.prod(dims0) * nrhs0)
+    log(f"  {t0:.1f} -> {t:.1f} us, work x {work:.3f}, time x {t / t0:.3f}")
+    assert t / t0 <= 1.1 * work
